@@ -16,6 +16,7 @@
 
 #include "nsgc.h"
 #include "nsgc_anon.hpp"
+#include "nsgc_grid.hpp"
 #include "nsgc_large.hpp"
 #include "nsgc_planner.hpp"
 
@@ -144,6 +145,7 @@ int get_ctx(DevCtx** out) {
       per_cu > 0)
     c->lds_limit = std::max(c->lds_limit, size_t(per_cu));
   NSGC_HIP(allow_large_lds(c->lds_limit));
+  NSGC_HIP(grid_allow_large_lds(c->lds_limit));
   g_devs[dev] = c;
   *out = c;
   return NSGC_OK;
@@ -217,7 +219,13 @@ struct Launch {
   size_t lds_small, lds_part, lds_link, lds_rc, lds_rce;
   size_t lds_linkw[2][2];
   uint32_t max_link_buckets, max_rc_buckets;
+  // grid windows: heavy sample, partition by tile size (2^11 ..), link
+  // aggregation of small / big cells, row/column aggregation
+  uint32_t gheavy, gpart[4], glinks[2], gwide, gover, grc;
+  size_t lds_grc;
 };
+
+constexpr int kGridKernels = 16;   // kernel numbers of nsgc_grid.hip start here
 
 // Workgroups per CU that can actually be resident (registers and LDS), at
 // most `want`: persistent workgroups beyond that would only queue.
@@ -226,7 +234,8 @@ int resident_cap(DevCtx* c, int which, uint32_t tile_log2, size_t lds, int want,
   auto it = c->resident.find(key);
   if (it == c->resident.end()) {
     int n = 0;
-    NSGC_HIP(resident_blocks(which, tile_log2, lds, &n));
+    NSGC_HIP(which >= kGridKernels ? grid_resident_blocks(which - kGridKernels, tile_log2, lds, &n)
+                                   : resident_blocks(which, tile_log2, lds, &n));
     it = c->resident.emplace(key, std::max(n, 1)).first;
   }
   *grid = uint32_t(c->cus) * uint32_t(std::min(want, it->second));
@@ -264,6 +273,19 @@ int launch_params(DevCtx* c, const nsgc_tune& t, Launch* out) {
       if ((rc = resident_cap(c, r ? 7 : 5, tile, L.lds_linkw[k][r], 4 * want, &L.grid_linkw[k][r])) !=
           NSGC_OK)
         return rc;
+  // grid windows: as many workgroups as fit (their kernels are sized for it)
+  L.lds_grc = lds_grid_rc_bytes(uint32_t(t.rc_slots_log2));
+  if (std::max(L.lds_grc, lds_grid_part_bytes(14, grid_max_cells(14))) > c->lds_limit) return NSGC_ERR_INVALID_ARG;
+  L.gheavy = uint32_t(c->cus) * 2;
+  L.gwide = uint32_t(c->cus);
+  L.gover = uint32_t(c->cus) * 3;
+  for (uint32_t k = 0; k < 4; ++k)
+    if ((rc = resident_cap(c, kGridKernels, 11 + k, lds_grid_part_bytes(11 + k, grid_max_cells(11 + k)), 16,
+                           &L.gpart[k])) != NSGC_OK)
+      return rc;
+  for (int k = 0; k < 2; ++k)
+    if ((rc = resident_cap(c, kGridKernels + 1 + k, 0, 0, 16, &L.glinks[k])) != NSGC_OK) return rc;
+  if ((rc = resident_cap(c, kGridKernels + 3, 0, L.lds_grc, 16, &L.grc)) != NSGC_OK) return rc;
   L.grid_finish = uint32_t(c->cus) * 4;
   L.grid_heavy = uint32_t(c->cus);   // one workgroup per row-complete window
   // the entity outputs' phase C (two tables per workgroup)
@@ -279,12 +301,14 @@ int launch_params(DevCtx* c, const nsgc_tune& t, Launch* out) {
 // Which kernels a plan needs: bit 0 the small-window kernel, bit 1 phases A
 // and C, bit 2 phase B by workgroups, bit 3 phase B by wavefronts, bit 4 the
 // wavefront kernel's larger counters (see wave_class), bit 5 row-complete
-// windows (the heavy-source sample and the wavefront kernel's row tables).
-constexpr int kVariants = 64;
+// windows (the heavy-source sample and the wavefront kernel's row tables),
+// bits 6 and 7 grid windows of small and of big cells, bits 8-9 their tile.
+constexpr int kVariants = 1024;
 int plan_variant(const HostPlan& hp) {
   return (hp.small.empty() ? 0 : 1) | (hp.win.empty() ? 0 : 2) | (hp.itemsBb ? 4 : 0) |
          (hp.itemsBw ? 8 : 0) | (hp.itemsBw && wave_class(hp.wave_rc_max) ? 16 : 0) |
-         (hp.num_rows ? 32 : 0);
+         (hp.num_rows ? 32 : 0) | (hp.gitemsS ? 64 : 0) | (hp.gitemsB > hp.gitemsS ? 128 : 0) |
+         (hp.gitemsB ? int(hp.gtile_log2 - 11) << 8 : 0);
 }
 
 // Enqueue the kernels of one uploaded plan.  With `fixed_grid` (graph
@@ -310,15 +334,30 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
   const bool linkb = fixed_grid ? (variant & 4) != 0 : hp.itemsBb > 0;
   const bool linkw = fixed_grid ? (variant & 8) != 0 : hp.itemsBw > 0;
   const bool rows = fixed_grid ? (variant & 32) != 0 : hp.num_rows > 0;
+  const bool gsmall = fixed_grid ? (variant & 64) != 0 : hp.gitemsS > 0;
+  const bool gbig = fixed_grid ? (variant & 128) != 0 : hp.gitemsB > hp.gitemsS;
+  const uint32_t gtile = fixed_grid ? uint32_t(variant >> 8) + 11 : hp.gtile_log2;
   NSGC_HIP(mark(0));
   if (small)
     NSGC_HIP(launch_small(dplan, grid(uint32_t(hp.small.size()), L.grid_small), L.lds_small, s));
   NSGC_HIP(mark(1));
   if (rows) NSGC_HIP(launch_heavy(dplan, grid(uint32_t(hp.win.size()), L.grid_heavy), s));
+  if (gsmall || gbig) {
+    NSGC_HIP(launch_grid_heavy(dplan, gtile, grid(uint32_t(hp.gwin.size()), L.gheavy), s));
+    NSGC_HIP(launch_grid_partition(dplan, gtile, grid_max_cells(gtile),
+                                   grid(hp.gitemsA, L.gpart[gtile - 11]), s));
+  }
   if (part)
     NSGC_HIP(launch_partition(dplan, tile_log2, L.max_link_buckets, rows, grid(hp.itemsA, L.grid_part),
                               L.lds_part, s));
   NSGC_HIP(mark(2));
+  if (gbig)
+    NSGC_HIP(launch_grid_links(dplan, 1, grid(hp.gitemsB - hp.gitemsS, L.glinks[1]), s));
+  if (gsmall) NSGC_HIP(launch_grid_links(dplan, 0, grid(hp.gitemsS, L.glinks[0]), s));
+  // what these leave over is known on the device only: small persistent grids
+  // (small cells alone are left over too seldom to be worth the wide pass)
+  if (gbig) NSGC_HIP(launch_grid_links(dplan, 2, grid(hp.gitemsB, L.gwide), s));
+  if (gsmall || gbig) NSGC_HIP(launch_grid_rounds(dplan, gbig, grid(hp.gitemsB, L.gover), s));
   // The phase-C order depends only on the partition's sizes: with wavefront
   // phase-B items it is computed by an extra workgroup of that kernel, beside
   // phase B, instead of by k_order after it.
@@ -334,13 +373,18 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
     NSGC_HIP(launch_links(dplan, L.combine && !hp.entity, L.max_rc_buckets,
                           grid(hp.itemsBb, L.grid_link), L.lds_link, s));
   NSGC_HIP(mark(3));
+  if (gsmall || gbig) {
+    NSGC_HIP(launch_grid_rowcol(dplan, grid(hp.gitemsC, L.grc), L.lds_grc, s));
+    NSGC_HIP(launch_grid_sweeps(dplan, grid(hp.gitemsC, L.gover), L.lds_grc, s));
+  }
   if (part && hp.entity) {
     NSGC_HIP(launch_rowcol_ent(dplan, grid(hp.itemsC, L.grid_rce), L.lds_rce, s));
   } else if (part) {
     if (!order_in_b) NSGC_HIP(launch_order(dplan, s));
     NSGC_HIP(launch_rowcol(dplan, grid(hp.itemsC, L.grid_rc), L.lds_rc, s));
   }
-  if (part) NSGC_HIP(launch_finish(dplan, grid(uint32_t(hp.win.size()), L.grid_finish), s));
+  if (part || gsmall || gbig)
+    NSGC_HIP(launch_finish(dplan, grid(uint32_t(hp.win.size() + hp.gwin.size()), L.grid_finish), s));
   NSGC_HIP(mark(4));
   if (!hp.large.empty()) {
     if (!la) return NSGC_ERR_INTERNAL;
@@ -424,6 +468,7 @@ size_t workspace_bound(int64_t max_packets, int64_t max_windows, const nsgc_tune
   size_t b = size_t(P * 24 + (tilemeta + lbmeta + 2 * items) * 4 + (bitems + items) * 16 + 10 * 256);
   // row-complete windows: source totals per phase-B item and a heavy table per window
   if (t.row_complete) b += size_t(bitems * 16 + W * NSGC_HEAVY_SLOTS * 4 + 2 * 256);
+  b += grid_workspace_bound(max_packets, max_windows, t);
   // a large window's region comes on top of the partitioned windows' regions
   if (large && t.large_min_log2 < 33 && P >= (uint64_t(1) << t.large_min_log2))
     b += large_window_bytes(P) + 256;
@@ -566,6 +611,10 @@ int run_fixed_scratch(const uint32_t* src, const uint32_t* dst, const int64_t* w
   }
   HostPlan hp;
   if ((rc = make_plan(window_offsets, num_windows, t, &hp)) != NSGC_OK) return rc;
+  if (!hp.gwin.empty() && (hp.plan_bytes() > plan_cap || hp.layout().total > ws_cap)) {
+    // grid windows take more workspace beside the keys than the other form
+    if ((rc = make_plan(window_offsets, num_windows, t, &hp, false, true, false)) != NSGC_OK) return rc;
+  }
   const size_t pbytes = hp.plan_bytes();
   const WsLayout lay = hp.layout();
   if (pbytes > plan_cap || lay.total > ws_cap) return NSGC_ERR_TOO_LARGE;
@@ -876,11 +925,11 @@ int nsgc_plan_inspect(const int64_t* window_offsets, int64_t num_windows, int32_
   for (int64_t w = 0; w < num_windows; ++w) {
     if (tier) tier[w] = hp.tier[size_t(w)];
     const bool part = hp.tier[size_t(w)] == 2;
-    const nsgc_win_desc* d = part ? &hp.win[m] : nullptr;
+    const PartShape* d = part ? &hp.shape[m] : nullptr;
     if (log2_link_buckets) log2_link_buckets[w] = d ? d->logB : -1;
     if (log2_row_buckets) log2_row_buckets[w] = d ? d->logR : -1;
     if (log2_col_buckets) log2_col_buckets[w] = d ? d->logC : -1;
-    if (tiles) tiles[w] = d ? int64_t(d->ntiles) : 0;
+    if (tiles) tiles[w] = d ? d->tiles : 0;
     if (part) ++m;
   }
   if (workspace_bytes) *workspace_bytes = int64_t(hp.layout().total);

@@ -250,6 +250,16 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan_shfl(uint32_t v) {
 
 // ---- block primitives -----------------------------------------------------
 
+// Barrier that orders LDS accesses only: global loads and stores stay in
+// flight across it (__syncthreads waits for the stores to be acknowledged and
+// for the loads to arrive).  For code whose threads do not read each other's
+// global stores.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Block-wide sum and max of per-thread values; every thread gets the result.
 // `red` is LDS scratch of 2*WAVES words.
 __device__ __forceinline__ void block_sum_max(uint32_t& sum, uint32_t& mx, uint32_t* red) {
@@ -273,25 +283,26 @@ __device__ __forceinline__ void block_sum_max(uint32_t& sum, uint32_t& mx, uint3
 }
 
 // Sums of a and b and the max of m over the block, valid in thread 0 only
-// (one barrier).  `red` (3*WAVES words) must not be reused before the block
+// (one barrier; a block of NW wavefronts).  `red` (3 * NW words) must not be reused before the block
 // has passed another barrier.
+template <int NW = WAVES>
 __device__ __forceinline__ void block_sum2_max_to0(uint32_t& a, uint32_t& b, uint32_t& m,
                                                    uint32_t* red) {
   const uint32_t sa = wave_sum(a), sb = wave_sum(b), sm = wave_max(m);
   const uint32_t w = threadIdx.x >> 6;
   if (lane_id() == 0) {
     red[w] = sa;
-    red[WAVES + w] = sb;
-    red[2 * WAVES + w] = sm;
+    red[NW + w] = sb;
+    red[2 * NW + w] = sm;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t ta = 0, tb = 0, tm = 0;
 #pragma unroll
-    for (int k = 0; k < WAVES; ++k) {
+    for (int k = 0; k < NW; ++k) {
       ta += red[k];
-      tb += red[WAVES + k];
-      tm = max(tm, red[2 * WAVES + k]);
+      tb += red[NW + k];
+      tm = max(tm, red[2 * NW + k]);
     }
     a = ta;
     b = tb;
@@ -301,23 +312,24 @@ __device__ __forceinline__ void block_sum2_max_to0(uint32_t& a, uint32_t& b, uin
 
 // The sum of s and the maxima of m1 and m2 over the block, valid in thread 0
 // only (one barrier; same reuse rule for `red` as above).
+template <int NW = WAVES>
 __device__ __forceinline__ void block_sum_max2_to0(uint32_t& s, uint32_t& m1, uint32_t& m2,
                                                    uint32_t* red) {
   const uint32_t ss = wave_sum(s), s1 = wave_max(m1), s2 = wave_max(m2);
   const uint32_t w = threadIdx.x >> 6;
   if (lane_id() == 0) {
     red[w] = ss;
-    red[WAVES + w] = s1;
-    red[2 * WAVES + w] = s2;
+    red[NW + w] = s1;
+    red[2 * NW + w] = s2;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t ts = 0, t1 = 0, t2 = 0;
 #pragma unroll
-    for (int k = 0; k < WAVES; ++k) {
+    for (int k = 0; k < NW; ++k) {
       ts += red[k];
-      t1 = max(t1, red[WAVES + k]);
-      t2 = max(t2, red[2 * WAVES + k]);
+      t1 = max(t1, red[NW + k]);
+      t2 = max(t2, red[2 * NW + k]);
     }
     s = ts;
     m1 = t1;

@@ -1,0 +1,1505 @@
+// Grid windows: statistics of the partitioned windows of more than 2^13
+// packets (layout and the treatment of dominant addresses: nsgc_plan.h).
+//
+// k_grid_heavy samples each window for dominant addresses, k_grid_partition
+// orders the window's hashed link keys by cell, k_grid_links counts each cell's
+// links and emits their row and column entries, and k_grid_rowcol adds those up
+// per source and per destination; k_grid_rounds and k_grid_sweeps finish the
+// cells and buckets that are too large for one pass.  k_finish combines the
+// totals.
+//
+// Against one link bucket per hash range (nsgc_kernels.hip): a cell's links
+// fall into the one to a few row and column buckets of its two strips instead
+// of every row and column bucket of the window, so its entries leave in long
+// runs, need next to no per-bucket counting, and phase C reads a few long
+// segments instead of one short one per link bucket.  Heavy-tailed traffic
+// has up to half of its packets between dominant addresses; those are counted
+// in LDS during the partition.
+//
+// Measured against that path, whole calls: 64 windows of 2^17 packets 237 ->
+// 208 us; one of 40013 packets 58 -> 45 us; nine of 2^12 .. 2^22 packets 434 ->
+// 184 us; 512 of 2^10 .. 2^23 packets 11.5 -> 7.1 ms; 128 of 2^23 14.2 -> 10.1
+// ms.  From 2^13 packets on no traffic mix was slower on the grid (two windows
+// of 10^4 packets 60 -> 53 us), and one link bucket holds smaller windows.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "nsgc_device.hpp"
+#include "nsgc_grid.hpp"
+#include "nsgc_phases.hpp"
+#include "nsgc_plan.h"
+
+namespace nsgc {
+
+namespace {
+
+constexpr uint32_t HVM = NSGC_GRID_HEAVY;   // most dominant addresses per view
+
+// The partition looks dominant ids up in a direct-mapped table of 512 entries
+// per view, indexed by bits 2 .. 10 of the hashed id; no two dominant ids of a
+// view share an entry.
+constexpr uint32_t HT = 512;
+__device__ __forceinline__ uint32_t heavy_index(uint32_t id) { return (id >> 2) & (HT - 1); }
+
+// The distance 1 .. 2^k - 1 (k >= 1) by which a link of a dominant address is
+// moved off its home strip, from the other address' hashed id.  It takes bits
+// 3 .. 18, which decide neither that address' strip and bucket (top bits) nor,
+// with one address fixed, the link's table slot.
+__device__ __forceinline__ uint32_t strip_shift(uint32_t other, uint32_t k) {
+  return 1u + ((((other >> 3) & 0xFFFFu) * ((1u << k) - 1u)) >> 16);
+}
+
+// Find-or-insert of U keys per lane in an open-addressing LDS table (linear
+// probing): the home slots of all U are tried together, then the keys still
+// without a slot probe on in step, a key's turn being skipped when no lane
+// needs it.  slot[u] comes in as the home slot and goes out as the key's slot;
+// fr[u]: this call inserted the key.  Call with the whole wavefront active;
+// returns whether a key of this lane found no slot.
+template <int U, class K>
+__device__ __forceinline__ bool insert_keys(K* tk, uint32_t mask, const K (&key)[U],
+                                            uint32_t (&slot)[U], const bool (&ok)[U], bool (&fr)[U]) {
+  constexpr K EMPTY = K(~K(0));
+  auto cas = [&](uint32_t s, K k) -> K {
+    if constexpr (sizeof(K) == 8) return lds_cas64(reinterpret_cast<u64*>(tk) + s, EMPTY64, k);
+    else return lds_cas32(reinterpret_cast<uint32_t*>(tk) + s, EMPTY32, k);
+  };
+  K old[U];
+  bool todo[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    old[u] = key[u];
+    if (ok[u]) old[u] = cas(slot[u], key[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    fr[u] = ok[u] && old[u] == EMPTY;
+    todo[u] = ok[u] && old[u] != EMPTY && old[u] != key[u];
+  }
+  for (uint32_t probe = 1; probe < NSGC_MAX_PROBES; ++probe) {
+    u64 any = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) any |= __ballot(todo[u]);
+    if (any == 0) break;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (todo[u]) {
+        slot[u] = (slot[u] + 1) & mask;
+        old[u] = cas(slot[u], key[u]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      fr[u] = fr[u] || (todo[u] && old[u] == EMPTY);
+      todo[u] = todo[u] && old[u] != EMPTY && old[u] != key[u];
+    }
+  }
+  bool failed = false;
+#pragma unroll
+  for (int u = 0; u < U; ++u) failed = failed || todo[u];
+  return failed;
+}
+
+// Second half of a find-or-insert of one key per lane in an open-addressing
+// LDS table (linear probing): `old` is what the compare-and-swap on the home
+// slot returned, `slot` goes in as the home slot and out as the slot last
+// tried.  Returns what that slot held: the table's marker if the key was
+// inserted, the key if it was there, anything else if it found no place.
+// (Plain values, no flags: flags carried through a divergent loop cost scalar
+// instructions per step.)
+template <class K>
+__device__ __forceinline__ K probe_on(K* tk, uint32_t mask, K key, K old, uint32_t& slot) {
+  constexpr K EMPTY = K(~K(0));
+  for (uint32_t left = NSGC_MAX_PROBES - 1; old != EMPTY && old != key && left; --left) {
+    slot = (slot + 1) & mask;
+    if constexpr (sizeof(K) == 8) old = lds_cas64(reinterpret_cast<u64*>(tk) + slot, EMPTY64, key);
+    else old = lds_cas32(reinterpret_cast<uint32_t*>(tk) + slot, EMPTY32, key);
+  }
+  return old;
+}
+
+constexpr uint32_t NO_SLOT = 0xFFFFFFFFu;
+
+// Work queue of phases B and C: like ItemQueue, but the item after the next is
+// requested as soon as the next one is announced, so that the answer is in
+// before the item's stores go out (memory operations complete in order: a
+// wait for it behind them would wait for them too).
+struct GridQueue {
+  NSGC_GLOBAL uint32_t* counter;
+  uint32_t base, step, pending;   // pending: thread 0's requested position
+  __device__ GridQueue(NSGC_GLOBAL uint32_t* counters) {
+    step = min(uint32_t(NSGC_QCLASSES), gridDim.x);
+    const uint32_t c = blockIdx.x % step;
+    counter = counters + c * NSGC_QSTRIDE;
+    base = gridDim.x + c;          // after the grid's static first items
+    pending = 0xFFFFFFFFu;
+    if (threadIdx.x == 0) take();
+  }
+  __device__ __forceinline__ void take() {
+    pending = base + step * __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // Thread 0 writes the next item (or NO_ITEM) to the LDS word *at and
+  // requests the one after it; visible after the caller's next barrier.
+  __device__ __forceinline__ void announce(uint32_t* at, uint32_t items) {
+    if (threadIdx.x == 0) {
+      *at = pending < items ? pending : NO_ITEM;
+      if (pending < items) take();
+    }
+  }
+};
+
+// The value, arrived: a load the compiler has already seen waited for is not
+// waited for again behind later stores.
+template <class T>
+__device__ __forceinline__ void arrived(T& x) {
+  asm volatile("" : "+v"(x));
+}
+__device__ __forceinline__ void loads_arrived() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
+// Four consecutive packets at any 4-byte aligned address.
+typedef uint32_t v4u32_any __attribute__((ext_vector_type(4), aligned(4)));
+
+}  // namespace
+
+// ---------------------------------------------------------------------------
+// Dominant addresses.  One workgroup per window counts the hashed sources
+// (first half of its threads) and destinations (second half) of a sample of
+// 2048 packets (4096 in batches with windows of more than 1024 cells), 64 runs
+// spread from the window's first packet to its last.  An address is a
+// candidate when the sample puts more than an eighth of a strip's share of the
+// packets on it, or half a bucket's (and at least 8 hits); of two candidates
+// that share a table entry the more frequent one stays, and of those the most
+// frequent NSGC_GRID_HEAVY.  The matrix starts at zero.  One trip to memory and
+// seven barriers: bound by latency, 4.5 us for one window and 7.6 us for 64.
+// ---------------------------------------------------------------------------
+
+constexpr uint32_t GH_NT = 1024;
+constexpr uint32_t GH_VT = GH_NT / 2;                       // threads per view
+constexpr uint32_t GH_MIN = 8;                              // hits of a candidate
+static_assert(HT == GH_VT, "one thread per table entry");
+
+template <uint32_t HV>
+__global__ __launch_bounds__(GH_NT) void k_grid_heavy(const nsgc_dev_plan* __restrict__ P) {
+  constexpr uint32_t SAMPLE = NSGC_GRID_SAMPLE(HV);
+  constexpr uint32_t GH_PER = SAMPLE / GH_VT;      // sampled packets per thread
+  constexpr uint32_t GH_TABLE = 2 * SAMPLE;
+  constexpr uint32_t GH_CAND = SAMPLE / GH_MIN;    // at most so many candidates per view
+  constexpr uint32_t RUN = SAMPLE / 64;
+  __shared__ __align__(16) uint32_t key[2][GH_TABLE];
+  __shared__ __align__(16) uint32_t cnt[2][GH_TABLE];
+  __shared__ __align__(16) u64 best[2][HT];   // hits << 32 | id of the candidate that holds an entry
+  __shared__ u64 cand[2][GH_CAND];
+  __shared__ uint32_t ncand[2];
+  const uint32_t v = threadIdx.x >= GH_VT ? 1u : 0u;   // view: sources, destinations
+  const uint32_t tid = threadIdx.x & (GH_VT - 1);
+  uint32_t* const k = key[v];
+  uint32_t* const c = cnt[v];
+  for (uint32_t wi = blockIdx.x; wi < P->num_grid; wi += gridDim.x) {
+    const nsgc_grid_desc W = sload_words(P->gwin + wi);
+    const NSGC_GLOBAL uint32_t* col = gptr(v ? W.dst : W.src);
+    uint32_t x[GH_PER];
+#pragma unroll
+    for (uint32_t u = 0; u < GH_PER; ++u) {
+      const uint32_t s = u * GH_VT + tid;
+      x[u] = col[uint32_t(u64(W.n - RUN) * (s / RUN) / 63u) + s % RUN];
+    }
+    const v4u32 e4 = {EMPTY32, EMPTY32, EMPTY32, EMPTY32}, z4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (uint32_t i = 0; i < GH_TABLE / 4 / GH_VT; ++i) {
+      reinterpret_cast<v4u32*>(k)[i * GH_VT + tid] = e4;
+      reinterpret_cast<v4u32*>(c)[i * GH_VT + tid] = z4;
+    }
+    best[v][tid] = 0;
+    if (tid == 0) ncand[v] = 0;
+    NSGC_GLOBAL uint32_t* out = gptr(W.heavy);
+    for (uint32_t i = threadIdx.x; i < HV * HV; i += GH_NT) out[2 * HV + i] = 0;
+    if (threadIdx.x < 2 * HV) out[threadIdx.x] = EMPTY32;   // unused (this id is never dominant)
+    lds_barrier();
+#pragma unroll
+    for (uint32_t u = 0; u < GH_PER; ++u) {
+      const uint32_t id = v ? col_hash(x[u]) : row_hash(x[u]);
+      if (id == EMPTY32) continue;   // the tables' marker keeps its own path
+      uint32_t sl = id & (GH_TABLE - 1);
+      for (;;) {   // ends: the table holds twice the sample
+        const uint32_t old = lds_cas32(k + sl, EMPTY32, id);
+        if (old == EMPTY32 || old == id) break;
+        sl = (sl + 1) & (GH_TABLE - 1);
+      }
+      lds_add(&c[sl], 1);
+    }
+    lds_barrier();
+    const uint32_t strip = v ? W.logBc : W.logA, bucket = v ? W.logC : W.logR;
+    const uint32_t thr = max(GH_MIN, min(SAMPLE >> (strip + 3), SAMPLE >> (bucket + 1)));
+#pragma unroll
+    for (uint32_t i = 0; i < GH_TABLE / GH_VT; ++i) {
+      const uint32_t h = c[i * GH_VT + tid];
+      if (h >= thr) {
+        const uint32_t id = k[i * GH_VT + tid];
+        __hip_atomic_fetch_max(&best[v][heavy_index(id)], (u64(h) << 32) | id, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    __syncthreads();   // (the unused marks in memory land before the ids below)
+    const u64 mine = best[v][tid];
+    if (mine) cand[v][lds_add(&ncand[v], 1)] = mine;
+    lds_barrier();
+    if (mine) {
+      uint32_t rank = 0;
+      const uint32_t nc = ncand[v];
+      for (uint32_t i = 0; i < nc; ++i) rank += cand[v][i] > mine;
+      if (rank < HV) out[v * HV + rank] = uint32_t(mine);
+    }
+    lds_barrier();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Phase A: a tile's packets ordered by cell.  Each workgroup takes a
+// contiguous run of tiles, so that it adds its part of a window's dominant
+// matrix to memory once per window and not once per tile.  The next tile's
+// packets are loaded while the current one's keys are written.  Moves 8 bytes
+// per packet in and up to 8 out: 2^23 packets (64 windows) in 34 us, 2^30 (128
+// windows, 2048 cells) in 3.9 ms, 3.3 TB/s of the copy rate's 5.1; LDS counting
+// and placing, one workgroup of 1024 per compute unit, is the rest.
+// ---------------------------------------------------------------------------
+
+namespace {
+constexpr size_t grid_part_lds(uint32_t tile_log2, uint32_t cells) {
+  const size_t HV = size_t(NSGC_GRID_HV(tile_log2));
+  return (size_t(1) << tile_log2) * 8 + (cells + 4) * 4 + HV * HV * 4 + 2 * HT * 4 + 2 * HT + 64;
+}
+}  // namespace
+
+size_t lds_grid_part_bytes(uint32_t tile_log2, uint32_t max_cells) {
+  return grid_part_lds(tile_log2, max_cells);
+}
+
+template <int PER, int NT, uint32_t HV>
+__global__ __launch_bounds__(NT) void k_grid_partition(const nsgc_dev_plan* __restrict__ P,
+                                                       uint32_t max_cells) {
+  static_assert(PER % 4 == 0, "PER must be a multiple of 4");
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr uint32_t T = NT * PER;
+  constexpr int NW = NT / 64;
+  u64* stage = reinterpret_cast<u64*>(smem);                       // [T]
+  uint32_t* hist = reinterpret_cast<uint32_t*>(stage + T);         // [max_cells + 1]
+  uint32_t* mat = hist + max_cells + 4;                            // [HV][HV]
+  uint32_t* idt = mat + HV * HV;                                   // [2][HT] dominant ids
+  uint8_t* ids = reinterpret_cast<uint8_t*>(idt + 2 * HT);         // [2][HT] their slots
+  uint32_t* red = reinterpret_cast<uint32_t*>(ids + 2 * HT);       // [NW]
+  const uint32_t tid = threadIdx.x, w = tid >> 6;
+  const uint32_t items = P->gitemsA;
+  const uint32_t per = (items + gridDim.x - 1) / gridDim.x;
+  const uint32_t beg = min(items, blockIdx.x * per), end = min(items, beg + per);
+  if (beg >= end) return;
+  uint32_t wi = uniform(owner_of_wave(gptr(P->gprefA), P->num_grid, beg));
+  nsgc_grid_desc W = sload_words(P->gwin + wi);
+  uint32_t first = sload(P->gprefA + wi), next = sload(P->gprefA + wi + 1);
+
+  // The window's dominant ids into the lookup table (a free entry holds an id
+  // that belongs to another entry).  Needs a barrier before and after.
+  auto load_heavy = [&]() {
+    for (uint32_t i = tid; i < 2 * HT; i += NT) idt[i] = ((i & (HT - 1)) ^ 1u) << 2;
+    lds_barrier();
+    if (tid < 2 * HV) {
+      const uint32_t id = gptr(W.heavy)[tid];
+      if (id != EMPTY32) {
+        const uint32_t at = (tid / HV) * HT + heavy_index(id);
+        idt[at] = id;
+        ids[at] = uint8_t(tid & (HV - 1));
+      }
+    }
+  };
+  auto flush = [&]() {   // the matrix counted so far to memory; leaves it zero
+    NSGC_GLOBAL uint32_t* m = gptr(W.heavy) + 2 * HV;
+    for (uint32_t i = tid; i < HV * HV; i += NT) {
+      if (mat[i]) __hip_atomic_fetch_add(m + i, mat[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      mat[i] = 0;
+    }
+  };
+  uint32_t r[PER], c[PER];
+  auto load = [&](uint32_t tbeg, uint32_t len) {
+    const NSGC_GLOBAL uint32_t* src = gptr(W.src) + tbeg;
+    const NSGC_GLOBAL uint32_t* dst = gptr(W.dst) + tbeg;
+    if (len == T) {
+#pragma unroll
+      for (int k = 0; k < PER / 4; ++k) {
+        const uint32_t idx = (k * NT + tid) * 4;
+        const v4u32 s4 = *(const NSGC_GLOBAL v4u32_any*)(src + idx);
+        const v4u32 d4 = *(const NSGC_GLOBAL v4u32_any*)(dst + idx);
+        r[4 * k + 0] = s4.x; r[4 * k + 1] = s4.y; r[4 * k + 2] = s4.z; r[4 * k + 3] = s4.w;
+        c[4 * k + 0] = d4.x; c[4 * k + 1] = d4.y; c[4 * k + 2] = d4.z; c[4 * k + 3] = d4.w;
+      }
+    } else {   // a window's last tile: a packet past the end repeats the last one, masked below
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const uint32_t at = min(uint32_t((k >> 2) * NT + tid) * 4 + (k & 3), len - 1);
+        r[k] = src[at];
+        c[k] = dst[at];
+      }
+    }
+  };
+
+  uint32_t t = beg - first, len = min(T, W.n - t * T);
+  load(t * T, len);
+  for (uint32_t i = tid; i < HV * HV; i += NT) mat[i] = 0;
+  load_heavy();
+  for (uint32_t item = beg;; ++item) {
+    const uint32_t a = W.logA, b = W.logBc, cells = 1u << (a + b);
+    for (uint32_t i = tid; i < cells; i += NT) hist[i] = 0;
+    lds_barrier();
+    uint32_t br[PER];   // rank in cell << 12 | cell; all ones: no key
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      r[k] = row_hash(r[k]);
+      c[k] = col_hash(c[k]);
+      const bool hs = idt[heavy_index(r[k])] == r[k], hd = idt[HT + heavy_index(c[k])] == c[k];
+      const bool ok = len == T || uint32_t((k >> 2) * NT + tid) * 4 + (k & 3) < len;
+      br[k] = ~0u;
+      uint32_t i = r[k] >> (32 - a), j = c[k] >> (32 - b);
+      if (hs && hd) {
+        if (ok) lds_add(&mat[uint32_t(ids[heavy_index(r[k])]) * HV + ids[HT + heavy_index(c[k])]], 1);
+      } else {
+        // a key names a dominant address by its slot, off the cell's strip
+        if (hs) {
+          i ^= strip_shift(c[k], a);
+          r[k] = ((i ^ 1u) << (32 - a)) | ids[heavy_index(r[k])];
+        }
+        if (hd) {
+          j ^= strip_shift(r[k], b);
+          c[k] = ((j ^ 1u) << (32 - b)) | ids[HT + heavy_index(c[k])];
+        }
+        const uint32_t cell = (i << b) | j;
+        if (ok) br[k] = (lds_add(&hist[cell], 1) << 12) | cell;
+      }
+    }
+    lds_barrier();
+    // counts -> starts
+    {
+      const uint32_t q = (cells + NT - 1) / NT;
+      const uint32_t h0 = min(cells, tid * q), h1 = min(cells, h0 + q);
+      uint32_t s = 0;
+      for (uint32_t i = h0; i < h1; ++i) s += hist[i];
+      const uint32_t incl = wave_inclusive_scan(s);
+      if (lane_id() == 63) red[w] = incl;
+      lds_barrier();
+      uint32_t run = incl - s, all = 0;
+#pragma unroll
+      for (int k = 0; k < NW; ++k) {
+        const uint32_t x = red[k];
+        if (uint32_t(k) < w) run += x;
+        all += x;
+      }
+      // the tile records go out here, start | length << 16
+      NSGC_GLOBAL uint32_t* tm = gptr(W.tile) + u64(t) * cells;
+      for (uint32_t i = h0; i < h1; ++i) {
+        const uint32_t x = hist[i];
+        hist[i] = run;
+        tm[i] = run | (x << 16);
+        run += x;
+      }
+      if (tid == 0) hist[cells] = all;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (br[k] != ~0u) stage[hist[br[k] & 0xFFFu] + (br[k] >> 12)] = (u64(r[k]) << 32) | c[k];
+    const uint32_t total = hist[cells];
+    NSGC_GLOBAL u64* out = gptr(W.keys) + t * T;
+    lds_barrier();
+    const bool more = item + 1 < end;
+    if (more) {
+      if (item + 1 >= next) {   // the run goes on into another window
+        flush();
+        do {
+          first = next;
+          next = sload(P->gprefA + ++wi + 1);
+        } while (item + 1 >= next);
+        W = sload_words(P->gwin + wi);
+        load_heavy();
+      }
+      t = item + 1 - first;
+      len = min(T, W.n - t * T);
+      load(t * T, len);
+    }
+    for (uint32_t i = tid; i < total; i += NT) out[i] = stage[i];
+    if (!more) break;
+  }
+  lds_barrier();
+  flush();
+}
+
+// ---------------------------------------------------------------------------
+// Shared by phases B and C: the elements of a list of segments, spread over
+// the workgroup.  Thread s describes segment s (n <= NT segments: base, len);
+// on return list[e] is the position of element e of their concatenation, for
+// all e below the total (returned; nothing is written if it exceeds `room`).
+// Groups of 2^g threads walk one segment each, as many as NT / n allows.
+// `tab` is LDS scratch of 2 * NT + 2 * NT / 64 words.  Begins and ends with
+// work that needs the caller's barrier: the caller passes one before `list`
+// and `tab` may be written and one before `list` is read.
+// ---------------------------------------------------------------------------
+
+template <int NT>
+__device__ __forceinline__ uint32_t spread_segments(uint32_t tid, uint32_t n, uint32_t base, uint32_t len,
+                                                    uint32_t& extra, uint32_t* tab, uint32_t* list,
+                                                    uint32_t room) {
+  constexpr int NW = NT / 64;
+  const uint32_t w = tid >> 6;
+  uint32_t* start = tab;
+  uint32_t* pos = tab + NT;
+  uint32_t* red = tab + 2 * NT;
+  const uint32_t incl = wave_inclusive_scan(len);
+  const uint32_t ex = wave_sum(extra);
+  if (lane_id() == 63) {
+    red[w] = incl;
+    red[NW + w] = ex;
+  }
+  pos[tid] = base;
+  lds_barrier();
+  uint32_t before = 0, total = 0, xs = 0;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {
+    const uint32_t x = red[k];
+    if (uint32_t(k) < w) before += x;
+    total += x;
+    xs += red[NW + k];
+  }
+  extra = uniform(xs);
+  total = uniform(total);
+  if (total > room) return total;
+  start[tid] = before + incl - len;
+  lds_barrier();
+  const uint32_t lg = min(6u, 31u - uint32_t(__builtin_clz(uint32_t(NT) / max(n, 1u))));
+  const uint32_t s = tid >> lg, g = 1u << lg;
+  if (s < n) {
+    const uint32_t at = start[s], p = pos[s];
+    const uint32_t l = (s + 1 < n ? start[s + 1] : total) - at;
+    for (uint32_t k = tid & (g - 1); k < l; k += g) list[at + k] = p + k;
+  }
+  return total;
+}
+
+// The same for at most 64 segments, described alike in every wavefront (lane
+// s: segment s): no barrier inside.
+template <int NT>
+__device__ __forceinline__ uint32_t spread_by_wave(uint32_t tid, uint32_t n, uint32_t base, uint32_t len,
+                                                   uint32_t& extra, uint32_t* list, uint32_t room) {
+  const uint32_t incl = wave_inclusive_scan(len);
+  const uint32_t total = uniform(readlane(incl, 63));
+  extra = uniform(wave_sum(extra));
+  if (total > room) return total;
+  const uint32_t lg = 31u - uint32_t(__builtin_clz(uint32_t(NT) / max(n, 1u)));
+  const uint32_t s = tid >> lg, g = 1u << lg;
+  const uint32_t at = lane_take(incl - len, s), p = lane_take(base, s), l = lane_take(len, s);
+  if (s < n)
+    for (uint32_t k = tid & (g - 1); k < l; k += g) list[at + k] = p + k;
+  return total;
+}
+
+// ---------------------------------------------------------------------------
+// Phase B: the links of one cell.  Bound by the latency of the item's serial
+// chain (records, positions, keys, table, counts, starts, stores), hidden by
+// five (BIG: three) workgroups per compute unit and by loading the next item's
+// records and asking for the one after it during the current one.  Keys stay in
+// registers from the insert to the emission: reading them again, or the table,
+// is another trip through LDS for every slot.  64 windows of 2^17 packets in 77
+// us against 94 us with a wavefront per link bucket; 128 of 2^23 in 3.8 ms
+// against 8.4 ms with a workgroup per link bucket.  Measured and not taken: all
+// four home slots probing on in step (88 us), entries staged in LDS and copied
+// out in lines (83 us), cells twice the size (100 us).
+// ---------------------------------------------------------------------------
+
+// The table, the CW words of counts, the bins and the flags of a cell, empty.
+template <int NT, int SL, int CW>
+__device__ __forceinline__ void clear_cell_table(uint32_t tid, u64* tk, uint32_t* tc, uint32_t* bin,
+                                                 uint32_t* misc) {
+  const v4u32 e4 = {EMPTY32, EMPTY32, EMPTY32, EMPTY32}, z4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (uint32_t i = 0; i < SL / 2 / NT; ++i) reinterpret_cast<v4u32*>(tk)[i * NT + tid] = e4;
+#pragma unroll
+  for (uint32_t i = 0; i < CW / 4 / NT; ++i) reinterpret_cast<v4u32*>(tc)[i * NT + tid] = z4;
+  if (tid < 2 * NSGC_GRID_MAX_SUB) bin[tid] = 0;
+  if (tid < 4) misc[tid] = 0;
+}
+
+// Counts -> exclusive starts of the row and the column bins: every wavefront
+// scans both (at most 64 bins, one per lane; lane i returns bin i's starts);
+// the first one publishes them for phase C.
+__device__ __forceinline__ void publish_starts(NSGC_GLOBAL uint32_t* rec, const uint32_t* bin,
+                                               uint32_t rsub, uint32_t csub, uint32_t below,
+                                               uint32_t& xr, uint32_t& xc) {
+  const uint32_t lane = lane_id();
+  const uint32_t nr = lane < rsub ? bin[lane] : 0u;
+  const uint32_t nc = lane < csub ? bin[NSGC_GRID_MAX_SUB + lane] : 0u;
+  const uint32_t ir = wave_inclusive_scan(nr), ic = wave_inclusive_scan(nc);
+  xr = ir - nr;
+  xc = ic - nc;
+  if (threadIdx.x < 64) {
+    if (lane == 0) rec[0] = below;
+    if (lane < rsub) rec[1 + lane] = xr;
+    if (lane < csub) rec[2 + rsub + lane] = xc;
+    if (lane == 63) {
+      rec[1 + rsub] = ir;
+      rec[2 + rsub + csub] = ic;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The cells that are too large for the single passes (more keys than their
+// threads hold, or more links than their tables take), by rounds.
+// ---------------------------------------------------------------------------
+
+constexpr int GR_NT = 512;
+constexpr int GR_SL = 4096;
+
+__global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_t after_wide) {
+  constexpr int NT = GR_NT, SL = GR_SL, NW = NT / 64;
+  __shared__ __align__(16) u64 tk[SL];
+  __shared__ __align__(16) uint32_t tc[SL];
+  __shared__ u64 acc[2 * HVM];
+  __shared__ uint32_t bin[2 * NSGC_GRID_MAX_SUB];   // rows, columns
+  __shared__ uint32_t misc[4];   // 0 failed, 1 special packets, 2 links, 3 max packets
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t items = P->gover[after_wide ? 2 : 0];
+  for (uint32_t x = blockIdx.x; x < items; x += gridDim.x) {
+  const uint32_t it = uniform(gptr(after_wide ? sload(&P->goverW) : sload(&P->goverB))[x]);
+  const uint32_t HV = NSGC_GRID_HV(sload(&P->gtile_log2));
+  if (tid < 2 * HV) acc[tid] = 0;
+  const uint32_t T = 1u << sload(&P->gtile_log2);
+  const nsgc_grid_desc W = sload_words(sload(&P->gwin) + sload(sload(&P->gitemB) + it));
+  const uint32_t cell = it - W.itemB;
+  const uint32_t a = W.logA, b = W.logBc, cells = 1u << (a + b);
+  const uint32_t ci = cell >> b, cj = cell & ((1u << b) - 1u);
+  const uint32_t rsub = 1u << (W.logR - a), csub = 1u << (W.logC - b);
+  const uint32_t nt = W.ntiles;
+  NSGC_GLOBAL u64* keys = gptr(W.keys);
+  const NSGC_GLOBAL uint32_t* tm = gptr(W.tile) + cell;
+  NSGC_GLOBAL uint32_t* rec = gptr(W.rec) + u64(cell) * (rsub + csub + 3);
+  uint32_t below = 0, total = 0;   // keys of the window in cells below this one; its own
+  for (uint32_t t = tid; t < nt; t += NT) {
+    const uint32_t y = tm[u64(t) * cells];
+    below += y & 0xFFFFu;
+    total += y >> 16;
+  }
+  below = wave_sum(below);
+  total = wave_sum(total);
+  if (lane == 0) {
+    tc[tid >> 6] = below;
+    tc[NW + (tid >> 6)] = total;
+  }
+  __syncthreads();
+  below = total = 0;
+  for (int k = 0; k < NW; ++k) {
+    below += tc[k];
+    total += tc[NW + k];
+  }
+  below = uniform(below);
+  total = uniform(total);
+  NSGC_GLOBAL u64* er = gptr(W.emit_row) + below;
+  NSGC_GLOBAL u64* ec = gptr(W.emit_col) + below;
+  auto row_bin = [&](uint32_t r) { return (r >> (32 - W.logR)) & (rsub - 1u); };
+  auto col_bin = [&](uint32_t c) { return (c >> (32 - W.logC)) & (csub - 1u); };
+  auto row_light = [&](uint32_t r) { return (r >> (32 - a)) == ci; };
+  auto col_light = [&](uint32_t c) { return (c >> (32 - b)) == cj; };
+  auto home = [&](u64 k) { return (uint32_t(k >> 32) ^ uint32_t(k)) & uint32_t(SL - 1); };
+  auto add_heavy = [&](uint32_t v, uint32_t id, uint32_t n) {
+    lds_add64(&acc[v * HV + (id & (HV - 1))], (u64(1) << 32) | n);
+  };
+  auto clear_table = [&]() { clear_cell_table<NT, SL, SL>(tid, tk, tc, bin, misc); };
+  auto starts = [&](uint32_t& xr, uint32_t& xc) { publish_starts(rec, bin, rsub, csub, below, xr, xc); };
+
+  // Rounds: each fills the table with as many links as it takes, counts
+  // all their packets and emits them.  If a key found no place, the keys
+  // that did are overwritten with the marker before the next round, which
+  // then sees only the others.  With more than one round a bin's segment
+  // gets one slot per packet of the bin, the most entries it can receive;
+  // slots left over hold empty entries (no packets), which phase C skips.
+  uint32_t links = 0, mx = 0;
+  bool abandoned = false;
+  uint32_t special = 0;
+  const uint32_t max_rounds = 1u << min(sload(&P->max_sweeps_log2), 24u);
+  auto seg = [&](uint32_t t, u64& base, uint32_t& len) {
+    const uint32_t x = tm[u64(t) * cells];
+    base = u64(t) * T + (x & 0xFFFFu);
+    len = x >> 16;
+  };
+  for (uint32_t round = 0;; ++round) {
+    if (round >= max_rounds) { abandoned = true; break; }
+    __syncthreads();
+    const uint32_t keep = round && tid < 2 * NSGC_GRID_MAX_SUB ? bin[tid] : 0u;
+    clear_table();
+    if (round && tid < 2 * NSGC_GRID_MAX_SUB) bin[tid] = keep;   // cursors stay
+    __syncthreads();
+    gather_by_wave<4, NW>(nt, seg, [&](const auto& pos, const auto& okin) {
+      constexpr int U = array_len<decltype(pos)>();
+      u64 key[U];
+      uint32_t at[U], add[U];
+      bool ok[U], fr[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) key[u] = keys[okin[u] ? pos[u] : 0ull];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        ok[u] = okin[u];
+        at[u] = home(key[u]);
+        add[u] = 1;
+        if (ok[u] && key[u] == EMPTY64) {   // round 0: special; later: counted already
+          if (round == 0) lds_add(&misc[1], 1);
+          ok[u] = false;
+        }
+        // combine the lanes holding the first valid lane's key
+        const u64 vm = __ballot(ok[u]);
+        if (vm) {
+          const int f = __ffsll(static_cast<unsigned long long>(vm)) - 1;
+          const bool same = ok[u] && key[u] == readlane64(key[u], uint32_t(f));
+          const uint32_t ns = __popcll(__ballot(same));
+          if (ns > 1 && same) {
+            if (int(lane_id()) == f) add[u] = ns;
+            else ok[u] = false;
+          }
+        }
+      }
+      if (insert_keys<U>(tk, uint32_t(SL - 1), key, at, ok, fr)) {
+        lds_store(&misc[0], 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u)   // a key without a slot is left to the next round
+          if (ok[u] && tk[at[u]] != key[u]) ok[u] = false;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (ok[u]) lds_add(&tc[at[u]], add[u]);
+    });
+    const bool failed = misc[0] != 0;
+    if (round == 0) special = misc[1];
+    if (failed) {   // mark the keys the table holds; round 0 also sizes the bins' segments
+      gather_by_wave<4, NW>(nt, seg, [&](const auto& pos, const auto& okin) {
+        constexpr int U = array_len<decltype(pos)>();
+        u64 key[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) key[u] = keys[okin[u] ? pos[u] : 0ull];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (!okin[u]) continue;
+          if (round == 0) {
+            if (row_light(uint32_t(key[u] >> 32))) lds_add(&bin[row_bin(uint32_t(key[u] >> 32))], 1);
+            if (col_light(uint32_t(key[u]))) lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(uint32_t(key[u]))], 1);
+          }
+          if (key[u] == EMPTY64) continue;
+          uint32_t s = home(key[u]);
+          for (uint32_t p = 0; p < NSGC_MAX_PROBES; ++p) {
+            const u64 cur = tk[s];
+            if (cur == key[u]) {
+              keys[pos[u]] = EMPTY64;
+              break;
+            }
+            if (cur == EMPTY64) break;
+            s = (s + 1) & uint32_t(SL - 1);
+          }
+        }
+      });
+    } else if (round == 0) {   // everything fits: count the entries per bin
+      for (uint32_t s = tid; s < SL; s += NT) {
+        const u64 k = tk[s];
+        if (k == EMPTY64) continue;
+        const uint32_t parts = entry_parts(tc[s], 1);
+        if (row_light(uint32_t(k >> 32))) lds_add(&bin[row_bin(uint32_t(k >> 32))], parts);
+        if (col_light(uint32_t(k))) lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(uint32_t(k))], parts);
+      }
+      if (tid == 0 && special) {
+        const uint32_t parts = entry_parts(special, 1);
+        lds_add(&bin[row_bin(EMPTY32)], parts);
+        lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(EMPTY32)], parts);
+      }
+    }
+    if (round == 0) {
+      __syncthreads();
+      uint32_t xr, xc;
+      starts(xr, xc);
+      __syncthreads();
+      if (tid < 64) {   // the starts become the emission cursors
+        if (lane < rsub) bin[lane] = xr;
+        if (lane < csub) bin[NSGC_GRID_MAX_SUB + lane] = xc;
+      }
+      if (failed)
+        for (uint32_t i = tid; i < total; i += NT) {
+          er[i] = 0ull;
+          ec[i] = 0ull;
+        }
+      __threadfence_block();   // the empty entries land before any emission
+      __syncthreads();
+    }
+    auto emit = [&](u64 k, uint32_t n) {
+      const uint32_t r = uint32_t(k >> 32), c = uint32_t(k), parts = entry_parts(n, 1);
+      if (row_light(r)) write_entry(er, lds_add(&bin[row_bin(r)], parts), r, n, 1, parts);
+      else add_heavy(0, r, n);
+      if (col_light(c)) write_entry(ec, lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(c)], parts), c, n, 1, parts);
+      else add_heavy(1, c, n);
+    };
+    for (uint32_t s = tid; s < SL; s += NT) {
+      const u64 k = tk[s];
+      if (k == EMPTY64) continue;
+      const uint32_t n = tc[s];
+      ++links;
+      mx = max(mx, n);
+      emit(k, n);
+    }
+    if (tid == 0 && special && round == 0) {
+      ++links;
+      mx = max(mx, special);
+      emit(EMPTY64, special);
+    }
+    if (!failed) break;
+  }
+  __syncthreads();
+  if (abandoned) {   // empty segments, so that phase C reads nothing here
+    for (uint32_t i = tid; i < rsub + csub + 3; i += NT) rec[i] = 0;
+  }
+  if (tid < 4) misc[tid] = 0;
+  __syncthreads();
+  links = wave_sum(links);
+  mx = wave_max(mx);
+  if (lane == 0) {
+    lds_add(&misc[2], links);
+    __hip_atomic_fetch_max(&misc[3], mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __syncthreads();
+  if (tid < 2 * HV) gptr(W.acc)[u64(cell) * (2 * HV) + tid] = acc[tid];
+  if (tid == 0) {
+    const v4u32 part = {total, misc[2], misc[3], abandoned ? 1u : 0u};
+    gptr(reinterpret_cast<v4u32*>(W.partB))[cell] = part;
+  }
+  __syncthreads();
+  }
+}
+
+// The phase in three sizes: SMALL and BIG for windows of smaller and of larger
+// cells, and WIDE for the cells that BIG listed as too large for it, with three
+// times the keys and twice the table (one workgroup per compute unit).  Cells
+// that SMALL or WIDE list go to k_grid_rounds.  Sixteen windows of 2^23 packets
+// among 4096 addresses, half of whose cells overflow BIG, took 8.2 ms without
+// WIDE and take 3.8 ms with it.
+enum GridCells { SMALL, BIG, WIDE };
+
+template <int NT, int SL, int E, GridCells KIND>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE ? 4 : 6))) void k_grid_links(
+    nsgc_dev_plan* P) {
+  constexpr int NW = NT / 64;
+  constexpr uint32_t ROOM = NT * E;
+  static_assert(ROOM * 4 <= SL * 8, "the positions share the key table");
+  static_assert((2 * NT + 2 * NW) * 4 <= SL * 2, "the segment table shares the counts");
+  static_assert(ROOM < 65536, "16-bit counts");
+  __shared__ __align__(16) u64 tk[SL];
+  __shared__ __align__(16) uint32_t tc[SL / 2];   // 16-bit counts, two to a word
+  __shared__ u64 acc[2 * HVM];
+  __shared__ uint32_t bin[2 * NSGC_GRID_MAX_SUB];   // rows, columns
+  __shared__ uint32_t misc[8];   // 0 failed, 1 special packets, 2 links, 3 max packets, 7 queue slot
+  const uint32_t lane = lane_id();
+  const uint32_t items = KIND == WIDE ? gptr(&P->gover[0])[0]
+                       : KIND == BIG  ? sload(&P->gitemsB) - sload(&P->gitemsS)
+                                      : sload(&P->gitemsS);
+  auto item_at = [&](uint32_t pos) -> uint32_t {
+    if (KIND == WIDE) return uniform(gptr(sload(&P->goverB))[pos]);
+    return uniform(KIND == BIG ? sload(&P->gitemsS) + pos : pos);
+  };
+  const uint32_t T = 1u << sload(&P->gtile_log2);
+
+  const uint32_t HV = NSGC_GRID_HV(sload(&P->gtile_log2));
+  if (threadIdx.x < 2 * HV) acc[threadIdx.x] = 0;
+
+  GridQueue q(gptr(&P->queue[KIND == WIDE ? 7 : KIND == BIG ? 5 : 4][0]));
+  // This thread's tile record of item `it` (lane or thread t: tile t), loaded
+  // for the next item while the current one is worked on.
+  auto record = [&](const nsgc_grid_desc& W, uint32_t it, uint32_t t) -> uint32_t {
+    if (W.ntiles <= 64) t &= 63u;
+    const uint32_t cells = 1u << (W.logA + W.logBc);
+    return t < W.ntiles ? gptr(W.tile)[u64(t) * cells + (it - W.itemB)] : 0u;
+  };
+  uint32_t x = 0, wnext = 0;   // the next item's record and window
+  bool have = false;
+  for (uint32_t pos0 = blockIdx.x < items ? blockIdx.x : NO_ITEM; pos0 != NO_ITEM;) {
+    // opaque, so that what depends on it is computed per item and does not
+    // hold registers across items
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const uint32_t it = item_at(pos0);
+    if (!have) wnext = sload(sload(&P->gitemB) + it);
+    const nsgc_grid_desc W = sload_words(sload(&P->gwin) + wnext);
+    const uint32_t cell = it - W.itemB;
+    const uint32_t nt = W.ntiles;
+
+    // the cell's segments (one per tile) and its packets; `below`: the
+    // window's keys in cells below this one, the emission base
+    uint32_t below = 0, total = ROOM + 1;
+    if (!have) {
+      x = record(W, it, tid);
+      arrived(x);
+    }
+    q.announce(&misc[6], items);
+    below = x & 0xFFFFu;
+    if (nt <= 64)
+      total = spread_by_wave<NT>(tid, nt, lane * T + (x & 0xFFFFu), x >> 16, below,
+                                 reinterpret_cast<uint32_t*>(tk), ROOM);
+    else if (nt <= NT)
+      total = spread_segments<NT>(tid, nt, tid * T + (x & 0xFFFFu), x >> 16, below, tc,
+                                  reinterpret_cast<uint32_t*>(tk), ROOM);
+    lds_barrier();
+    const uint32_t ahead = uniform(misc[6]);
+    have = ahead != NO_ITEM;
+    const uint32_t itnext = have ? item_at(ahead) : it;
+    wnext = sload(sload(&P->gitemB) + itnext);
+    bool done = false;
+    uint32_t links = 0, mx = 0;
+    if (total <= ROOM) {
+      const uint32_t a = W.logA, b = W.logBc, cells = 1u << (a + b);
+      const uint32_t ci = cell >> b, cj = cell & ((1u << b) - 1u);
+      const uint32_t rsub = 1u << (W.logR - a), csub = 1u << (W.logC - b);
+      NSGC_GLOBAL u64* keys = gptr(W.keys);
+      NSGC_GLOBAL uint32_t* rec = gptr(W.rec) + u64(cell) * (rsub + csub + 3);
+      NSGC_GLOBAL u64* er = gptr(W.emit_row) + below;
+      NSGC_GLOBAL u64* ec = gptr(W.emit_col) + below;
+      auto row_bin = [&](uint32_t r) { return (r >> (32 - W.logR)) & (rsub - 1u); };
+      auto col_bin = [&](uint32_t c) { return (c >> (32 - W.logC)) & (csub - 1u); };
+      auto row_light = [&](uint32_t r) { return (r >> (32 - a)) == ci; };
+      auto col_light = [&](uint32_t c) { return (c >> (32 - b)) == cj; };
+      auto home = [&](u64 k) { return (uint32_t(k >> 32) ^ uint32_t(k)) & uint32_t(SL - 1); };
+      // a link of the dominant source (v = 0) or destination (v = 1) that `id` names
+      auto add_heavy = [&](uint32_t v, uint32_t id, uint32_t n) {
+        lds_add64(&acc[v * HV + (id & (HV - 1))], (u64(1) << 32) | n);
+      };
+      // only the last cell can hold the key that equals the table's marker
+      const bool marker = cell == cells - 1u;
+      const uint32_t kmax = uniform((total + NT - 1) / NT);
+      const uint32_t* list = reinterpret_cast<const uint32_t*>(tk);
+      const uint16_t* tc16 = reinterpret_cast<const uint16_t*>(tc);
+      u64 key[E];
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        key[k] = 0;
+        if (uint32_t(k) < kmax) {
+          const uint32_t e = k * NT + tid;
+          key[k] = keys[e < total ? list[e] : 0u];
+        }
+      }
+      lds_barrier();
+      clear_cell_table<NT, SL, SL / 2>(tid, tk, tc, bin, misc);
+      lds_barrier();
+      loads_arrived();
+      if (have) x = record(sload_words(sload(&P->gwin) + wnext), itnext, tid);
+      uint32_t at[E];   // slot of a link that this thread inserted
+#pragma unroll
+      for (int k0 = 0; k0 < E; k0 += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) at[k0 + u] = NO_SLOT;
+        if (uint32_t(k0) < kmax) {
+          // the home slots of four keys together, then each key's probing
+          u64 old[4];
+          uint32_t s[4];
+          bool ok[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            ok[u] = uint32_t((k0 + u) * NT) + tid < total;
+            s[u] = home(key[k0 + u]);
+            old[u] = key[k0 + u];
+          }
+          if (marker) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (ok[u] && key[k0 + u] == EMPTY64) {   // counted outside the table
+                lds_add(&misc[1], 1);
+                ok[u] = false;
+              }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (ok[u]) old[u] = lds_cas64(&tk[s[u]], EMPTY64, key[k0 + u]);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (ok[u]) {
+              const u64 o = probe_on<u64>(tk, uint32_t(SL - 1), key[k0 + u], old[u], s[u]);
+              if (o == EMPTY64) at[k0 + u] = s[u];
+              else if (o == key[k0 + u]) lds_add(&tc[s[u] >> 1], 1u << ((s[u] & 1u) << 4));
+              else misc[0] = 1;
+            }
+          }
+        }
+      }
+      // the next item's record and the queue's answer, before any store
+      arrived(x);
+      arrived(q.pending);
+      lds_barrier();
+      done = misc[0] == 0;
+      if (done) {
+        const uint32_t special = marker ? misc[1] : 0u;
+        uint32_t nf = 0, nr = 0, nc = 0;   // the wavefront's links, and their light entries
+        uint32_t rk[E];   // ranks in the row bin | column bin << 16 (several bins)
+#pragma unroll
+        for (int k = 0; k < E; ++k)   // from here on `at` is the link's packets, 0 for none
+          if (uint32_t(k) < kmax) at[k] = at[k] != NO_SLOT ? tc16[at[k]] + 1u : 0u;
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+          rk[k] = 0;
+          if (uint32_t(k) < kmax) {
+            const uint32_t r = uint32_t(key[k] >> 32), c = uint32_t(key[k]);
+            const bool fr = at[k] != 0, rl = fr && row_light(r), cl = fr && col_light(c);
+            nf += __popcll(__ballot(fr));
+            mx = max(mx, at[k]);
+            if (rsub == 1) nr += __popcll(__ballot(rl));
+            else if (rl) rk[k] = lds_add(&bin[row_bin(r)], 1);
+            if (csub == 1) nc += __popcll(__ballot(cl));
+            else if (cl) rk[k] |= lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(c)], 1) << 16;
+            if (fr && !rl) add_heavy(0, r, at[k]);
+            if (fr && !cl) add_heavy(1, c, at[k]);
+          }
+        }
+        uint32_t srk = 0;
+        if (tid == 0 && special) {   // its addresses are never dominant
+          srk = lds_add(&bin[rsub - 1], 1) | (lds_add(&bin[NSGC_GRID_MAX_SUB + csub - 1], 1) << 16);
+          ++nf;
+          mx = max(mx, special);
+        }
+        mx = wave_max(mx);
+        uint32_t br = 0, bc = 0;   // single bins: the wavefront's first entry
+        if (lane == 0) {
+          if (rsub == 1) br = lds_add(&bin[0], nr);
+          if (csub == 1) bc = lds_add(&bin[NSGC_GRID_MAX_SUB], nc);
+          lds_add(&misc[2], nf);
+          __hip_atomic_fetch_max(&misc[3], mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        br = uniform(br);
+        bc = uniform(bc);
+        lds_barrier();
+        uint32_t xr, xc;
+        publish_starts(rec, bin, rsub, csub, below, xr, xc);
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+          if (uint32_t(k) < kmax) {
+            arrived(key[k]);   // (recomputed from the key: registers are short)
+            const uint32_t r = uint32_t(key[k] >> 32), c = uint32_t(key[k]);
+            const bool rl = at[k] && row_light(r), cl = at[k] && col_light(c);
+            uint32_t pr, pc;
+            if (rsub == 1) {
+              const u64 m = __ballot(rl);
+              pr = br + rank_below(m);
+              br += __popcll(m);
+            } else {
+              pr = lane_take(xr, row_bin(r)) + (rk[k] & 0xFFFFu);
+            }
+            if (csub == 1) {
+              const u64 m = __ballot(cl);
+              pc = bc + rank_below(m);
+              bc += __popcll(m);
+            } else {
+              pc = lane_take(xc, col_bin(c)) + (rk[k] >> 16);
+            }
+            const uint32_t lo = (1u << NSGC_ENT_PACKET_BITS) | at[k];   // below 2^19: one entry
+            if (rl) er[pr] = (u64(r) << 32) | lo;
+            if (cl) ec[pc] = (u64(c) << 32) | lo;
+          }
+        }
+        if (special) {   // the last bin of each strip
+          const uint32_t bs = lane_take(xr, rsub - 1), cs = lane_take(xc, csub - 1);
+          if (tid == 0) {
+            const u64 e = (u64(EMPTY32) << 32) | (u64(1) << NSGC_ENT_PACKET_BITS) | special;
+            er[bs + (srk & 0xFFFFu)] = e;
+            ec[cs + (srk >> 16)] = e;
+          }
+        }
+        links = misc[2];
+        mx = misc[3];
+      }
+    }
+    if (done) {   // (the last write of `acc` is behind a barrier)
+      if (tid < 2 * HV) {
+        gptr(W.acc)[u64(cell) * (2 * HV) + tid] = acc[tid];
+        acc[tid] = 0;
+      }
+      if (tid == 0) {
+        const v4u32 part = {total, links, mx, 0u};
+        gptr(reinterpret_cast<v4u32*>(W.partB))[cell] = part;
+      }
+    } else if (tid == 0) {   // listed for WIDE or k_grid_rounds
+      const uint32_t at = __hip_atomic_fetch_add(gptr(&P->gover[KIND == WIDE ? 2 : 0]), 1u, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+      gptr(KIND == WIDE ? sload(&P->goverW) : sload(&P->goverB))[at] = it;
+    }
+    if (total > ROOM && have) {
+      x = record(sload_words(sload(&P->gwin) + wnext), itnext, tid);
+      arrived(x);
+    }
+    pos0 = ahead;
+    lds_barrier();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Phase C: the sources of one row bucket (or the destinations of one column
+// bucket, or a few neighbouring buckets).  A few more items per window add up
+// its dominant addresses.  Like phase B one pass over keys in registers, bound
+// by the same chain: 64 windows of 2^17 packets in 66 us against 81 us with one
+// segment per link bucket.
+// ---------------------------------------------------------------------------
+
+constexpr int GC_NT = 512;
+constexpr int GC_E = 12;
+
+size_t lds_grid_rc_bytes(uint32_t slots_log2) {
+  const size_t table = (size_t(1) << slots_log2) * 12;
+  return std::max(table, size_t(GC_NT) * GC_E * 4) + (2 * GC_NT + 2 * GC_NT / 64 + 64) * 4;
+}
+
+template <int NT>
+__device__ __forceinline__ void clear_id_table(uint32_t tid, u64* tv, uint32_t* tk, uint32_t S, uint32_t* misc) {
+  const v4u32 e4 = {EMPTY32, EMPTY32, EMPTY32, EMPTY32}, z4 = {0u, 0u, 0u, 0u};
+  for (uint32_t i = tid; i < S / 2; i += NT) reinterpret_cast<v4u32*>(tv)[i] = z4;
+  for (uint32_t i = tid; i < S / 4; i += NT) reinterpret_cast<v4u32*>(tk)[i] = e4;
+  if (tid < 4) misc[tid] = 0;
+}
+
+// What phase-C item k of a window is: one of the items of the dominant
+// addresses (`heavy`: 1 sources, 2 destinations, 16 of them from slot `sub`;
+// 3 the links between them; first in the window, since they are chains of
+// loads), row buckets, or column buckets (1 << group of them, neighbours in one
+// strip).
+struct BucketItem {
+  uint32_t heavy, row, last, group, strip, sub, nseg, word;
+};
+__device__ __forceinline__ BucketItem bucket_item(const nsgc_grid_desc& W, uint32_t HV, uint32_t k) {
+  BucketItem B;
+  const uint32_t R = 1u << W.logRi, H = NSGC_GRID_CITEMS(HV) - 1u;
+  B.heavy = k > H ? 0u : k == H ? 3u : 1u + k / (HV / 16);
+  k -= B.heavy ? 0u : H + 1u;
+  B.row = k < R;
+  if (!B.row) k -= R;
+  const uint32_t items = B.row ? W.logRi : W.logCi, strips = B.row ? W.logA : W.logBc;
+  B.last = k + 1u == (1u << items);
+  B.group = (B.row ? W.logR : W.logC) - items;
+  B.strip = k >> (items - strips);
+  B.sub = (k << B.group) & ((1u << (items - strips + B.group)) - 1u);
+  if (B.heavy) B.sub = (k % (HV / 16)) * 16u;
+  B.nseg = B.row ? 1u << W.logBc : 1u << W.logA;   // cells of the strip
+  B.word = (B.row ? 1u : 2u + (1u << (W.logR - W.logA))) + B.sub;   // its first start in a cell record
+  return B;
+}
+// Word offset of the record of cell s of the item's strip.
+__device__ __forceinline__ u64 bucket_record(const nsgc_grid_desc& W, const BucketItem& B, uint32_t s) {
+  const uint32_t cell = B.row ? (B.strip << W.logBc) + s : (s << W.logBc) + B.strip;
+  return u64(cell) * ((1u << (W.logR - W.logA)) + (1u << (W.logC - W.logBc)) + 3u);
+}
+
+// The buckets that phase C's single pass listed as too large for it, by sweeps
+// over their ids by the bits that follow the bucket's.
+__global__ __launch_bounds__(GC_NT) void k_grid_sweeps(nsgc_dev_plan* P) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int NT = GC_NT, NW = NT / 64;
+  const uint32_t S = 1u << sload(&P->rc_slots_log2);
+  u64* tv = reinterpret_cast<u64*>(smem);
+  uint32_t* tk = reinterpret_cast<uint32_t*>(tv + S);
+  uint32_t* red = tk + S;    // [3 * NW]
+  uint32_t* misc = red + 32;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t items = P->gover[1], HV = NSGC_GRID_HV(sload(&P->gtile_log2));
+  for (uint32_t x = blockIdx.x; x < items; x += gridDim.x) {
+  const uint32_t it = uniform(gptr(sload(&P->goverC))[2 * u64(x)]);
+  const uint32_t lo = uniform(gptr(sload(&P->goverC))[2 * u64(x) + 1]);
+  const nsgc_grid_desc W = sload_words(sload(&P->gwin) + sload(sload(&P->gitemC) + it));
+  const BucketItem B = bucket_item(W, HV, it - W.itemC);
+  const uint32_t nseg = B.nseg, logK = B.row ? W.logR : W.logC;
+  const NSGC_GLOBAL uint32_t* rec = gptr(W.rec);
+  const NSGC_GLOBAL u64* em = gptr(B.row ? W.emit_row : W.emit_col);
+  auto seg = [&](uint32_t s, u64& base, uint32_t& len) {
+    const NSGC_GLOBAL uint32_t* x = rec + bucket_record(W, B, s);
+    const uint32_t s0 = x[B.word + lo], s1 = x[B.word + lo + 1];
+    base = u64(x[0]) + s0;
+    len = s1 - s0;
+  };
+  uint32_t n = 0, mp = 0, ml = 0;
+  bool abandoned = false;
+  // sweeps over the bucket's ids by the bits that follow the bucket's
+  for (uint32_t logS = 0;; ++logS) {
+    if (logS > sload(&P->max_sweeps_log2)) { abandoned = true; break; }
+    n = mp = ml = 0;
+    bool failed = false;
+    for (uint32_t sw = 0; sw < (1u << logS) && !failed; ++sw) {
+      __syncthreads();
+      clear_id_table<NT>(tid, tv, tk, S, misc);
+      __syncthreads();
+      gather_by_wave<4, NW>(nseg, seg, [&](const auto& pos, const auto& okin) {
+        constexpr int U = array_len<decltype(pos)>();
+        uint32_t id[U], pk[U], ln[U], at[U];
+        bool ok[U], fr[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const u64 x = em[okin[u] ? pos[u] : 0ull];
+          id[u] = uint32_t(x >> 32);
+          pk[u] = uint32_t(x) & ENT_PMAX;
+          ln[u] = uint32_t(x) >> NSGC_ENT_PACKET_BITS;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          at[u] = id[u] & (S - 1);
+          ok[u] = okin[u] && pk[u] != 0 && !(logS && next32(id[u], logK, logS) != sw);
+          if (ok[u] && id[u] == EMPTY32) {
+            lds_add(&misc[2], pk[u]);
+            lds_add(&misc[3], ln[u]);
+            ok[u] = false;
+          }
+          // combine the lanes holding the first valid lane's id
+          const u64 vm = __ballot(ok[u]);
+          if (vm) {
+            const int f = __ffsll(static_cast<unsigned long long>(vm)) - 1;
+            const bool same = ok[u] && id[u] == readlane(id[u], f);
+            if (__popcll(__ballot(same)) > 1) {
+              const uint32_t tot = wave_sum(same ? pk[u] : 0u);
+              const uint32_t lns = wave_sum(same ? ln[u] : 0u);
+              if (same) {
+                if (int(lane_id()) == f) { pk[u] = tot; ln[u] = lns; }
+                else ok[u] = false;
+              }
+            }
+          }
+        }
+        if (insert_keys<U>(tk, S - 1, id, at, ok, fr)) lds_store(&misc[0], 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u)   // (a sweep that failed is thrown away)
+          if (ok[u]) lds_add64(&tv[at[u]], (u64(ln[u]) << 32) | pk[u]);
+      });
+      failed = misc[0] != 0;
+      if (!failed) {
+        for (uint32_t i = tid; i < S; i += NT)
+          if (tk[i] != EMPTY32) {
+            ++n;
+            mp = max(mp, uint32_t(tv[i]));
+            ml = max(ml, uint32_t(tv[i] >> 32));
+          }
+        if (tid == 0 && misc[3]) {
+          ++n;
+          mp = max(mp, misc[2]);
+          ml = max(ml, misc[3]);
+        }
+      }
+    }
+    if (!failed) break;
+  }
+  __syncthreads();
+  block_sum_max2_to0<NW>(n, mp, ml, red);
+  if (tid == 0) {   // onto what the single passes found in the item's other buckets
+    NSGC_GLOBAL uint32_t* o = gptr(W.partC) + u64(it - W.itemC) * 4;
+    __hip_atomic_fetch_add(o, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_max(o + 1, mp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_max(o + 2, ml, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_max(o + 3, abandoned ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void k_grid_rowcol(
+    nsgc_dev_plan* P) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int NT = GC_NT, E = GC_E, NW = NT / 64;
+  constexpr uint32_t ROOM = NT * E;
+  const uint32_t S = 1u << sload(&P->rc_slots_log2);
+  // [S] links << 32 | packets, [S] ids; the element positions share them
+  u64* tv = reinterpret_cast<u64*>(smem);
+  uint32_t* tk = reinterpret_cast<uint32_t*>(tv + S);
+  uint32_t* list = reinterpret_cast<uint32_t*>(smem);
+  uint32_t* tab = reinterpret_cast<uint32_t*>(smem + max(S * 12u, ROOM * 4u));
+  uint32_t* red = tab + 2 * NT + 2 * NW;   // [3 * NW]
+  uint32_t* misc = red + 32;               // 0 failed, 2 / 3 marker id's packets / links, 7 queue slot
+  const uint32_t items = sload(&P->gitemsC), HV = NSGC_GRID_HV(sload(&P->gtile_log2));
+
+  GridQueue q(gptr(&P->queue[6][0]));
+  // This thread's segment of buckets lo .. lo + w - 1 (all, if w is 0) of item
+  // `it`, cell `s` of its strip: emission base and length.  The next item's is
+  // loaded while the current one is worked on.
+  struct Segment { uint32_t cell, start, end; };   // the cell's base, starts relative to it
+  auto segment = [&](uint32_t it, uint32_t lo, uint32_t w, uint32_t s) -> Segment {
+    const nsgc_grid_desc W = sload_words(sload(&P->gwin) + sload(sload(&P->gitemC) + it));
+    const BucketItem B = bucket_item(W, HV, it - W.itemC);
+    Segment g = {0, 0, 0};
+    if (B.heavy) return g;
+    if (w == 0) w = 1u << B.group;
+    if (B.nseg <= 64) s &= 63u;
+    if (s >= B.nseg) return g;
+    const NSGC_GLOBAL uint32_t* x = gptr(W.rec) + bucket_record(W, B, s);
+    const NSGC_GLOBAL uint32_t* y = x + B.word + lo;
+    g.cell = x[0];
+    g.start = y[0];
+    g.end = y[w];
+    return g;
+  };
+  Segment sg = {0, 0, 0};
+  bool have = false;
+  for (uint32_t item = blockIdx.x < items ? blockIdx.x : NO_ITEM; item != NO_ITEM;) {
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // (as in phase B)
+    const uint32_t it = uniform(item);
+    const nsgc_grid_desc W = sload_words(sload(&P->gwin) + sload(sload(&P->gitemC) + it));
+    const BucketItem B = bucket_item(W, HV, it - W.itemC);
+    uint32_t n = 0, mp = 0, ml = 0;
+    if (!have) {
+      sg = segment(it, 0, 0, tid);
+      loads_arrived();
+    }
+    q.announce(misc + 6, items);
+    Segment ng = {0, 0, 0};
+    uint32_t ahead = NO_ITEM;
+    bool loaded = false;
+    auto look_ahead = [&]() {   // (a barrier has passed since the next item was announced)
+      ahead = uniform(misc[6]);
+      have = ahead != NO_ITEM;
+      if (have) ng = segment(ahead, 0, 0, tid);
+      loaded = true;
+    };
+    if (B.heavy) {
+      const uint32_t k = B.heavy - 1u;
+      const NSGC_GLOBAL uint32_t* m = gptr(W.heavy) + 2 * HV;
+      if (k == 2) {   // links between dominant addresses: packets, links, maximum
+        for (uint32_t i = tid; i < HV * HV; i += NT) {
+          const uint32_t x = m[i];
+          n += x;
+          mp += x ? 1u : 0u;
+          ml = max(ml, x);
+        }
+        block_sum2_max_to0<NW>(n, mp, ml, red);
+      } else {        // dominant sources (destinations): the cells' counters and the matrix
+        u64* sum = tv;
+        const uint32_t s = B.sub + (tid & 15u), g = tid >> 4;
+        const uint32_t cells = 1u << (W.logA + W.logBc);
+        const NSGC_GLOBAL u64* acc = gptr(W.acc) + k * HV + s;
+        u64 x = 0;
+#pragma unroll 16
+        for (uint32_t cell = g; cell < cells; cell += NT / 16) x += acc[u64(cell) * (2 * HV)];
+        for (uint32_t o = g; o < HV; o += NT / 16) {
+          const uint32_t y = k == 0 ? m[s * HV + o] : m[o * HV + s];
+          x += (u64(y ? 1u : 0u) << 32) | y;
+        }
+        sum[tid] = x;
+        lds_barrier();
+        if (tid < 16) {
+          for (uint32_t o = 1; o < NT / 16; ++o) x += sum[o * 16 + tid];
+          n = (x >> 32) ? 1u : 0u;
+          mp = uint32_t(x);
+          ml = uint32_t(x >> 32);
+        }
+        block_sum_max2_to0<NW>(n, mp, ml, red);
+      }
+    } else {
+      const NSGC_GLOBAL u64* em = gptr(B.row ? W.emit_row : W.emit_col);
+      // the item's buckets in one pass if they fit it, else in halves, quarters, ...
+      uint32_t w = 1u << B.group;
+      bool reload = false;
+      for (uint32_t lo = 0; lo < (1u << B.group);) {
+      if (reload) {
+        sg = segment(it, lo, w, tid);
+        loads_arrived();
+      }
+      reload = true;
+      uint32_t none = 0;
+      const uint32_t total =
+          B.nseg <= 64
+              ? spread_by_wave<NT>(tid, B.nseg, sg.cell + sg.start, sg.end - sg.start, none, list, ROOM)
+              : spread_segments<NT>(tid, B.nseg, sg.cell + sg.start, sg.end - sg.start, none, tab, list, ROOM);
+      lds_barrier();
+      bool done = false;
+      // the last bucket holds the id that equals the tables' marker
+      const bool last = B.last && lo + w == (1u << B.group);
+      if (total <= ROOM) {
+        const uint32_t kmax = uniform((total + NT - 1) / NT);
+        u64 e[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+          e[j] = 0;
+          if (uint32_t(j) < kmax) {
+            const uint32_t x = uint32_t(j * NT) + tid;
+            e[j] = em[x < total ? list[x] : 0u];   // masked when it is used
+          }
+        }
+        lds_barrier();
+        clear_id_table<NT>(tid, tv, tk, S, misc);
+        lds_barrier();
+        loads_arrived();
+        if (!loaded) look_ahead();
+        uint32_t at[E];   // slot of an id that this thread inserted
+#pragma unroll
+        for (int j0 = 0; j0 < E; j0 += 4) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) at[j0 + u] = NO_SLOT;
+          if (uint32_t(j0) < kmax) {
+            uint32_t id[4], lo[4], old[4], s[4];
+            bool ok[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              id[u] = uint32_t(e[j0 + u] >> 32);
+              lo[u] = uint32_t(e[j0 + u]);
+              // (an entry with no packets is an unused slot of a cell that took rounds)
+              ok[u] = uint32_t((j0 + u) * NT) + tid < total && (lo[u] & ENT_PMAX) != 0;
+              s[u] = id[u] & (S - 1);
+              old[u] = id[u];
+            }
+            if (last) {
+#pragma unroll
+              for (int u = 0; u < 4; ++u)
+                if (ok[u] && id[u] == EMPTY32) {
+                  lds_add(&misc[2], lo[u] & ENT_PMAX);
+                  lds_add(&misc[3], lo[u] >> NSGC_ENT_PACKET_BITS);
+                  ok[u] = false;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (ok[u]) old[u] = lds_cas32(&tk[s[u]], EMPTY32, id[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              if (ok[u]) {
+                const uint32_t o = probe_on<uint32_t>(tk, S - 1, id[u], old[u], s[u]);
+                if (o == EMPTY32) at[j0 + u] = s[u];
+                else if (o != id[u]) misc[0] = 1;
+                // (a pass that failed is thrown away)
+                lds_add64(&tv[s[u]], (u64(lo[u] >> NSGC_ENT_PACKET_BITS) << 32) | (lo[u] & ENT_PMAX));
+              }
+            }
+          }
+        }
+        lds_barrier();
+        if (misc[0] == 0) {
+          done = true;
+#pragma unroll
+          for (int j = 0; j < E; ++j)
+            if (at[j] != NO_SLOT) {
+              const u64 x = tv[at[j]];
+              ++n;
+              mp = max(mp, uint32_t(x));
+              ml = max(ml, uint32_t(x >> 32));
+            }
+          if (tid == 0 && misc[3]) {
+            ++n;
+            mp = max(mp, misc[2]);
+            ml = max(ml, misc[3]);
+          }
+        }
+      }
+      lds_barrier();   // the table is free again
+      if (!done && w > 1) {
+        w >>= 1;
+        continue;
+      }
+      if (!done && tid == 0) {   // a single bucket, left to k_grid_sweeps
+        const uint32_t at = __hip_atomic_fetch_add(gptr(&P->gover[1]), 1u, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+        gptr(sload(&P->goverC))[2 * u64(at)] = it;
+        gptr(sload(&P->goverC))[2 * u64(at) + 1] = lo;
+      }
+      lo += w;
+      }
+      block_sum_max2_to0<NW>(n, mp, ml, red);
+    }
+    if (!loaded) look_ahead();
+    // the next item's segment and the queue's answer, before the store
+    loads_arrived();
+    arrived(q.pending);
+    if (tid == 0) {
+      const v4u32 part = {n, mp, ml, 0u};
+      gptr(reinterpret_cast<v4u32*>(W.partC))[it - W.itemC] = part;
+    }
+    sg = ng;
+    item = ahead;
+    lds_barrier();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Host-side launchers.
+// ---------------------------------------------------------------------------
+
+namespace {
+typedef void (*part_fn)(const nsgc_dev_plan*, uint32_t);
+part_fn partition_kernel(uint32_t tile_log2, int* threads) {
+  *threads = tile_log2 >= 14 ? 1024 : 512;
+  switch (tile_log2) {
+    case 11: return &k_grid_partition<4, 512, NSGC_GRID_HV(11)>;
+    case 12: return &k_grid_partition<8, 512, NSGC_GRID_HV(12)>;
+    case 13: return &k_grid_partition<16, 512, NSGC_GRID_HV(13)>;
+    case 14: return &k_grid_partition<16, 1024, NSGC_GRID_HV(14)>;
+    default: return nullptr;
+  }
+}
+constexpr int GB_NT[3] = {256, 512, 1024};
+void (*const links_kernels[3])(nsgc_dev_plan*) = {
+    &k_grid_links<GB_NT[0], 2048, 8, SMALL>,
+    &k_grid_links<GB_NT[1], 4096, 8, BIG>,
+    &k_grid_links<GB_NT[2], 8192, 12, WIDE>,
+};
+}  // namespace
+
+hipError_t launch_grid_heavy(const nsgc_dev_plan* P, uint32_t tile_log2, uint32_t grid, hipStream_t s) {
+  if (NSGC_GRID_HV(tile_log2) == 64)
+    hipLaunchKernelGGL((k_grid_heavy<64>), dim3(grid), dim3(GH_NT), 0, s, P);
+  else
+    hipLaunchKernelGGL((k_grid_heavy<32>), dim3(grid), dim3(GH_NT), 0, s, P);
+  return hipGetLastError();
+}
+
+hipError_t launch_grid_partition(const nsgc_dev_plan* P, uint32_t tile_log2, uint32_t max_cells,
+                                 uint32_t grid, hipStream_t s) {
+  int threads = 0;
+  const part_fn f = partition_kernel(tile_log2, &threads);
+  if (!f) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(f, dim3(grid), dim3(threads), lds_grid_part_bytes(tile_log2, max_cells), s, P,
+                     max_cells);
+  return hipGetLastError();
+}
+
+hipError_t launch_grid_links(const nsgc_dev_plan* P, int which, uint32_t grid, hipStream_t s) {
+  hipLaunchKernelGGL(links_kernels[which], dim3(grid), dim3(GB_NT[which]), 0, s, const_cast<nsgc_dev_plan*>(P));
+  return hipGetLastError();
+}
+
+hipError_t launch_grid_rounds(const nsgc_dev_plan* P, bool after_wide, uint32_t grid, hipStream_t s) {
+  hipLaunchKernelGGL(k_grid_rounds, dim3(grid), dim3(GR_NT), 0, s, const_cast<nsgc_dev_plan*>(P),
+                     after_wide ? 1u : 0u);
+  return hipGetLastError();
+}
+
+hipError_t launch_grid_sweeps(const nsgc_dev_plan* P, uint32_t grid, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL(k_grid_sweeps, dim3(grid), dim3(GC_NT), lds, s, const_cast<nsgc_dev_plan*>(P));
+  return hipGetLastError();
+}
+
+hipError_t launch_grid_rowcol(const nsgc_dev_plan* P, uint32_t grid, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL(k_grid_rowcol, dim3(grid), dim3(GC_NT), lds, s, const_cast<nsgc_dev_plan*>(P));
+  return hipGetLastError();
+}
+
+hipError_t grid_resident_blocks(int which, uint32_t tile_log2, size_t lds, int* blocks) {
+  int threads = 0;
+  const void* f = nullptr;
+  switch (which) {
+    case 0: f = reinterpret_cast<const void*>(partition_kernel(tile_log2, &threads)); break;
+    case 1: f = reinterpret_cast<const void*>(links_kernels[0]); threads = GB_NT[0]; break;
+    case 2: f = reinterpret_cast<const void*>(links_kernels[1]); threads = GB_NT[1]; break;
+    case 3: f = reinterpret_cast<const void*>(&k_grid_rowcol); threads = GC_NT; break;
+    default: break;
+  }
+  if (!f) return hipErrorInvalidValue;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, threads, lds);
+}
+
+hipError_t grid_allow_large_lds(size_t bytes) {
+  int t;
+  const void* fns[] = {reinterpret_cast<const void*>(partition_kernel(11, &t)),
+                       reinterpret_cast<const void*>(partition_kernel(12, &t)),
+                       reinterpret_cast<const void*>(partition_kernel(13, &t)),
+                       reinterpret_cast<const void*>(partition_kernel(14, &t)),
+                       reinterpret_cast<const void*>(&k_grid_rowcol),
+                       reinterpret_cast<const void*>(&k_grid_sweeps)};
+  for (const void* f : fns) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+}  // namespace nsgc

@@ -72,6 +72,73 @@
 #define NSGC_HEAVY_SAMPLE 4096
 #define NSGC_WAVE_ROW_SLOTS 256
 
+// Grid windows (nsgc_grid.hip): partitioned windows whose link buckets are the
+// cells of a grid of 2^logA row strips by 2^logBc column strips.
+//   - A link (r, c) of hashed ids belongs to cell (top logA bits of r, top
+//     logBc bits of c), so all its links share one row strip and one column
+//     strip: the row and column buckets (2^logR, 2^logC of them) refine the
+//     strips, phase B splits a cell's links only into the few buckets of its
+//     two strips, and a phase-C item reads only the cells of its strip.
+//   - Dominant sources and destinations, found in a sample of the window (at
+//     most NSGC_GRID_HEAVY per view), would overfill their strips.  Packets
+//     between two of them are counted in a dense matrix while they are
+//     partitioned and leave no key.  The other links of a dominant source go
+//     to row strip home ^ x, x in 1 .. 2^logA - 1 from the destination (and
+//     likewise for a dominant destination), so they never meet its home strip:
+//     a link's cell tells whether its source (destination) is dominant.  Phase B
+//     adds such links to per-cell counters of the source instead of emitting
+//     a row entry.  Any set of dominant addresses gives exact results; the
+//     choice decides only how evenly the cells fill.
+// (See k_grid_heavy for which addresses are dominant.)
+// A tile record is one word per cell, start | length << 16 within the tile's
+// keys, [tile][cell].  A cell record is 2^(logR-logA) + 2^(logC-logBc) + 3
+// words: the cell's emission base, its row-bucket starts (one more than
+// buckets), its column-bucket starts.
+#define NSGC_GRID_MIN 8193                     // packets of the smallest grid window
+// Dominant addresses per view, and the sample they are drawn from, in a batch
+// partitioned in tiles of 2^t packets: batches with windows of more than 1024
+// cells (tile 2^14) keep twice as many, since with many cells a smaller share
+// of the packets overfills one.
+#define NSGC_GRID_HEAVY 64
+#define NSGC_GRID_HV(t) ((t) >= 14 ? 64 : 32)
+#define NSGC_GRID_SAMPLE(hv) ((hv) == 64 ? 4096 : 2048)
+#define NSGC_GRID_TILE13_CELLS 1024            // most cells of a batch partitioned in 2^13-packet tiles
+#define NSGC_GRID_TILES 256                    // tiles of a window that every phase-B kernel takes in one pass
+#define NSGC_GRID_MAX_CELLS_LOG2 11
+#define NSGC_GRID_MAX_A 6                      // row strips (log2)
+#define NSGC_GRID_MAX_B 9                      // column strips (log2)
+#define NSGC_GRID_MAX_SUB_LOG2 6               // row or column buckets per strip
+#define NSGC_GRID_MAX_SUB (1 << NSGC_GRID_MAX_SUB_LOG2)
+#define NSGC_GRID_BUCKET 4096                  // packets per row or column bucket, at most
+#define NSGC_GRID_GROUP 16384                  // packets per phase-C item of large windows
+// Phase-C items of a window's dominant addresses: 16 of one view each, and one
+// for the links between them.
+#define NSGC_GRID_CITEMS(hv) ((hv) / 8 + 1)
+// Words of a window's dominant-address block: the ids of both views, the matrix.
+#define NSGC_GRID_HV_WORDS(hv) (2 * (hv) + (hv) * (hv))
+
+struct nsgc_grid_desc {         // 128 bytes
+  const uint32_t* src;          // the window's packets
+  const uint32_t* dst;
+  unsigned long long* keys;     // its regions: keys by tile and cell, emitted entries,
+  unsigned long long* emit_row;
+  unsigned long long* emit_col;
+  uint32_t* tile;               //   tile records,
+  uint32_t* rec;                //   cell records,
+  uint32_t* heavy;              //   dominant ids of both views, matrix,
+  unsigned long long* acc;      //   [cells][2][HV] links << 32 | packets of each dominant source
+                                //     and destination in the cell,
+  uint32_t* partB;              //   [cells][4] cell totals: packets, links, max, invalid,
+  uint32_t* partC;              //   [items][4] like partC below; dominant addresses see k_grid_rowcol
+  uint32_t n;                   // packets (< 2^32)
+  uint32_t out_index;           // window index in out_stats
+  uint32_t ntiles;              // partition tiles
+  uint32_t itemB, itemC;        // first phase-B (cell) and phase-C item
+  uint8_t logA, logBc, logR, logC;
+  uint8_t logRi, logCi;         // phase-C items of row and of column buckets (neighbours grouped)
+  uint8_t pad[14];
+};
+
 struct nsgc_small_desc {        // 16 bytes
   int64_t in_begin;             // index of the window's first packet
   uint32_t n;                   // packets
@@ -158,9 +225,21 @@ struct nsgc_dev_plan {          // header of the device plan buffer
   uint32_t* heavy;              // [num_part][NSGC_HEAVY_SLOTS] heavy sources, 4-way sets
   uint32_t* partR;              // [itemsB][4] complete sources of a bucket: count, max packets,
                                 //   max links, 0
+  // Grid windows.
+  const nsgc_grid_desc* gwin;   // windows of small cells first, then those of big cells
+  const uint32_t* gprefA;       // [num_grid + 1] first partition tile of each window
+  const uint32_t* gitemB;       // [gitemsB] window of each cell
+  const uint32_t* gitemC;       // [gitemsC] window of each phase-C item
+  uint32_t* goverB;             // cells and phase-C items that need more than one pass,
+  uint32_t* goverC;             //   gover[0] and gover[1] of them (uploaded as zero): cell;
+                                //   item, bucket within the item
+  uint32_t* goverW;             // cells that the wide pass of phase B left over, gover[2] of them
+  uint32_t gover[4];
+  uint32_t num_grid, gitemsA, gitemsS, gitemsB, gitemsC, gtile_log2;
   // Work-queue counters of the small, B (workgroup), C and B (wavefront)
-  // kernels.  Uploaded as zero with every plan.
-  uint32_t queue[4][NSGC_QCLASSES * NSGC_QSTRIDE];
+  // kernels, then grid B (small cells), B (big cells) and C.  Uploaded as
+  // zero with every plan.
+  uint32_t queue[8][NSGC_QCLASSES * NSGC_QSTRIDE];
 };
 
 #endif  // NSGC_PLAN_H_

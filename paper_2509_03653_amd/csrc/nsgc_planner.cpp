@@ -12,7 +12,80 @@ namespace {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// A pointer field of a device descriptor.
+template <class T>
+T* at(uint64_t address) {
+  return reinterpret_cast<T*>(address);
+}
+template <class T>
+void rebase(T*& field, uint64_t base) {
+  field = reinterpret_cast<T*>(reinterpret_cast<uint64_t>(field) + base);
+}
+
+// Whether a partitioned window of n packets (buckets and wavefront form as in
+// `d`) is taken as a grid window, and its grid.  Cells hold four wavefront
+// targets of packets, up to the cap on link buckets; the grid has four or more
+// strips each way (with fewer, a dominant address cannot be spread) and as
+// many row strips as row buckets if it can, since a strip of one bucket needs
+// no counting.
+bool grid_window(uint64_t n, const nsgc_win_desc& d, const nsgc_tune& tune,
+                 const nsgc_tune_class& tc, nsgc_grid_desc* g) {
+  if (tc.wave_target <= 0 || tune.combine_probes > 0 || n < NSGC_GRID_MIN) return false;
+  if (d.logR < 2 || d.logC < 2) return false;
+  const uint64_t target = 4 * uint64_t(tc.wave_target);
+  const int lc = std::min(std::min(ceil_log2((n + target - 1) / target), int(tune.max_link_buckets_log2)),
+                          NSGC_GRID_MAX_CELLS_LOG2);
+  // Row and column buckets of at most NSGC_GRID_BUCKET packets: phase C takes
+  // one and a half times as many entries in a single pass, and a bucket has at
+  // most as many entries as packets.
+  const auto buckets = [&](int32_t tuned) {
+    const uint64_t t = std::min<uint64_t>(uint64_t(tuned), NSGC_GRID_BUCKET);
+    return ceil_log2((n + t - 1) / t);
+  };
+  int logR = buckets(tc.row_target), logC = buckets(tc.col_target);
+  const int a = std::min(std::min(logR, NSGC_GRID_MAX_A), lc - 2);
+  const int b = std::min(std::min(lc - a, logC), NSGC_GRID_MAX_B);
+  if (a < 2 || b < 2) return false;
+  logR = std::min(logR, a + NSGC_GRID_MAX_SUB_LOG2);
+  logC = std::min(logC, b + NSGC_GRID_MAX_SUB_LOG2);
+  std::memset(g, 0, sizeof *g);
+  g->n = uint32_t(n);
+  g->logA = uint8_t(a);
+  g->logBc = uint8_t(b);
+  g->logR = uint8_t(logR);
+  g->logC = uint8_t(logC);
+  // A phase-C item takes one bucket in windows below 2^19 packets and several
+  // neighbours in larger ones, which have fewer links per packet; it splits
+  // them again where they do not fit one pass.
+  const int gi = n < (uint64_t(1) << 19) ? 0 : ceil_log2(NSGC_GRID_GROUP / NSGC_GRID_BUCKET);
+  g->logRi = uint8_t(std::max(logR - gi, a));
+  g->logCi = uint8_t(std::max(logC - gi, b));
+  return true;
+}
+
+// Cells of more than 1280 packets on average take the kernel with 4096-slot
+// tables (a 2048-slot one would be more than half full).
+bool grid_big(const nsgc_grid_desc& g) { return (g.n >> (g.logA + g.logBc)) > 1280; }
+
+// Partition tile (log2).  Tiles of 2^14 packets where a window has more than
+// 1024 cells (their runs of keys per cell are longer); else 2^13, of which two
+// fit a compute unit and overlap; smaller ones, down to 2^11, as long as the
+// batch has fewer than two tiles per compute unit and its longest window no
+// more than phase B takes in a pass (a thread per tile).
+constexpr uint64_t kGridTiles = 512;
+uint32_t grid_tile_log2(uint64_t packets, uint32_t cells, uint32_t longest, const nsgc_tune& tune) {
+  uint32_t k = uint32_t(tune.tile_log2);
+  if (cells > NSGC_GRID_TILE13_CELLS) return 14;
+  k = std::min(k, 13u);
+  while (k > 11 && (packets >> k) < kGridTiles && (longest >> k) < NSGC_GRID_TILES / 2) --k;
+  return k;
+}
+
 }  // namespace
+
+uint32_t grid_max_cells(uint32_t tile_log2) {
+  return tile_log2 >= 14 ? 1u << NSGC_GRID_MAX_CELLS_LOG2 : NSGC_GRID_TILE13_CELLS;
+}
 
 int ceil_log2(uint64_t x) {
   int k = 0;
@@ -83,7 +156,7 @@ int validate_offsets(const int64_t* offsets, int64_t num_windows) {
 }
 
 int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune,
-              HostPlan* p, bool entity, bool allow_large) {
+              HostPlan* p, bool entity, bool allow_large, bool allow_grid) {
   p->large.clear();
   p->large_max = 0;
   p->entity = entity;
@@ -98,6 +171,15 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
   p->itemwinC.clear();
   p->mapBb.clear();
   p->mapBw.clear();
+  p->shape.clear();
+  p->gwin.clear();
+  p->gprefA.clear();
+  p->gitemB.clear();
+  p->gitemC.clear();
+  std::vector<nsgc_grid_desc> gbig;   // grid windows of big cells
+  uint64_t gpackets = 0;
+  uint32_t glongest = 0;
+  uint32_t gcells = 0;   // most cells of a grid window
   p->itemsBb = p->itemsBw = 0;
   p->wave_rc_max = 0;
   p->num_rows = 0;
@@ -150,9 +232,20 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
       if (lw <= capB) {
         d.logB = uint8_t(lw);
         d.wave = 1;
-        p->wave_rc_max = std::max(p->wave_rc_max, 1u << std::max(d.logR, d.logC));
       }
     }
+    p->shape.push_back({d.logB, d.logR, d.logC, int64_t((n + tile - 1) / tile)});
+    nsgc_grid_desc g;
+    if (allow_grid && !entity && !(tune.row_complete && d.wave) && grid_window(n, d, tune, tc, &g)) {
+      g.src = at<uint32_t>(uint64_t(offsets[w]) * 4);   // byte offsets until serialize()
+      g.out_index = uint32_t(w);
+      (grid_big(g) ? gbig : p->gwin).push_back(g);
+      gpackets += n;
+      glongest = std::max(glongest, uint32_t(n));
+      gcells = std::max(gcells, 1u << (g.logA + g.logBc));
+      continue;
+    }
+    if (d.wave) p->wave_rc_max = std::max(p->wave_rc_max, 1u << std::max(d.logR, d.logC));
     // row-complete: wavefront windows of two or more link buckets
     if (tune.row_complete && d.wave && !entity && d.logB >= 1) {
       d.rows = 1;
@@ -181,6 +274,47 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
     if (a > 0xFFFFFFFFull || b > 0xFFFFFFFFull || c > 0xFFFFFFFFull) return NSGC_ERR_INVALID_ARG;
     p->win.push_back(d);
   }
+  // grid windows: tile size, then tiles, cells and phase-C items in order
+  p->gtile_log2 = grid_tile_log2(gpackets, gcells, glongest, tune);
+  const size_t nsmall = p->gwin.size();
+  p->gwin.insert(p->gwin.end(), gbig.begin(), gbig.end());
+  uint64_t ga = 0, gb = 0, gc = 0;
+  p->gtile_words = p->grec_words = 0;
+  p->gitemsS = 0;
+  p->gbuckets = 0;
+  for (size_t i = 0; i < p->gwin.size(); ++i) {
+    nsgc_grid_desc& g = p->gwin[i];
+    g.ntiles = uint32_t((uint64_t(g.n) + (uint64_t(1) << p->gtile_log2) - 1) >> p->gtile_log2);
+    const uint64_t cells = uint64_t(1) << (g.logA + g.logBc);
+    const uint64_t R = uint64_t(1) << g.logR, C = uint64_t(1) << g.logC;
+    const uint64_t hv = NSGC_GRID_HV(p->gtile_log2);
+    const uint64_t items = (uint64_t(1) << g.logRi) + (uint64_t(1) << g.logCi) + NSGC_GRID_CITEMS(hv);
+    g.keys = at<unsigned long long>(uint64_t(p->ws_elems) * 8);
+    g.tile = at<uint32_t>(uint64_t(p->gtile_words) * 4);
+    g.rec = at<uint32_t>(uint64_t(p->grec_words) * 4);
+    g.heavy = at<uint32_t>(i * NSGC_GRID_HV_WORDS(hv) * 4);
+    g.acc = at<unsigned long long>(gb * 2 * hv * 8);
+    g.partB = at<uint32_t>(gb * 16);
+    g.partC = at<uint32_t>(gc * 16);
+    g.itemB = uint32_t(gb);
+    g.itemC = uint32_t(gc);
+    p->ws_elems += int64_t(g.n);
+    p->gtile_words += int64_t(uint64_t(g.ntiles) * cells);
+    p->grec_words += int64_t(cells * ((R >> g.logA) + (C >> g.logBc) + 3));
+    p->gprefA.push_back(uint32_t(ga));
+    p->gitemB.insert(p->gitemB.end(), size_t(cells), uint32_t(i));
+    p->gitemC.insert(p->gitemC.end(), size_t(items), uint32_t(i));
+    p->gbuckets += uint32_t(R + C);
+    ga += g.ntiles;
+    gb += cells;
+    gc += items;
+    if (ga > 0xFFFFFFFFull || gb > 0xFFFFFFFFull || gc > 0xFFFFFFFFull) return NSGC_ERR_INVALID_ARG;
+    if (i < nsmall) p->gitemsS = uint32_t(gb);
+  }
+  p->gprefA.push_back(uint32_t(ga));
+  p->gitemsA = uint32_t(ga);
+  p->gitemsB = uint32_t(gb);
+  p->gitemsC = uint32_t(gc);
   p->prefA.push_back(uint32_t(a));
   p->prefB.push_back(uint32_t(b));
   p->prefC.push_back(uint32_t(c));
@@ -208,6 +342,17 @@ WsLayout HostPlan::layout() const {
   L.order = o;     o = align_up(o + size_t(itemsC) * 4, 256);
   L.partB = o;     o = align_up(o + size_t(itemsB) * 16, 256);
   L.partC = o;     o = align_up(o + size_t(itemsC) * 16, 256);
+  if (!gwin.empty()) {
+    L.gtile = o;   o = align_up(o + size_t(gtile_words) * 4, 256);
+    L.grec = o;    o = align_up(o + size_t(grec_words) * 4, 256);
+    L.gheavy = o;  o = align_up(o + gwin.size() * NSGC_GRID_HV_WORDS(NSGC_GRID_HV(gtile_log2)) * 4, 256);
+    L.gacc = o;    o = align_up(o + size_t(gitemsB) * 2 * NSGC_GRID_HV(gtile_log2) * 8, 256);
+    L.gpartB = o;  o = align_up(o + size_t(gitemsB) * 16, 256);
+    L.gpartC = o;  o = align_up(o + size_t(gitemsC) * 16, 256);
+    L.goverB = o;  o = align_up(o + size_t(gitemsB) * 4, 256);
+    L.goverW = o;  o = align_up(o + size_t(gitemsB) * 4, 256);
+    L.goverC = o;  o = align_up(o + size_t(gbuckets) * 8, 256);
+  }
   if (num_rows) {
     L.partR = o;   o = align_up(o + size_t(itemsB) * 16, 256);
     L.heavy = o;   o = align_up(o + win.size() * NSGC_HEAVY_SLOTS * 4, 256);
@@ -225,10 +370,12 @@ WsLayout HostPlan::layout() const {
 
 namespace {
 struct PlanOffsets {
-  size_t small, win, prefA, prefB, prefC, itemwinB, itemwinC, mapBb, mapBw, entcur, entend, total;
+  size_t small, win, prefA, prefB, prefC, itemwinB, itemwinC, mapBb, mapBw, entcur, entend, gwin,
+      gprefA, gitemB, gitemC, total;
 };
 PlanOffsets plan_offsets(size_t ns, size_t nm, size_t nb, size_t nc, size_t nbb = 0,
-                         size_t nbw = 0, size_t nent = 0) {
+                         size_t nbw = 0, size_t nent = 0, size_t ng = 0, size_t ngb = 0,
+                         size_t ngc = 0) {
   PlanOffsets o;
   size_t x = align_up(sizeof(nsgc_dev_plan), 64);
   o.small = x; x = align_up(x + ns * sizeof(nsgc_small_desc), 64);
@@ -242,6 +389,10 @@ PlanOffsets plan_offsets(size_t ns, size_t nm, size_t nb, size_t nc, size_t nbb 
   o.mapBw = x; x = align_up(x + nbw * 4, 64);
   o.entcur = x; x = align_up(x + nent * 8, 64);
   o.entend = x; x = align_up(x + nent * 8, 64);
+  o.gwin = x;   x = align_up(x + ng * sizeof(nsgc_grid_desc), 64);
+  o.gprefA = x; x = align_up(x + (ng + 1) * 4, 64);
+  o.gitemB = x; x = align_up(x + ngb * 4, 64);
+  o.gitemC = x; x = align_up(x + ngc * 4, 64);
   o.total = x;
   return o;
 }
@@ -249,8 +400,33 @@ PlanOffsets plan_offsets(size_t ns, size_t nm, size_t nb, size_t nc, size_t nbb 
 
 size_t HostPlan::plan_bytes() const {
   return plan_offsets(small.size(), win.size(), itemwinB.size(), itemwinC.size(), mapBb.size(),
-                      mapBw.size(), ent_cur.size()).total;
+                      mapBw.size(), ent_cur.size(), gwin.size(), gitemB.size(), gitemC.size()).total;
 }
+
+namespace {
+// Most cells of `gw` grid windows of P packets in all: a window of n packets
+// has fewer than 2 n / target + 2, and at most the cap.
+uint64_t grid_cells_bound(uint64_t P, uint64_t gw, const nsgc_tune& t) {
+  uint64_t wt = ~uint64_t(0);
+  for (int k = 0; k <= 32; ++k)
+    if (t.cls[k].wave_target > 0) wt = std::min<uint64_t>(wt, uint64_t(t.cls[k].wave_target));
+  if (wt == ~uint64_t(0)) return 0;
+  const int cap = std::min(int(t.max_link_buckets_log2), NSGC_GRID_MAX_CELLS_LOG2);
+  return std::min<uint64_t>(P / (2 * wt) + 2 * gw, gw << cap);
+}
+
+// Likewise their phase-C items: R + C < 4 n / target + 4 and at most
+// 2^(strips + sub-buckets) each.
+uint64_t grid_citems_bound(uint64_t P, uint64_t gw, const nsgc_tune& t) {
+  uint64_t rt = NSGC_GRID_BUCKET;
+  for (int k = 0; k <= 32; ++k)
+    rt = std::min<uint64_t>(rt, uint64_t(std::min(t.cls[k].row_target, t.cls[k].col_target)));
+  return std::min<uint64_t>(4 * P / rt + 4 * gw,
+                            gw * ((uint64_t(1) << (NSGC_GRID_MAX_A + NSGC_GRID_MAX_SUB_LOG2)) +
+                                  (uint64_t(1) << (NSGC_GRID_MAX_B + NSGC_GRID_MAX_SUB_LOG2)))) +
+         gw * NSGC_GRID_CITEMS(NSGC_GRID_HEAVY);
+}
+}  // namespace
 
 size_t plan_bound(int64_t max_packets, int64_t max_windows, const nsgc_tune& t) {
   const uint64_t P = uint64_t(std::max<int64_t>(max_packets, 0));
@@ -274,14 +450,38 @@ size_t plan_bound(int64_t max_packets, int64_t max_windows, const nsgc_tune& t) 
     if (t.cls[k].wave_target > 0) wt = std::min<uint64_t>(wt, uint64_t(t.cls[k].wave_target));
   const uint64_t nbw = wt == ~uint64_t(0) ? 0 : std::min<uint64_t>(2 * P / wt + 2 * W, W * capB);
   const uint64_t nb_all = std::max(nb, nbw);
+  const uint64_t gw = std::min<uint64_t>(W, P / NSGC_GRID_MIN);
   return plan_offsets(size_t(W), size_t(W), size_t(nb_all), size_t(nc), size_t(nb_all),
-                      size_t(nb_all)).total + 1024;
+                      size_t(nb_all), 0, size_t(gw), size_t(grid_cells_bound(P, gw, t)),
+                      size_t(grid_citems_bound(P, gw, t))).total + 1024;
+}
+
+size_t grid_workspace_bound(int64_t max_packets, int64_t max_windows, const nsgc_tune& t) {
+  const uint64_t P = uint64_t(std::max<int64_t>(max_packets, 0));
+  const uint64_t gw = std::min<uint64_t>(uint64_t(std::max<int64_t>(max_windows, 1)), P / NSGC_GRID_MIN);
+  if (gw == 0) return 0;
+  const uint64_t cells = grid_cells_bound(P, gw, t);
+  // tile records: windows of up to 1024 cells in tiles of 2^13 packets (or the
+  // tuning's, if smaller; smaller still only below 2 * kGridTiles tiles in all),
+  // batches with larger ones in tiles of 2^14
+  const uint64_t c13 = std::min<uint64_t>(cells, NSGC_GRID_TILE13_CELLS);
+  const uint64_t c14 = std::min<uint64_t>(cells, uint64_t(1) << NSGC_GRID_MAX_CELLS_LOG2);
+  const uint64_t tile_words =
+      std::max((P >> std::min(t.tile_log2, 13)) * c13, (P >> 14) * c14) + (2 * kGridTiles + gw) * c14;
+  const uint64_t citems = grid_citems_bound(P, gw, t);
+  // a cell record has at most 2 NSGC_GRID_MAX_SUB + 3 words, and per window
+  // cells * (R / strips + C / strips + 3) <= cells * 3 + (R + C) * max strips
+  const uint64_t rec = std::min<uint64_t>(cells * (2 * NSGC_GRID_MAX_SUB + 3),
+                                          cells * 3 + (citems << NSGC_GRID_MAX_B));
+  return size_t((tile_words + rec + gw * NSGC_GRID_HV_WORDS(NSGC_GRID_HEAVY)) * 4 +
+                cells * (2 * NSGC_GRID_HEAVY * 8 + 24) + citems * 24 + 9 * 256);
 }
 
 void HostPlan::serialize(void* buf, uint64_t dev_plan, uint64_t dev_ws, const uint32_t* src,
                          const uint32_t* dst, void* out) const {
   const PlanOffsets o = plan_offsets(small.size(), win.size(), itemwinB.size(), itemwinC.size(),
-                                     mapBb.size(), mapBw.size(), ent_cur.size());
+                                     mapBb.size(), mapBw.size(), ent_cur.size(), gwin.size(),
+                                     gitemB.size(), gitemC.size());
   const WsLayout L = layout();
   char* base = static_cast<char*>(buf);
   std::memset(base, 0, align_up(sizeof(nsgc_dev_plan), 64));
@@ -312,6 +512,21 @@ void HostPlan::serialize(void* buf, uint64_t dev_plan, uint64_t dev_ws, const ui
   h.itemwinC = reinterpret_cast<const uint32_t*>(dev_plan + o.itemwinC);
   h.mapBb = mapBb.empty() ? nullptr : reinterpret_cast<const uint32_t*>(dev_plan + o.mapBb);
   h.mapBw = mapBw.empty() ? nullptr : reinterpret_cast<const uint32_t*>(dev_plan + o.mapBw);
+  if (!gwin.empty()) {
+    h.gwin = reinterpret_cast<const nsgc_grid_desc*>(dev_plan + o.gwin);
+    h.gprefA = reinterpret_cast<const uint32_t*>(dev_plan + o.gprefA);
+    h.gitemB = reinterpret_cast<const uint32_t*>(dev_plan + o.gitemB);
+    h.gitemC = reinterpret_cast<const uint32_t*>(dev_plan + o.gitemC);
+    h.goverB = reinterpret_cast<uint32_t*>(dev_ws + L.goverB);
+    h.goverW = reinterpret_cast<uint32_t*>(dev_ws + L.goverW);
+    h.goverC = reinterpret_cast<uint32_t*>(dev_ws + L.goverC);
+  }
+  h.num_grid = uint32_t(gwin.size());
+  h.gitemsA = gitemsA;
+  h.gitemsS = gitemsS;
+  h.gitemsB = gitemsB;
+  h.gitemsC = gitemsC;
+  h.gtile_log2 = gtile_log2;
   h.itemsBb = itemsBb;
   h.itemsBw = itemsBw;
   h.num_small = uint32_t(small.size());
@@ -348,6 +563,29 @@ void HostPlan::serialize(void* buf, uint64_t dev_plan, uint64_t dev_ws, const ui
   if (!itemwinC.empty()) std::memcpy(base + o.itemwinC, itemwinC.data(), itemwinC.size() * 4);
   if (!mapBb.empty()) std::memcpy(base + o.mapBb, mapBb.data(), mapBb.size() * 4);
   if (!mapBw.empty()) std::memcpy(base + o.mapBw, mapBw.data(), mapBw.size() * 4);
+  if (!gwin.empty()) {
+    nsgc_grid_desc* gd = reinterpret_cast<nsgc_grid_desc*>(base + o.gwin);
+    for (size_t i = 0; i < gwin.size(); ++i) {
+      nsgc_grid_desc g = gwin[i];
+      g.dst = g.src;
+      g.emit_row = g.emit_col = g.keys;
+      rebase(g.src, reinterpret_cast<uint64_t>(src));
+      rebase(g.dst, reinterpret_cast<uint64_t>(dst));
+      rebase(g.keys, dev_ws + L.keys);
+      rebase(g.emit_row, dev_ws + L.emit_row);
+      rebase(g.emit_col, dev_ws + L.emit_col);
+      rebase(g.tile, dev_ws + L.gtile);
+      rebase(g.rec, dev_ws + L.grec);
+      rebase(g.heavy, dev_ws + L.gheavy);
+      rebase(g.acc, dev_ws + L.gacc);
+      rebase(g.partB, dev_ws + L.gpartB);
+      rebase(g.partC, dev_ws + L.gpartC);
+      std::memcpy(gd + i, &g, sizeof g);
+    }
+    std::memcpy(base + o.gprefA, gprefA.data(), gprefA.size() * 4);
+    std::memcpy(base + o.gitemB, gitemB.data(), gitemB.size() * 4);
+    std::memcpy(base + o.gitemC, gitemC.data(), gitemC.size() * 4);
+  }
   if (!ent_cur.empty()) std::memcpy(base + o.entcur, ent_cur.data(), ent_cur.size() * 8);
   if (!ent_end.empty()) std::memcpy(base + o.entend, ent_end.data(), ent_end.size() * 8);
 }

@@ -16,7 +16,9 @@ namespace nsgc {
 // Workspace regions of one batch, as byte offsets from the workspace base.
 struct WsLayout {
   size_t keys = 0, emit_row = 0, emit_col = 0, tilemeta = 0, lbmeta = 0, rcsize = 0, order = 0,
-         partB = 0, partC = 0, partU = 0, stats = 0, large = 0, partR = 0, heavy = 0;
+         partB = 0, partC = 0, partU = 0, stats = 0, large = 0, partR = 0, heavy = 0, gtile = 0,
+         grec = 0, gheavy = 0, gacc = 0, gpartB = 0, gpartC = 0,
+         goverB = 0, goverW = 0, goverC = 0;
   size_t total = 0;
 };
 
@@ -27,6 +29,12 @@ struct LargeWindow {
   uint32_t out_index;
 };
 
+// Bucket counts (log2) and tiles of a partitioned window under the tuning.
+struct PartShape {
+  uint8_t logB, logR, logC;
+  int64_t tiles;
+};
+
 struct HostPlan {
   std::vector<nsgc_small_desc> small;
   std::vector<LargeWindow> large;
@@ -35,6 +43,12 @@ struct HostPlan {
   std::vector<uint32_t> prefA, prefB, prefC;
   std::vector<uint32_t> itemwinB, itemwinC;   // window of each phase-B / phase-C item
   std::vector<uint32_t> mapBb, mapBw;         // phase-B items by kernel (empty: identity)
+  std::vector<PartShape> shape;               // per partitioned window (tier 2), in window order
+  std::vector<nsgc_grid_desc> gwin;           // grid windows: small cells, then big cells
+  std::vector<uint32_t> gprefA, gitemB, gitemC;
+  uint32_t gitemsA = 0, gitemsS = 0, gitemsB = 0, gitemsC = 0, gtile_log2 = 14;
+  uint32_t gbuckets = 0;       // row and column buckets of the grid windows
+  int64_t gtile_words = 0, grec_words = 0;
   uint32_t itemsBb = 0, itemsBw = 0;
   uint32_t wave_rc_max = 0;    // largest row or column bucket count of a wavefront window
   uint32_t num_rows = 0;       // row-complete windows (tune row_complete)
@@ -69,10 +83,14 @@ int validate_offsets(const int64_t* offsets, int64_t num_windows);
 
 // Builds the plan.  Returns NSGC_OK or NSGC_ERR_* (offsets must be valid).
 int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune,
-              HostPlan* plan, bool entity = false, bool allow_large = true);
+              HostPlan* plan, bool entity = false, bool allow_large = true,
+              bool allow_grid = true);
 
 void default_tune(nsgc_tune* t);
 int check_tune(const nsgc_tune& t);
+
+// Most cells of a grid window in a batch partitioned in tiles of 2^tile_log2.
+uint32_t grid_max_cells(uint32_t tile_log2);
 
 // Smallest k with 2^k >= x (x >= 1).
 int ceil_log2(uint64_t x);
@@ -80,6 +98,10 @@ int ceil_log2(uint64_t x);
 // Upper bound of plan_bytes() for any batch of <= max_packets packets in <=
 // max_windows windows planned with `t`.
 size_t plan_bound(int64_t max_packets, int64_t max_windows, const nsgc_tune& t);
+
+// Upper bound of the workspace that grid windows take beyond 24 bytes per
+// packet, for the same batches.
+size_t grid_workspace_bound(int64_t max_packets, int64_t max_windows, const nsgc_tune& t);
 
 
 }  // namespace nsgc
