@@ -41,9 +41,10 @@
  *     call returns after enqueueing; results are valid once the stream has
  *     reached that point.  Input buffers must stay alive and unmodified until
  *     then.  One exception: a batch with a window of the large-window tier
- *     (nsgc_tune.large_min_log2) waits once per such window for the stream,
- *     to read back the window's link count, so the call returns only after
- *     the work enqueued before that point has run.
+ *     (nsgc_tune.large_min_log2) waits for the stream once per such window,
+ *     to read back whether the window's hash partitioning came out even
+ *     enough (and once more if it has to be sorted), so the call returns only
+ *     after the work enqueued before that point has run.
  *   - Argument errors are reported synchronously with nothing enqueued and
  *     out_stats untouched.  A HIP runtime failure returns NSGC_ERR_HIP and
  *     nsgc_last_hip_error() gives the hipError_t.
@@ -225,9 +226,11 @@ typedef struct nsgc_tune {
                                large share of the links), with this probe
                                limit before falling back to per-link entries */
   nsgc_tune_class cls[33];
-  int32_t large_min_log2;   /* windows of at least 2^k packets are computed by
-                               sorting instead of hash partitioning, one window
-                               at a time, with one wait for the stream each
+  int32_t large_min_log2;   /* windows of at least 2^k packets are computed one
+                               at a time, by hash partitioning in two levels
+                               (above 2^30 packets, or if that comes out too
+                               uneven, by sorting), with a wait for the stream
+                               each
                                (20..33; 33 turns the tier off; the graph form
                                and the entity outputs never use it) */
   int32_t row_complete;     /* 0 (default): link buckets by the hash of the whole

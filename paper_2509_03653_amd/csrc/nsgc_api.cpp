@@ -18,6 +18,7 @@
 #include "nsgc_anon.hpp"
 #include "nsgc_grid.hpp"
 #include "nsgc_large.hpp"
+#include "nsgc_large_grid.hpp"
 #include "nsgc_planner.hpp"
 
 namespace nsgc {
@@ -146,6 +147,7 @@ int get_ctx(DevCtx** out) {
     c->lds_limit = std::max(c->lds_limit, size_t(per_cu));
   NSGC_HIP(allow_large_lds(c->lds_limit));
   NSGC_HIP(grid_allow_large_lds(c->lds_limit));
+  NSGC_HIP(large_grid_allow_lds(c->lds_limit));
   g_devs[dev] = c;
   *out = c;
   return NSGC_OK;
@@ -389,9 +391,25 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
   if (!hp.large.empty()) {
     if (!la) return NSGC_ERR_INTERNAL;
     char* region = la->ws + hp.layout().large;
-    for (const LargeWindow& lw : hp.large)
-      NSGC_HIP(large_window_stats(la->src + lw.in_begin, la->dst + lw.in_begin, lw.n, region,
-                                  la->out + (unsigned long long)lw.out_index * 9, la->grid, s));
+    const LargeGridLaunch lg = {la->grid / 8, L.glinks[1], L.gwide, L.gover, L.grc, L.lds_grc,
+                                hp.rc_slots_log2};
+    for (const LargeWindow& lw : hp.large) {
+      const uint32_t* src = la->src + lw.in_begin;
+      const uint32_t* dst = la->dst + lw.in_begin;
+      unsigned long long* out = la->out + (unsigned long long)lw.out_index * 9;
+      // By grid, and by sorting if that is out of range or gave up on the
+      // window (one wait for the stream tells).
+      const size_t need = large_grid_bytes(lw.n);
+      bool sorted = need == 0 || need > large_window_bytes(lw.n);
+      if (!sorted) {
+        NSGC_HIP(large_grid_stats(src, dst, lw.n, region, out, lg, s));
+        unsigned long long packets = 0;
+        NSGC_HIP(hipMemcpyAsync(&packets, out, sizeof packets, hipMemcpyDeviceToHost, s));
+        NSGC_HIP(hipStreamSynchronize(s));
+        sorted = packets != lw.n;
+      }
+      if (sorted) NSGC_HIP(large_window_stats(src, dst, lw.n, region, out, la->grid, s));
+    }
   }
   NSGC_HIP(mark(5));
   return NSGC_OK;

@@ -18,7 +18,7 @@
 //
 // Measured against that path, whole calls: 64 windows of 2^17 packets 237 ->
 // 208 us; one of 40013 packets 58 -> 45 us; nine of 2^12 .. 2^22 packets 434 ->
-// 184 us; 512 of 2^10 .. 2^23 packets 11.5 -> 7.1 ms; 128 of 2^23 14.2 -> 10.1
+// 184 us; 512 of 2^10 .. 2^23 packets 11.5 -> 7.2 ms; 128 of 2^23 14.2 -> 9.6
 // ms.  From 2^13 packets on no traffic mix was slower on the grid (two windows
 // of 10^4 packets 60 -> 53 us), and one link bucket holds smaller windows.
 #include <hip/hip_runtime.h>
@@ -27,6 +27,7 @@
 
 #include "nsgc_device.hpp"
 #include "nsgc_grid.hpp"
+#include "nsgc_grid_device.hpp"
 #include "nsgc_phases.hpp"
 #include "nsgc_plan.h"
 
@@ -35,20 +36,6 @@ namespace nsgc {
 namespace {
 
 constexpr uint32_t HVM = NSGC_GRID_HEAVY;   // most dominant addresses per view
-
-// The partition looks dominant ids up in a direct-mapped table of 512 entries
-// per view, indexed by bits 2 .. 10 of the hashed id; no two dominant ids of a
-// view share an entry.
-constexpr uint32_t HT = 512;
-__device__ __forceinline__ uint32_t heavy_index(uint32_t id) { return (id >> 2) & (HT - 1); }
-
-// The distance 1 .. 2^k - 1 (k >= 1) by which a link of a dominant address is
-// moved off its home strip, from the other address' hashed id.  It takes bits
-// 3 .. 18, which decide neither that address' strip and bucket (top bits) nor,
-// with one address fixed, the link's table slot.
-__device__ __forceinline__ uint32_t strip_shift(uint32_t other, uint32_t k) {
-  return 1u + ((((other >> 3) & 0xFFFFu) * ((1u << k) - 1u)) >> 16);
-}
 
 // Find-or-insert of U keys per lane in an open-addressing LDS table (linear
 // probing): the home slots of all U are tried together, then the keys still
@@ -157,9 +144,6 @@ __device__ __forceinline__ void arrived(T& x) {
 }
 __device__ __forceinline__ void loads_arrived() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
-// Four consecutive packets at any 4-byte aligned address.
-typedef uint32_t v4u32_any __attribute__((ext_vector_type(4), aligned(4)));
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -169,15 +153,19 @@ typedef uint32_t v4u32_any __attribute__((ext_vector_type(4), aligned(4)));
 // spread from the window's first packet to its last.  An address is a
 // candidate when the sample puts more than an eighth of a strip's share of the
 // packets on it, or half a bucket's (and at least 8 hits); of two candidates
-// that share a table entry the more frequent one stays, and of those the most
-// frequent NSGC_GRID_HEAVY.  The matrix starts at zero.  One trip to memory and
-// seven barriers: bound by latency, 4.5 us for one window and 7.6 us for 64.
+// that share an entry of the lookup table the more frequent one stays, and of
+// those the most frequent NSGC_GRID_HEAVY.  The lookup's shift is the one of
+// eight that leaves out the fewest hits: with a fixed one about four of 64
+// addresses were left out, now and then a very frequent one, whose strip then
+// overfilled (128 skewed windows of 2^23 packets 10.1 -> 9.6 ms).  The matrix
+// starts at zero.  One trip to memory and a dozen barriers: bound by latency,
+// 4.5 us for one window and 8.2 us for 64.
 // ---------------------------------------------------------------------------
 
 constexpr uint32_t GH_NT = 1024;
 constexpr uint32_t GH_VT = GH_NT / 2;                       // threads per view
 constexpr uint32_t GH_MIN = 8;                              // hits of a candidate
-static_assert(HT == GH_VT, "one thread per table entry");
+static_assert(HT == GH_VT, "one thread per table entry and per candidate");
 
 template <uint32_t HV>
 __global__ __launch_bounds__(GH_NT) void k_grid_heavy(const nsgc_dev_plan* __restrict__ P) {
@@ -186,15 +174,15 @@ __global__ __launch_bounds__(GH_NT) void k_grid_heavy(const nsgc_dev_plan* __res
   constexpr uint32_t GH_TABLE = 2 * SAMPLE;
   constexpr uint32_t GH_CAND = SAMPLE / GH_MIN;    // at most so many candidates per view
   constexpr uint32_t RUN = SAMPLE / 64;
-  __shared__ __align__(16) uint32_t key[2][GH_TABLE];
-  __shared__ __align__(16) uint32_t cnt[2][GH_TABLE];
-  __shared__ __align__(16) u64 best[2][HT];   // hits << 32 | id of the candidate that holds an entry
-  __shared__ u64 cand[2][GH_CAND];
+  static_assert(GH_CAND <= GH_VT && HEAVY_SHIFTS * HT * 8 <= 2 * GH_TABLE * 4, "entries lie in the table");
+  __shared__ __align__(16) uint32_t table[2][2][GH_TABLE];   // ids and counts of each view
+  __shared__ u64 cand[2][GH_CAND];            // hits << 32 | id
+  __shared__ uint32_t lost[2][HEAVY_SHIFTS];   // hits of the candidates without an entry
   __shared__ uint32_t ncand[2];
   const uint32_t v = threadIdx.x >= GH_VT ? 1u : 0u;   // view: sources, destinations
   const uint32_t tid = threadIdx.x & (GH_VT - 1);
-  uint32_t* const k = key[v];
-  uint32_t* const c = cnt[v];
+  uint32_t* const k = table[v][0];
+  uint32_t* const c = table[v][1];
   for (uint32_t wi = blockIdx.x; wi < P->num_grid; wi += gridDim.x) {
     const nsgc_grid_desc W = sload_words(P->gwin + wi);
     const NSGC_GLOBAL uint32_t* col = gptr(v ? W.dst : W.src);
@@ -210,8 +198,8 @@ __global__ __launch_bounds__(GH_NT) void k_grid_heavy(const nsgc_dev_plan* __res
       reinterpret_cast<v4u32*>(k)[i * GH_VT + tid] = e4;
       reinterpret_cast<v4u32*>(c)[i * GH_VT + tid] = z4;
     }
-    best[v][tid] = 0;
     if (tid == 0) ncand[v] = 0;
+    if (tid < HEAVY_SHIFTS) lost[v][tid] = 0;
     NSGC_GLOBAL uint32_t* out = gptr(W.heavy);
     for (uint32_t i = threadIdx.x; i < HV * HV; i += GH_NT) out[2 * HV + i] = 0;
     if (threadIdx.x < 2 * HV) out[threadIdx.x] = EMPTY32;   // unused (this id is never dominant)
@@ -234,15 +222,36 @@ __global__ __launch_bounds__(GH_NT) void k_grid_heavy(const nsgc_dev_plan* __res
 #pragma unroll
     for (uint32_t i = 0; i < GH_TABLE / GH_VT; ++i) {
       const uint32_t h = c[i * GH_VT + tid];
-      if (h >= thr) {
-        const uint32_t id = k[i * GH_VT + tid];
-        __hip_atomic_fetch_max(&best[v][heavy_index(id)], (u64(h) << 32) | id, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
+      if (h >= thr) cand[v][lds_add(&ncand[v], 1)] = (u64(h) << 32) | k[i * GH_VT + tid];
     }
+    lds_barrier();
+    // the candidate that holds each entry under each shift, where the table was
+    u64* const best = reinterpret_cast<u64*>(k);
+#pragma unroll
+    for (uint32_t i = 0; i < HEAVY_SHIFTS; ++i) best[i * HT + tid] = 0;
+    lds_barrier();
+    u64 mine = tid < ncand[v] ? cand[v][tid] : 0ull;
+    if (mine) {
+#pragma unroll
+      for (uint32_t i = 0; i < HEAVY_SHIFTS; ++i)
+        __hip_atomic_fetch_max(&best[i * HT + heavy_index(uint32_t(mine), i)], mine, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    lds_barrier();
+    if (mine) {
+#pragma unroll
+      for (uint32_t i = 0; i < HEAVY_SHIFTS; ++i)
+        if (best[i * HT + heavy_index(uint32_t(mine), i)] != mine) lds_add(&lost[v][i], uint32_t(mine >> 32));
+    }
+    lds_barrier();
+    uint32_t shift = 0;
+#pragma unroll
+    for (uint32_t i = 1; i < HEAVY_SHIFTS; ++i)
+      if (lost[v][i] < lost[v][shift]) shift = i;
+    if (tid == 0) out[2 * HV + HV * HV + v] = shift;
+    if (mine && best[shift * HT + heavy_index(uint32_t(mine), shift)] != mine) mine = 0;
     __syncthreads();   // (the unused marks in memory land before the ids below)
-    const u64 mine = best[v][tid];
-    if (mine) cand[v][lds_add(&ncand[v], 1)] = mine;
+    if (tid < GH_CAND && !mine) cand[v][tid] = 0;
     lds_barrier();
     if (mine) {
       uint32_t rank = 0;
@@ -275,7 +284,8 @@ size_t lds_grid_part_bytes(uint32_t tile_log2, uint32_t max_cells) {
   return grid_part_lds(tile_log2, max_cells);
 }
 
-template <int PER, int NT, uint32_t HV>
+// KEYS: the window's packets are link keys already (W.src points to them).
+template <int PER, int NT, uint32_t HV, bool KEYS = false>
 __global__ __launch_bounds__(NT) void k_grid_partition(const nsgc_dev_plan* __restrict__ P,
                                                        uint32_t max_cells) {
   static_assert(PER % 4 == 0, "PER must be a multiple of 4");
@@ -299,13 +309,16 @@ __global__ __launch_bounds__(NT) void k_grid_partition(const nsgc_dev_plan* __re
 
   // The window's dominant ids into the lookup table (a free entry holds an id
   // that belongs to another entry).  Needs a barrier before and after.
+  uint32_t sh = 0, dh = 0;   // lookup shifts
   auto load_heavy = [&]() {
-    for (uint32_t i = tid; i < 2 * HT; i += NT) idt[i] = ((i & (HT - 1)) ^ 1u) << 2;
+    sh = uniform(gptr(W.heavy)[2 * HV + HV * HV]);
+    dh = uniform(gptr(W.heavy)[2 * HV + HV * HV + 1]);
+    for (uint32_t i = tid; i < 2 * HT; i += NT) idt[i] = free_entry(i, i < HT ? sh : dh);
     lds_barrier();
     if (tid < 2 * HV) {
       const uint32_t id = gptr(W.heavy)[tid];
       if (id != EMPTY32) {
-        const uint32_t at = (tid / HV) * HT + heavy_index(id);
+        const uint32_t at = (tid / HV) * HT + heavy_index(id, tid < HV ? sh : dh);
         idt[at] = id;
         ids[at] = uint8_t(tid & (HV - 1));
       }
@@ -320,6 +333,16 @@ __global__ __launch_bounds__(NT) void k_grid_partition(const nsgc_dev_plan* __re
   };
   uint32_t r[PER], c[PER];
   auto load = [&](uint32_t tbeg, uint32_t len) {
+    if constexpr (KEYS) {
+      const NSGC_GLOBAL u64* in = (const NSGC_GLOBAL u64*)gptr(W.src) + tbeg;
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const u64 x = in[min(uint32_t((k >> 2) * NT + tid) * 4 + (k & 3), len - 1)];
+        r[k] = uint32_t(x >> 32);
+        c[k] = uint32_t(x);
+      }
+      return;
+    }
     const NSGC_GLOBAL uint32_t* src = gptr(W.src) + tbeg;
     const NSGC_GLOBAL uint32_t* dst = gptr(W.dst) + tbeg;
     if (len == T) {
@@ -346,31 +369,33 @@ __global__ __launch_bounds__(NT) void k_grid_partition(const nsgc_dev_plan* __re
   for (uint32_t i = tid; i < HV * HV; i += NT) mat[i] = 0;
   load_heavy();
   for (uint32_t item = beg;; ++item) {
-    const uint32_t a = W.logA, b = W.logBc, cells = 1u << (a + b);
+    const uint32_t a = W.logA, b = W.logBc, cells = 1u << (W.subA + W.subB);
     for (uint32_t i = tid; i < cells; i += NT) hist[i] = 0;
     lds_barrier();
     uint32_t br[PER];   // rank in cell << 12 | cell; all ones: no key
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      r[k] = row_hash(r[k]);
-      c[k] = col_hash(c[k]);
-      const bool hs = idt[heavy_index(r[k])] == r[k], hd = idt[HT + heavy_index(c[k])] == c[k];
+      if constexpr (!KEYS) {
+        r[k] = row_hash(r[k]);
+        c[k] = col_hash(c[k]);
+      }
+      const bool hs = idt[heavy_index(r[k], sh)] == r[k], hd = idt[HT + heavy_index(c[k], dh)] == c[k];
       const bool ok = len == T || uint32_t((k >> 2) * NT + tid) * 4 + (k & 3) < len;
       br[k] = ~0u;
       uint32_t i = r[k] >> (32 - a), j = c[k] >> (32 - b);
       if (hs && hd) {
-        if (ok) lds_add(&mat[uint32_t(ids[heavy_index(r[k])]) * HV + ids[HT + heavy_index(c[k])]], 1);
+        if (ok) lds_add(&mat[uint32_t(ids[heavy_index(r[k], sh)]) * HV + ids[HT + heavy_index(c[k], dh)]], 1);
       } else {
         // a key names a dominant address by its slot, off the cell's strip
         if (hs) {
           i ^= strip_shift(c[k], a);
-          r[k] = ((i ^ 1u) << (32 - a)) | ids[heavy_index(r[k])];
+          r[k] = ((i ^ 1u) << (32 - a)) | ids[heavy_index(r[k], sh)];
         }
         if (hd) {
           j ^= strip_shift(r[k], b);
-          c[k] = ((j ^ 1u) << (32 - b)) | ids[HT + heavy_index(c[k])];
+          c[k] = ((j ^ 1u) << (32 - b)) | ids[HT + heavy_index(c[k], dh)];
         }
-        const uint32_t cell = (i << b) | j;
+        const uint32_t cell = ((i & ((1u << W.subA) - 1u)) << W.subB) | (j & ((1u << W.subB) - 1u));
         if (ok) br[k] = (lds_add(&hist[cell], 1) << 12) | cell;
       }
     }
@@ -571,8 +596,8 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
   const uint32_t T = 1u << sload(&P->gtile_log2);
   const nsgc_grid_desc W = sload_words(sload(&P->gwin) + sload(sload(&P->gitemB) + it));
   const uint32_t cell = it - W.itemB;
-  const uint32_t a = W.logA, b = W.logBc, cells = 1u << (a + b);
-  const uint32_t ci = cell >> b, cj = cell & ((1u << b) - 1u);
+  const uint32_t a = W.logA, b = W.logBc, cells = 1u << (W.subA + W.subB);
+  const uint32_t ci = W.strip_i + (cell >> W.subB), cj = W.strip_j + (cell & ((1u << W.subB) - 1u));
   const uint32_t rsub = 1u << (W.logR - a), csub = 1u << (W.logC - b);
   const uint32_t nt = W.ntiles;
   NSGC_GLOBAL u64* keys = gptr(W.keys);
@@ -598,8 +623,8 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
   }
   below = uniform(below);
   total = uniform(total);
-  NSGC_GLOBAL u64* er = gptr(W.emit_row) + below;
-  NSGC_GLOBAL u64* ec = gptr(W.emit_col) + below;
+  NSGC_GLOBAL u64* er = gptr(W.emit_row) + W.base + below;
+  NSGC_GLOBAL u64* ec = gptr(W.emit_col) + W.base + below;
   auto row_bin = [&](uint32_t r) { return (r >> (32 - W.logR)) & (rsub - 1u); };
   auto col_bin = [&](uint32_t c) { return (c >> (32 - W.logC)) & (csub - 1u); };
   auto row_light = [&](uint32_t r) { return (r >> (32 - a)) == ci; };
@@ -609,7 +634,7 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
     lds_add64(&acc[v * HV + (id & (HV - 1))], (u64(1) << 32) | n);
   };
   auto clear_table = [&]() { clear_cell_table<NT, SL, SL>(tid, tk, tc, bin, misc); };
-  auto starts = [&](uint32_t& xr, uint32_t& xc) { publish_starts(rec, bin, rsub, csub, below, xr, xc); };
+  auto starts = [&](uint32_t& xr, uint32_t& xc) { publish_starts(rec, bin, rsub, csub, W.base + below, xr, xc); };
 
   // Rounds: each fills the table with as many links as it takes, counts
   // all their packets and emits them.  If a key found no place, the keys
@@ -618,7 +643,8 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
   // gets one slot per packet of the bin, the most entries it can receive;
   // slots left over hold empty entries (no packets), which phase C skips.
   uint32_t links = 0, mx = 0;
-  bool abandoned = false;
+  const uint32_t most = sload(&P->gmax_keys);
+  bool abandoned = most && total > most;
   uint32_t special = 0;
   const uint32_t max_rounds = 1u << min(sload(&P->max_sweeps_log2), 24u);
   auto seg = [&](uint32_t t, u64& base, uint32_t& len) {
@@ -626,7 +652,7 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
     base = u64(t) * T + (x & 0xFFFFu);
     len = x >> 16;
   };
-  for (uint32_t round = 0;; ++round) {
+  for (uint32_t round = 0; !abandoned; ++round) {
     if (round >= max_rounds) { abandoned = true; break; }
     __syncthreads();
     const uint32_t keep = round && tid < 2 * NSGC_GRID_MAX_SUB ? bin[tid] : 0u;
@@ -813,7 +839,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
   // for the next item while the current one is worked on.
   auto record = [&](const nsgc_grid_desc& W, uint32_t it, uint32_t t) -> uint32_t {
     if (W.ntiles <= 64) t &= 63u;
-    const uint32_t cells = 1u << (W.logA + W.logBc);
+    const uint32_t cells = 1u << (W.subA + W.subB);
     return t < W.ntiles ? gptr(W.tile)[u64(t) * cells + (it - W.itemB)] : 0u;
   };
   uint32_t x = 0, wnext = 0;   // the next item's record and window
@@ -826,7 +852,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
     const uint32_t it = item_at(pos0);
     if (!have) wnext = sload(sload(&P->gitemB) + it);
     const nsgc_grid_desc W = sload_words(sload(&P->gwin) + wnext);
-    const uint32_t cell = it - W.itemB;
+    const uint32_t cell = it - W.itemB, wcur = wnext;
     const uint32_t nt = W.ntiles;
 
     // the cell's segments (one per tile) and its packets; `below`: the
@@ -852,24 +878,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
     bool done = false;
     uint32_t links = 0, mx = 0;
     if (total <= ROOM) {
-      const uint32_t a = W.logA, b = W.logBc, cells = 1u << (a + b);
-      const uint32_t ci = cell >> b, cj = cell & ((1u << b) - 1u);
-      const uint32_t rsub = 1u << (W.logR - a), csub = 1u << (W.logC - b);
-      NSGC_GLOBAL u64* keys = gptr(W.keys);
-      NSGC_GLOBAL uint32_t* rec = gptr(W.rec) + u64(cell) * (rsub + csub + 3);
-      NSGC_GLOBAL u64* er = gptr(W.emit_row) + below;
-      NSGC_GLOBAL u64* ec = gptr(W.emit_col) + below;
-      auto row_bin = [&](uint32_t r) { return (r >> (32 - W.logR)) & (rsub - 1u); };
-      auto col_bin = [&](uint32_t c) { return (c >> (32 - W.logC)) & (csub - 1u); };
-      auto row_light = [&](uint32_t r) { return (r >> (32 - a)) == ci; };
-      auto col_light = [&](uint32_t c) { return (c >> (32 - b)) == cj; };
       auto home = [&](u64 k) { return (uint32_t(k >> 32) ^ uint32_t(k)) & uint32_t(SL - 1); };
-      // a link of the dominant source (v = 0) or destination (v = 1) that `id` names
-      auto add_heavy = [&](uint32_t v, uint32_t id, uint32_t n) {
-        lds_add64(&acc[v * HV + (id & (HV - 1))], (u64(1) << 32) | n);
-      };
+      NSGC_GLOBAL u64* keys = gptr(W.keys);
       // only the last cell can hold the key that equals the table's marker
-      const bool marker = cell == cells - 1u;
+      const bool marker = ((W.strip_i + (cell >> W.subB) + 1u) >> W.logA) != 0 &&
+                          ((W.strip_j + (cell & ((1u << W.subB) - 1u)) + 1u) >> W.logBc) != 0;
       const uint32_t kmax = uniform((total + NT - 1) / NT);
       const uint32_t* list = reinterpret_cast<const uint32_t*>(tk);
       const uint16_t* tc16 = reinterpret_cast<const uint16_t*>(tc);
@@ -931,6 +944,24 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
       lds_barrier();
       done = misc[0] == 0;
       if (done) {
+        // (the descriptor again: scalar registers are short above)
+        uint32_t wi = wcur;
+        asm volatile("" : "+s"(wi));
+        const nsgc_grid_desc G = sload_words(sload(&P->gwin) + wi);
+        const uint32_t a = G.logA, b = G.logBc;
+        const uint32_t ci = G.strip_i + (cell >> G.subB), cj = G.strip_j + (cell & ((1u << G.subB) - 1u));
+        const uint32_t rsub = 1u << (G.logR - a), csub = 1u << (G.logC - b);
+        NSGC_GLOBAL uint32_t* rec = gptr(G.rec) + u64(cell) * (rsub + csub + 3);
+        NSGC_GLOBAL u64* er = gptr(G.emit_row) + G.base + below;
+        NSGC_GLOBAL u64* ec = gptr(G.emit_col) + G.base + below;
+        auto row_bin = [&](uint32_t r) { return (r >> (32 - G.logR)) & (rsub - 1u); };
+        auto col_bin = [&](uint32_t c) { return (c >> (32 - G.logC)) & (csub - 1u); };
+        auto row_light = [&](uint32_t r) { return (r >> (32 - a)) == ci; };
+        auto col_light = [&](uint32_t c) { return (c >> (32 - b)) == cj; };
+        // a link of the dominant source (v = 0) or destination (v = 1) that `id` names
+        auto add_heavy = [&](uint32_t v, uint32_t id, uint32_t n) {
+          lds_add64(&acc[v * HV + (id & (HV - 1))], (u64(1) << 32) | n);
+        };
         const uint32_t special = marker ? misc[1] : 0u;
         uint32_t nf = 0, nr = 0, nc = 0;   // the wavefront's links, and their light entries
         uint32_t rk[E];   // ranks in the row bin | column bin << 16 (several bins)
@@ -971,7 +1002,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
         bc = uniform(bc);
         lds_barrier();
         uint32_t xr, xc;
-        publish_starts(rec, bin, rsub, csub, below, xr, xc);
+        publish_starts(rec, bin, rsub, csub, G.base + below, xr, xc);
 #pragma unroll
         for (int k = 0; k < E; ++k) {
           if (uint32_t(k) < kmax) {
@@ -1084,7 +1115,9 @@ __device__ __forceinline__ BucketItem bucket_item(const nsgc_grid_desc& W, uint3
 }
 // Word offset of the record of cell s of the item's strip.
 __device__ __forceinline__ u64 bucket_record(const nsgc_grid_desc& W, const BucketItem& B, uint32_t s) {
-  const uint32_t cell = B.row ? (B.strip << W.logBc) + s : (s << W.logBc) + B.strip;
+  const uint32_t i = B.row ? B.strip : s, j = B.row ? s : B.strip;
+  const uint32_t sub = ((i & ((1u << W.subA) - 1u)) << W.subB) | (j & ((1u << W.subB) - 1u));
+  const uint32_t cell = ((((i >> W.subA) << (W.logBc - W.subB)) | (j >> W.subB)) << (W.subA + W.subB)) | sub;
   return u64(cell) * ((1u << (W.logR - W.logA)) + (1u << (W.logC - W.logBc)) + 3u);
 }
 
@@ -1267,7 +1300,7 @@ __global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void
       } else {        // dominant sources (destinations): the cells' counters and the matrix
         u64* sum = tv;
         const uint32_t s = B.sub + (tid & 15u), g = tid >> 4;
-        const uint32_t cells = 1u << (W.logA + W.logBc);
+        const uint32_t cells = 1u << W.logP;
         const NSGC_GLOBAL u64* acc = gptr(W.acc) + k * HV + s;
         u64 x = 0;
 #pragma unroll 16
@@ -1416,13 +1449,15 @@ __global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void
 
 namespace {
 typedef void (*part_fn)(const nsgc_dev_plan*, uint32_t);
-part_fn partition_kernel(uint32_t tile_log2, int* threads) {
+part_fn partition_kernel(uint32_t tile_log2, int* threads, bool keys = false) {
   *threads = tile_log2 >= 14 ? 1024 : 512;
   switch (tile_log2) {
     case 11: return &k_grid_partition<4, 512, NSGC_GRID_HV(11)>;
     case 12: return &k_grid_partition<8, 512, NSGC_GRID_HV(12)>;
     case 13: return &k_grid_partition<16, 512, NSGC_GRID_HV(13)>;
-    case 14: return &k_grid_partition<16, 1024, NSGC_GRID_HV(14)>;
+    case 14:
+      return keys ? &k_grid_partition<16, 1024, NSGC_GRID_HV(14), true>
+                  : &k_grid_partition<16, 1024, NSGC_GRID_HV(14)>;
     default: return nullptr;
   }
 }
@@ -1443,9 +1478,9 @@ hipError_t launch_grid_heavy(const nsgc_dev_plan* P, uint32_t tile_log2, uint32_
 }
 
 hipError_t launch_grid_partition(const nsgc_dev_plan* P, uint32_t tile_log2, uint32_t max_cells,
-                                 uint32_t grid, hipStream_t s) {
+                                 uint32_t grid, hipStream_t s, bool keys) {
   int threads = 0;
-  const part_fn f = partition_kernel(tile_log2, &threads);
+  const part_fn f = partition_kernel(tile_log2, &threads, keys);
   if (!f) return hipErrorInvalidValue;
   hipLaunchKernelGGL(f, dim3(grid), dim3(threads), lds_grid_part_bytes(tile_log2, max_cells), s, P,
                      max_cells);
@@ -1493,6 +1528,7 @@ hipError_t grid_allow_large_lds(size_t bytes) {
                        reinterpret_cast<const void*>(partition_kernel(12, &t)),
                        reinterpret_cast<const void*>(partition_kernel(13, &t)),
                        reinterpret_cast<const void*>(partition_kernel(14, &t)),
+                       reinterpret_cast<const void*>(partition_kernel(14, &t, true)),
                        reinterpret_cast<const void*>(&k_grid_rowcol),
                        reinterpret_cast<const void*>(&k_grid_sweeps)};
   for (const void* f : fns) {

@@ -2123,7 +2123,7 @@ __global__ __launch_bounds__(256) void k_finish(nsgc_dev_plan* P) {
     const uint32_t *partB = P->partB, *partC = P->partC;
     if (gridw) {
       const nsgc_grid_desc G = gload(P->gwin + (w - np));
-      B = 1u << (G.logA + G.logBc); R = 1u << G.logRi; C = 1u << G.logCi;
+      B = 1u << G.logP; R = 1u << G.logRi; C = 1u << G.logCi;
       partB = G.partB;
       gh = NSGC_GRID_CITEMS(NSGC_GRID_HV(P->gtile_log2));
       partC = G.partC + 4 * gh;   // (the dominant addresses' items come first)
@@ -2286,6 +2286,8 @@ hipError_t launch_finish(const nsgc_dev_plan* P, uint32_t grid, hipStream_t s) {
   hipLaunchKernelGGL(k_finish, dim3(grid), dim3(256), 0, s, const_cast<nsgc_dev_plan*>(P));
   return hipGetLastError();
 }
+
+hipError_t launch_grid_finish(const nsgc_dev_plan* P, hipStream_t s) { return launch_finish(P, 1, s); }
 
 hipError_t launch_order(const nsgc_dev_plan* P, hipStream_t s) {
   hipLaunchKernelGGL(k_order, dim3(1), dim3(NSGC_BLOCK), 0, s, const_cast<nsgc_dev_plan*>(P));

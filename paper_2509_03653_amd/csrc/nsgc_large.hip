@@ -1,9 +1,8 @@
 // Large-window tier: the nine statistics of one very large window by sorting
-// instead of LDS hashing (Table III rows 1-9 and their src/dst reverse).
-//
-// A window of hundreds of millions of packets would need many levels of hash
-// partitioning before its buckets fit LDS tables; sorting reaches the same
-// groups directly:
+// instead of LDS hashing (Table III rows 1-9 and their src/dst reverse), for
+// windows of more than 2^30 packets and those whose hash partitioning
+// (nsgc_large_grid.hip) gave up: whatever the addresses, sorting takes the
+// same few passes:
 //   1. each packet becomes its hashed link key row_hash(src) << 32 |
 //      col_hash(dst) (a bijection of the pair), and the keys are radix-sorted;
 //   2. equal keys are now adjacent: a link is a run of equal keys (its length

@@ -1,5 +1,4 @@
-// Large-window tier (nsgc_large.hip): the statistics of one window by
-// sorting, for windows too large for one level of LDS hash partitioning.
+// Large-window tier (nsgc_large.hip): the statistics of one window by sorting.
 #ifndef NSGC_LARGE_HPP_
 #define NSGC_LARGE_HPP_
 

@@ -114,8 +114,9 @@
 // Phase-C items of a window's dominant addresses: 16 of one view each, and one
 // for the links between them.
 #define NSGC_GRID_CITEMS(hv) ((hv) / 8 + 1)
-// Words of a window's dominant-address block: the ids of both views, the matrix.
-#define NSGC_GRID_HV_WORDS(hv) (2 * (hv) + (hv) * (hv))
+// Words of a window's dominant-address block: the ids of both views, the matrix,
+// the lookup shift of each view.
+#define NSGC_GRID_HV_WORDS(hv) (2 * (hv) + (hv) * (hv) + 2)
 
 struct nsgc_grid_desc {         // 128 bytes
   const uint32_t* src;          // the window's packets
@@ -134,9 +135,13 @@ struct nsgc_grid_desc {         // 128 bytes
   uint32_t out_index;           // window index in out_stats
   uint32_t ntiles;              // partition tiles
   uint32_t itemB, itemC;        // first phase-B (cell) and phase-C item
+  uint32_t base;                // position of the window's first entry in emit_row / emit_col
+  uint16_t strip_i, strip_j;    // strips of its first cell
   uint8_t logA, logBc, logR, logC;
+  uint8_t subA, subB;           // its cells: 2^subA x 2^subB strips from strip_i, strip_j
   uint8_t logRi, logCi;         // phase-C items of row and of column buckets (neighbours grouped)
-  uint8_t pad[14];
+  uint8_t logP;                 // rows of acc and partB that phase C and k_finish add up
+  uint8_t pad[3];
 };
 
 struct nsgc_small_desc {        // 16 bytes
@@ -236,6 +241,7 @@ struct nsgc_dev_plan {          // header of the device plan buffer
   uint32_t* goverW;             // cells that the wide pass of phase B left over, gover[2] of them
   uint32_t gover[4];
   uint32_t num_grid, gitemsA, gitemsS, gitemsB, gitemsC, gtile_log2;
+  uint32_t gmax_keys;           // a cell of more keys is abandoned (0: none is)
   // Work-queue counters of the small, B (workgroup), C and B (wavefront)
   // kernels, then grid B (small cells), B (big cells) and C.  Uploaded as
   // zero with every plan.

@@ -52,6 +52,9 @@ bool grid_window(uint64_t n, const nsgc_win_desc& d, const nsgc_tune& tune,
   g->n = uint32_t(n);
   g->logA = uint8_t(a);
   g->logBc = uint8_t(b);
+  g->subA = g->logA;
+  g->subB = g->logBc;
+  g->logP = uint8_t(a + b);
   g->logR = uint8_t(logR);
   g->logC = uint8_t(logC);
   // A phase-C item takes one bucket in windows below 2^19 packets and several

@@ -122,3 +122,27 @@ def test_graph_replays_between_other_work():
             assert_same(gpu_stats(src, dst, off, "graph", graph=g), want, f"{sizes} replay {k}")
             assert_same(gpu_stats(src, dst, off), want, f"{sizes} batched {k}")
     g.close()
+
+
+# the large-window tier's two-level grid: its smallest sizes, one more tile,
+# range, strip and cell size; what it gives up on is sorted
+@pytest.mark.parametrize("n,rbits,cbits", [
+    (1 << 20, 0, 0), ((1 << 20) + 1, 0, 0), ((1 << 21) - 3, 0, 0), (2560 << 10, 0, 0), ((2560 << 10) + 1, 0, 0),
+    ((2560 << 11) + 16385, 0, 0), ((1 << 24) + 77, 0, 0),
+    (1 << 20, 4, 4), ((1 << 20) + 5, 14, 0), (1 << 20, 0, 15), (1 << 20, 10, 10), (3000001, 12, 11),
+])
+def test_large_windows(n, rbits, cbits):
+    t = nsgc.default_tune()
+    t.large_min_log2 = 20
+    nsgc.set_tune(t)
+    rng = np.random.default_rng(n + rbits)
+    if rbits or cbits:   # distinct links with shared top bits of their hashed forms
+        src = hashed(rng.integers(0, 1 << (32 - rbits), n).astype(np.uint64), ROW)
+        dst = hashed(rng.integers(0, 1 << (32 - cbits), n).astype(np.uint64), COL)
+    else:
+        src, dst = heavy_tailed(rng, n), heavy_tailed(rng, n)
+        src[::97], dst[::89] = SOURCE_MARKER, DESTINATION_MARKER
+    off = np.array([0, n], np.int64)
+    assert int(nsgc.plan_inspect(off)["tier"][0]) == 3
+    say(f"[gpu] large grid {n} {rbits}/{cbits}")
+    assert_same(gpu_stats(src, dst, off), oracle.window_stats(src, dst, off), f"large {n} {rbits}/{cbits}")
