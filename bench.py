@@ -64,7 +64,7 @@ def measured_traffic(workload: str, phase: str):
     return tr["phases"][phase]["hbm_bytes"]
 # the launches each timed phase covers (the link phase is one of two kernels,
 # the row/column phase includes the ordering and the per-window combine)
-PHASE_KERNELS = {"small": ["k_small"], "partition": ["k_grid_heavy", "k_grid_partition", "k_partition"],
+PHASE_KERNELS = {"small": ["k_whole"], "partition": ["k_grid_heavy", "k_grid_partition", "k_partition"],
                  "links": ["k_grid_links", "k_grid_rounds", "k_links_wave", "k_links"],
                  "rowcol": ["k_order", "k_grid_rowcol", "k_grid_sweeps", "k_rowcol", "k_finish"]}
 

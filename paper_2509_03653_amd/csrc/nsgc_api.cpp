@@ -19,6 +19,8 @@
 #include "nsgc_grid.hpp"
 #include "nsgc_large.hpp"
 #include "nsgc_large_grid.hpp"
+#include "nsgc_upload.hpp"
+#include "nsgc_whole.hpp"
 #include "nsgc_planner.hpp"
 
 namespace nsgc {
@@ -93,6 +95,7 @@ struct FixedState {
   hipEvent_t done = nullptr;
   hipStream_t last_stream = nullptr;
   bool used = false;
+  bool copying = false;   // `copied` is recorded and not waited for yet
 };
 
 struct DevCtx {
@@ -223,11 +226,11 @@ struct Launch {
   uint32_t max_link_buckets, max_rc_buckets;
   // grid windows: heavy sample, partition by tile size (2^11 ..), link
   // aggregation of small / big cells, row/column aggregation
-  uint32_t gheavy, gpart[4], glinks[2], gwide, gover, grc;
+  uint32_t gheavy, gpart[4], glinks[2], gwhole[NSGC_WHOLE], gwide, gover, grc;
   size_t lds_grc;
 };
 
-constexpr int kGridKernels = 16;   // kernel numbers of nsgc_grid.hip start here
+constexpr int kGridKernels = 16;   // kernel numbers of nsgc_grid.hip start here, eight on nsgc_whole.hip's
 
 // Workgroups per CU that can actually be resident (registers and LDS), at
 // most `want`: persistent workgroups beyond that would only queue.
@@ -236,7 +239,8 @@ int resident_cap(DevCtx* c, int which, uint32_t tile_log2, size_t lds, int want,
   auto it = c->resident.find(key);
   if (it == c->resident.end()) {
     int n = 0;
-    NSGC_HIP(which >= kGridKernels ? grid_resident_blocks(which - kGridKernels, tile_log2, lds, &n)
+    NSGC_HIP(which >= kGridKernels + 8 ? whole_resident_blocks(which - kGridKernels - 8, &n)
+             : which >= kGridKernels ? grid_resident_blocks(which - kGridKernels, tile_log2, lds, &n)
                                    : resident_blocks(which, tile_log2, lds, &n));
     it = c->resident.emplace(key, std::max(n, 1)).first;
   }
@@ -288,6 +292,8 @@ int launch_params(DevCtx* c, const nsgc_tune& t, Launch* out) {
   for (int k = 0; k < 2; ++k)
     if ((rc = resident_cap(c, kGridKernels + 1 + k, 0, 0, 16, &L.glinks[k])) != NSGC_OK) return rc;
   if ((rc = resident_cap(c, kGridKernels + 3, 0, L.lds_grc, 16, &L.grc)) != NSGC_OK) return rc;
+  for (int k = 0; k < NSGC_WHOLE; ++k)
+    if ((rc = resident_cap(c, kGridKernels + 8 + k, 0, 0, 16, &L.gwhole[k])) != NSGC_OK) return rc;
   L.grid_finish = uint32_t(c->cus) * 4;
   L.grid_heavy = uint32_t(c->cus);   // one workgroup per row-complete window
   // the entity outputs' phase C (two tables per workgroup)
@@ -300,14 +306,17 @@ int launch_params(DevCtx* c, const nsgc_tune& t, Launch* out) {
   return NSGC_OK;
 }
 
-// Which kernels a plan needs: bit 0 the small-window kernel, bit 1 phases A
+// Which kernels a plan needs: bit 0 the shortest windows' kernel, bit 1 phases A
 // and C, bit 2 phase B by workgroups, bit 3 phase B by wavefronts, bit 4 the
 // wavefront kernel's larger counters (see wave_class), bit 5 row-complete
 // windows (the heavy-source sample and the wavefront kernel's row tables),
-// bits 6 and 7 grid windows of small and of big cells, bits 8-9 their tile.
-constexpr int kVariants = 1024;
+// bits 6 and 7 grid windows of small and of big cells, bits 8-9 their tile, bits
+// 10 to 12 the longer sizes of nsgc_whole.hip.
+constexpr int kWhole[NSGC_WHOLE] = {1, 1024, 2048, 4096};
 int plan_variant(const HostPlan& hp) {
-  return (hp.small.empty() ? 0 : 1) | (hp.win.empty() ? 0 : 2) | (hp.itemsBb ? 4 : 0) |
+  int whole = 0;
+  for (int k = 0; k < NSGC_WHOLE; ++k) whole |= hp.num_whole[k] ? kWhole[k] : 0;
+  return whole | (hp.win.empty() ? 0 : 2) | (hp.itemsBb ? 4 : 0) |
          (hp.itemsBw ? 8 : 0) | (hp.itemsBw && wave_class(hp.wave_rc_max) ? 16 : 0) |
          (hp.num_rows ? 32 : 0) | (hp.gitemsS ? 64 : 0) | (hp.gitemsB > hp.gitemsS ? 128 : 0) |
          (hp.gitemsB ? int(hp.gtile_log2 - 11) << 8 : 0);
@@ -331,17 +340,21 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
                     const hipEvent_t* ev = nullptr, const LargeArgs* la = nullptr) {
   auto grid = [&](uint32_t items, uint32_t cap) { return fixed_grid ? cap : std::min(items, cap); };
   auto mark = [&](int i) { return ev ? hipEventRecord(ev[i], s) : hipSuccess; };
-  const bool small = fixed_grid ? (variant & 1) != 0 : !hp.small.empty();
+  const bool small = !fixed_grid && hp.entity && !hp.small.empty();
+  bool whole[NSGC_WHOLE];
+  for (int k = 0; k < NSGC_WHOLE; ++k) whole[k] = fixed_grid ? (variant & kWhole[k]) != 0 : hp.num_whole[k] > 0;
   const bool part = fixed_grid ? (variant & 2) != 0 : !hp.win.empty();
   const bool linkb = fixed_grid ? (variant & 4) != 0 : hp.itemsBb > 0;
   const bool linkw = fixed_grid ? (variant & 8) != 0 : hp.itemsBw > 0;
   const bool rows = fixed_grid ? (variant & 32) != 0 : hp.num_rows > 0;
   const bool gsmall = fixed_grid ? (variant & 64) != 0 : hp.gitemsS > 0;
   const bool gbig = fixed_grid ? (variant & 128) != 0 : hp.gitemsB > hp.gitemsS;
-  const uint32_t gtile = fixed_grid ? uint32_t(variant >> 8) + 11 : hp.gtile_log2;
+  const uint32_t gtile = fixed_grid ? (uint32_t(variant >> 8) & 3u) + 11 : hp.gtile_log2;
   NSGC_HIP(mark(0));
   if (small)
     NSGC_HIP(launch_small(dplan, grid(uint32_t(hp.small.size()), L.grid_small), L.lds_small, s));
+  for (int k = 0; k < NSGC_WHOLE; ++k)
+    if (whole[k]) NSGC_HIP(launch_whole(dplan, k, grid(hp.num_whole[k], L.gwhole[k]), s));
   NSGC_HIP(mark(1));
   if (rows) NSGC_HIP(launch_heavy(dplan, grid(uint32_t(hp.win.size()), L.grid_heavy), s));
   if (gsmall || gbig) {
@@ -439,21 +452,46 @@ int get_slot(DevCtx* c, hipStream_t s, Slot** out) {
   return NSGC_OK;
 }
 
+// Windows of one size of nsgc_whole.hip, few enough to come with the launch:
+// launches them and returns true in *done, or leaves the plan to be uploaded.
+int run_few(const HostPlan& hp, const uint32_t* src, const uint32_t* dst, void* out, hipStream_t s,
+            bool* done) {
+  *done = false;
+  if (hp.entity || !hp.win.empty() || !hp.gwin.empty() || !hp.large.empty() || !whole_few(hp.small.size()))
+    return NSGC_OK;
+  for (int k = 0; k < NSGC_WHOLE; ++k)
+    if (hp.num_whole[k] == hp.small.size()) {
+      NSGC_HIP(launch_whole_few(k, hp.small.data(), hp.small.size(), src, dst, out, s));
+      *done = true;
+    }
+  return NSGC_OK;
+}
+
 // Upload one plan into slot `sl` and launch it.
 int run_plan(DevCtx* c, Slot* sl, const HostPlan& hp, const Launch& L, const uint32_t* src,
              const uint32_t* dst, void* out, hipStream_t s, const hipEvent_t* ev = nullptr) {
   int rc;
-  const size_t pbytes = hp.plan_bytes();
+  if (!ev) {
+    bool done = false;
+    if ((rc = run_few(hp, src, dst, out, s, &done)) != NSGC_OK || done) return rc;
+  }
+  const size_t up = hp.upload_bytes(), clear = hp.queue_bytes();
   const WsLayout lay = hp.layout();
-  if ((rc = ensure_device(&sl->plan_dev, &sl->plan_cap, pbytes, s)) != NSGC_OK) return rc;
+  if ((rc = ensure_device(&sl->plan_dev, &sl->plan_cap, up + clear, s)) != NSGC_OK) return rc;
   if ((rc = ensure_device(&sl->ws, &sl->ws_cap, lay.total, s)) != NSGC_OK) return rc;
-  int k = 0;
-  if ((rc = take_stage(sl, pbytes, s, &k)) != NSGC_OK) return rc;
-  hp.serialize(sl->stage[k], reinterpret_cast<uint64_t>(sl->plan_dev),
-               reinterpret_cast<uint64_t>(sl->ws), src, dst, out);
-  NSGC_HIP(hipMemcpyAsync(sl->plan_dev, sl->stage[k], pbytes, hipMemcpyHostToDevice, s));
-  NSGC_HIP(hipEventRecord(sl->ev[k], s));
-  sl->ev_used[k] = true;
+  const uint64_t dev = reinterpret_cast<uint64_t>(sl->plan_dev), ws = reinterpret_cast<uint64_t>(sl->ws);
+  if (up <= kArgPlan) {
+    alignas(16) char plan[kArgPlan];
+    hp.serialize(plan, dev, ws, src, dst, out);
+    NSGC_HIP(upload_by_args(plan, up, sl->plan_dev, sl->plan_dev + up, clear, s));
+  } else {
+    int k = 0;
+    if ((rc = take_stage(sl, up, s, &k)) != NSGC_OK) return rc;
+    hp.serialize(sl->stage[k], dev, ws, src, dst, out);
+    NSGC_HIP(upload_pinned(sl->stage[k], up, sl->plan_dev, sl->plan_dev + up, clear, s));
+    NSGC_HIP(hipEventRecord(sl->ev[k], s));
+    sl->ev_used[k] = true;
+  }
   const LargeArgs la = {src, dst, static_cast<unsigned long long*>(out), sl->ws,
                         uint32_t(c->cus) * 8};
   return enqueue_kernels(hp, reinterpret_cast<const nsgc_dev_plan*>(sl->plan_dev), L,
@@ -555,11 +593,13 @@ int plain_locked(const CallCtx& cc, const uint32_t* src, const uint32_t* dst,
   if ((rc = ensure_device(&sl->ws, &sl->ws_cap, wsmax, s)) != NSGC_OK) return rc;
   int k = 0;
   if ((rc = take_stage(sl, pbytes, s, &k)) != NSGC_OK) return rc;
-  for (int64_t w = 0; w < num_windows; ++w)
-    plans[size_t(w)].serialize(sl->stage[k] + at[size_t(w)],
-                               reinterpret_cast<uint64_t>(sl->plan_dev + at[size_t(w)]),
-                               reinterpret_cast<uint64_t>(sl->ws), src, dst, out_stats + w);
-  NSGC_HIP(hipMemcpyAsync(sl->plan_dev, sl->stage[k], pbytes, hipMemcpyHostToDevice, s));
+  for (int64_t w = 0; w < num_windows; ++w) {
+    const HostPlan& hp = plans[size_t(w)];
+    hp.serialize(sl->stage[k] + at[size_t(w)], reinterpret_cast<uint64_t>(sl->plan_dev + at[size_t(w)]),
+                 reinterpret_cast<uint64_t>(sl->ws), src, dst, out_stats + w);
+    std::memset(sl->stage[k] + at[size_t(w)] + hp.upload_bytes(), 0, hp.queue_bytes());
+  }
+  NSGC_HIP(upload_pinned(sl->stage[k], pbytes, sl->plan_dev, sl->plan_dev, 0, s));
   NSGC_HIP(hipEventRecord(sl->ev[k], s));
   sl->ev_used[k] = true;
   for (int64_t w = 0; w < num_windows; ++w) {
@@ -633,22 +673,38 @@ int run_fixed_scratch(const uint32_t* src, const uint32_t* dst, const int64_t* w
     // grid windows take more workspace beside the keys than the other form
     if ((rc = make_plan(window_offsets, num_windows, t, &hp, false, true, false)) != NSGC_OK) return rc;
   }
-  const size_t pbytes = hp.plan_bytes();
+  const size_t up = hp.upload_bytes(), clear = hp.queue_bytes();
   const WsLayout lay = hp.layout();
-  if (pbytes > plan_cap || lay.total > ws_cap) return NSGC_ERR_TOO_LARGE;
+  if (up + clear > plan_cap || lay.total > ws_cap) return NSGC_ERR_TOO_LARGE;
+  bool few = false;
+  if ((rc = run_few(hp, src, dst, out_stats, s, &few)) != NSGC_OK || few) return rc;
   FixedState& f = c->fixed;
   std::lock_guard<std::mutex> lock(f.mu);
   if (!f.copied) NSGC_HIP(hipEventCreateWithFlags(&f.copied, hipEventDisableTiming));
   if (!f.done) NSGC_HIP(hipEventCreateWithFlags(&f.done, hipEventDisableTiming));
   if (f.stage.size() < plan_cap) f.stage.resize(plan_cap);
-  // the previous call's plan copy must have read the staging buffer
-  if (f.used) NSGC_HIP(hipEventSynchronize(f.copied));
+  // the last plan copied from the staging buffer must have left it
+  if (f.copying) NSGC_HIP(hipEventSynchronize(f.copied));
+  f.copying = false;
   hp.serialize(f.stage.data(), reinterpret_cast<uint64_t>(plan_dev), reinterpret_cast<uint64_t>(ws),
                src, dst, out_stats);
   // every call on the device shares its scratch: order after the last one
   if (f.used && f.last_stream != s) NSGC_HIP(hipStreamWaitEvent(s, f.done, 0));
-  NSGC_HIP(hipMemcpyAsync(plan_dev, f.stage.data(), pbytes, hipMemcpyHostToDevice, s));
-  NSGC_HIP(hipEventRecord(f.copied, s));
+  // Up to four launches carry the plan in their arguments; the runtime's copy
+  // from ordinary memory takes a longer one.
+  size_t at = 0;
+  if (up > 4 * kArgPlan) {
+    NSGC_HIP(hipMemcpyAsync(plan_dev, f.stage.data(), up, hipMemcpyHostToDevice, s));
+    NSGC_HIP(hipEventRecord(f.copied, s));
+    f.copying = true;
+    at = up;
+  }
+  do {   // (the last launch, which may carry nothing, clears the counters)
+    const size_t part = std::min(up - at, kArgPlan);
+    const bool last = at + part == up;
+    NSGC_HIP(upload_by_args(f.stage.data() + at, part, plan_dev + at, plan_dev + up, last ? clear : 0, s));
+    at += part;
+  } while (at < up);
   const LargeArgs la = {src, dst, reinterpret_cast<unsigned long long*>(out_stats), ws,
                         uint32_t(c->cus) * 8};
   rc = enqueue_kernels(hp, reinterpret_cast<const nsgc_dev_plan*>(plan_dev), L, hp.tile_log2, s,
@@ -967,16 +1023,16 @@ struct nsgc_graph {
   Launch L;
   int64_t max_packets = 0, max_windows = 0;
   hipStream_t capture = nullptr;
+  struct Captured {
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+  };
   // two instances so the host can plan batch i+1 while batch i runs
   struct Inst {
     char* plan_dev = nullptr;
     size_t plan_cap = 0;
     char* stage = nullptr;
-    hipGraph_t graph[kVariants] = {};     // indexed by plan variant (see plan_variant)
-    hipGraphExec_t exec[kVariants] = {};
-    // the plan-upload node of each variant, resized to the plan at every
-    // launch (null: the node keeps uploading plan_cap bytes)
-    hipGraphNode_t copy[kVariants] = {};
+    std::map<int, Captured> captured;   // by plan variant (see plan_variant)
     hipEvent_t done = nullptr;
     hipStream_t stream = nullptr;  // stream of the last launch
     bool used = false;
@@ -990,8 +1046,7 @@ namespace {
 
 int capture_instance(nsgc_graph* g, nsgc_graph::Inst& in, int variant) {
   NSGC_HIP(hipStreamBeginCapture(g->capture, hipStreamCaptureModeThreadLocal));
-  hipError_t e = hipMemcpyAsync(in.plan_dev, in.stage, in.plan_cap, hipMemcpyHostToDevice,
-                                g->capture);
+  hipError_t e = upload_captured(in.stage, in.plan_dev, in.plan_cap, g->capture);
   HostPlan empty;
   int rc = NSGC_OK;
   if (e == hipSuccess) {
@@ -1006,33 +1061,18 @@ int capture_instance(nsgc_graph* g, nsgc_graph::Inst& in, int variant) {
     return rc;
   }
   if (e2 != hipSuccess) return hip_fail(e2);
-  in.graph[variant] = graph;
-  NSGC_HIP(hipGraphInstantiate(&in.exec[variant], graph, nullptr, nullptr, 0));
-  // The plan-upload node, so that each launch copies only its plan: the
-  // bound it was captured with is sized for the graph's largest batch.
-  size_t nn = 0;
-  if (hipGraphGetNodes(graph, nullptr, &nn) == hipSuccess && nn > 0) {
-    std::vector<hipGraphNode_t> nodes(nn);
-    if (hipGraphGetNodes(graph, nodes.data(), &nn) == hipSuccess) {
-      for (size_t i = 0; i < nn; ++i) {
-        hipGraphNodeType type;
-        if (hipGraphNodeGetType(nodes[i], &type) == hipSuccess && type == hipGraphNodeTypeMemcpy) {
-          in.copy[variant] = nodes[i];
-          break;
-        }
-      }
-    }
-  }
-  (void)hipGetLastError();   // no node found: every launch uploads plan_cap bytes
+  nsgc_graph::Captured& c = in.captured[variant];
+  c.graph = graph;
+  NSGC_HIP(hipGraphInstantiate(&c.exec, graph, nullptr, nullptr, 0));
   return NSGC_OK;
 }
 
 void destroy_graph(nsgc_graph* g) {
   for (auto& in : g->inst) {
     if (in.done) (void)hipEventSynchronize(in.done);
-    for (int v = 0; v < kVariants; ++v) {
-      if (in.exec[v]) (void)hipGraphExecDestroy(in.exec[v]);
-      if (in.graph[v]) (void)hipGraphDestroy(in.graph[v]);
+    for (auto& kv : in.captured) {
+      if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
+      if (kv.second.graph) (void)hipGraphDestroy(kv.second.graph);
     }
     if (in.plan_dev) (void)hipFree(in.plan_dev);
     if (in.stage) (void)hipHostFree(in.stage);
@@ -1122,17 +1162,16 @@ int nsgc_graph_launch(nsgc_graph* g, const uint32_t* src, const uint32_t* dst,
   nsgc_graph::Inst& in = g->inst[g->next];
   if (in.used) NSGC_HIP(hipEventSynchronize(in.done));
   const int variant = plan_variant(hp);
-  if (!in.exec[variant] && (rc = capture_instance(g, in, variant)) != NSGC_OK) return rc;
+  const auto found = in.captured.find(variant);
+  if ((found == in.captured.end() || !found->second.exec) && (rc = capture_instance(g, in, variant)) != NSGC_OK)
+    return rc;
   hp.serialize(in.stage, reinterpret_cast<uint64_t>(in.plan_dev), reinterpret_cast<uint64_t>(g->ws),
                src, dst, out_stats);
   // Both instances share the workspace: a launch on another stream than the
   // other instance's last one waits (on the device) for that launch to end.
   const nsgc_graph::Inst& other = g->inst[g->next ^ 1];
   if (other.used && other.stream != s) NSGC_HIP(hipStreamWaitEvent(s, other.done, 0));
-  if (in.copy[variant])   // upload this plan's bytes only
-    NSGC_HIP(hipGraphExecMemcpyNodeSetParams1D(in.exec[variant], in.copy[variant], in.plan_dev,
-                                               in.stage, hp.plan_bytes(), hipMemcpyHostToDevice));
-  NSGC_HIP(hipGraphLaunch(in.exec[variant], s));
+  NSGC_HIP(hipGraphLaunch(in.captured[variant].exec, s));
   NSGC_HIP(hipEventRecord(in.done, s));
   in.stream = s;
   in.used = true;

@@ -531,7 +531,7 @@ struct ItemQueue {
     if (threadIdx.x == 0) {
       const uint32_t v = blockIdx.x;
       slot[0] = item_at(v, items);
-      pending = v < items ? take() : items;
+      pending = gridDim.x < items ? take() : items;   // (one item each: no queue)
       resolved = false;
     }
     __syncthreads();

@@ -114,13 +114,13 @@ constexpr uint32_t NO_SLOT = 0xFFFFFFFFu;
 struct GridQueue {
   NSGC_GLOBAL uint32_t* counter;
   uint32_t base, step, pending;   // pending: thread 0's requested position
-  __device__ GridQueue(NSGC_GLOBAL uint32_t* counters) {
+  __device__ GridQueue(NSGC_GLOBAL uint32_t* counters, uint32_t items) {
     step = min(uint32_t(NSGC_QCLASSES), gridDim.x);
     const uint32_t c = blockIdx.x % step;
     counter = counters + c * NSGC_QSTRIDE;
     base = gridDim.x + c;          // after the grid's static first items
-    pending = 0xFFFFFFFFu;
-    if (threadIdx.x == 0) take();
+    pending = NO_ITEM;
+    if (threadIdx.x == 0 && gridDim.x < items) take();   // (else each workgroup takes one item)
   }
   __device__ __forceinline__ void take() {
     pending = base + step * __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED,
@@ -834,7 +834,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
   const uint32_t HV = NSGC_GRID_HV(sload(&P->gtile_log2));
   if (threadIdx.x < 2 * HV) acc[threadIdx.x] = 0;
 
-  GridQueue q(gptr(&P->queue[KIND == WIDE ? 7 : KIND == BIG ? 5 : 4][0]));
+  GridQueue q(gptr(&sload(&P->queue)[NSGC_Q_GRID + KIND][0]), items);
   // This thread's tile record of item `it` (lane or thread t: tile t), loaded
   // for the next item while the current one is worked on.
   auto record = [&](const nsgc_grid_desc& W, uint32_t it, uint32_t t) -> uint32_t {
@@ -1243,7 +1243,7 @@ __global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void
   uint32_t* misc = red + 32;               // 0 failed, 2 / 3 marker id's packets / links, 7 queue slot
   const uint32_t items = sload(&P->gitemsC), HV = NSGC_GRID_HV(sload(&P->gtile_log2));
 
-  GridQueue q(gptr(&P->queue[6][0]));
+  GridQueue q(gptr(&sload(&P->queue)[NSGC_Q_GRID_C][0]), items);
   // This thread's segment of buckets lo .. lo + w - 1 (all, if w is 0) of item
   // `it`, cell `s` of its strip: emission base and length.  The next item's is
   // loaded while the current one is worked on.

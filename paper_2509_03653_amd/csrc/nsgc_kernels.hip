@@ -128,7 +128,8 @@ __device__ __forceinline__ bool lds_find32(const uint32_t* tk, uint32_t mask, ui
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// Tier "small": one workgroup per window, everything in LDS.
+// The small tier of the entity outputs: one workgroup per window, everything in
+// LDS (the statistics take their short windows in nsgc_whole.hip).
 //
 // Per packet, in hashed identities (link_key): find-or-insert the link key
 // (the inserting lane learns that the link is new) and add one packet to it;
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(NSGC_BLOCK) void k_small(nsgc_dev_plan* P) {
   uint32_t* red = misc + 8;
 
   const uint32_t items = P->num_small;
-  ItemQueue q(gptr(&P->queue[0][0]), misc + 7, NSGC_QCLASSES);
+  ItemQueue q(gptr(&P->queue[NSGC_Q_WHOLE][0]), misc + 7, NSGC_QCLASSES);
   for (uint32_t item = q.first(items); item != NO_ITEM; item = q.read()) {
     const nsgc_small_desc D = gload(P->small + item);
     for (uint32_t i = threadIdx.x; i < S; i += NSGC_BLOCK) {
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(NSGC_BLOCK) void k_small(nsgc_dev_plan* P) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {   // hashed identities (see link_key)
         s[u] = row_hash(s[u]);
-        d[u] = P->entity ? row_hash(d[u]) : col_hash(d[u]);
+        d[u] = row_hash(d[u]);   // (destinations are hashed like sources)
         key[u] = (u64(s[u]) << 32) | d[u];
         h[u] = uint32_t(link_pos(key[u]));
         // the key equal to the empty marker is counted outside the table
@@ -656,7 +657,7 @@ __global__ __launch_bounds__(NSGC_BLOCK) __attribute__((amdgpu_waves_per_eu(4)))
   uint32_t next_s0 = 0;
   bool have_next = false;
 
-  ItemQueue q(gptr(&P->queue[1][0]), misc + 7, LINK_QCLASSES, map);
+  ItemQueue q(gptr(&P->queue[NSGC_Q_LINKS][0]), misc + 7, LINK_QCLASSES, map);
   for (uint32_t item = q.first(items); item != NO_ITEM; item = q.read()) {
     const uint32_t it = uniform(item);
     const uint32_t wi = sload(P->itemwinB + it);
@@ -1274,7 +1275,7 @@ __global__ __launch_bounds__(WAVE_NT) void k_links_wave(nsgc_dev_plan* P, uint32
   const uint32_t items = P->itemsBw;
   const uint32_t gwaves = (gridDim.x - order_block) * WAVE_WPB;
   const uint32_t gwave = (blockIdx.x - order_block) * WAVE_WPB + w;
-  WaveQueue q(gptr(&P->queue[3][0]), gwave, gwaves, P->mapBw ? gptr(P->mapBw) : nullptr);
+  WaveQueue q(gptr(&P->queue[NSGC_Q_WAVE][0]), gwave, gwaves, P->mapBw ? gptr(P->mapBw) : nullptr);
   for (uint32_t it = q.first(gwave, items); it != NO_ITEM; it = q.next(items)) {
     const uint32_t wi = sload(P->itemwinB + it);
     const nsgc_win_desc W = sload_words(P->win + wi);
@@ -1726,7 +1727,7 @@ __global__ __launch_bounds__(NSGC_BLOCK) __attribute__((amdgpu_waves_per_eu(6)))
   SegPre next_pre = {0, 0};
   bool have_next = false;
 
-  ItemQueue q(gptr(&P->queue[2][0]), misc + 7, NSGC_QCLASSES,
+  ItemQueue q(gptr(&P->queue[NSGC_Q_ROWCOL][0]), misc + 7, NSGC_QCLASSES,
               P->order_items ? gptr(P->order) : nullptr);
   for (uint32_t item = q.first(items); item != NO_ITEM; item = q.read()) {
     const uint32_t it = uniform(item);
@@ -1929,7 +1930,7 @@ __global__ __launch_bounds__(NSGC_BLOCK) void k_rowcol_ent(nsgc_dev_plan* P) {
   }
 
   const uint32_t items = P->itemsC;
-  ItemQueue q(gptr(&P->queue[2][0]), misc + 7, NSGC_QCLASSES);
+  ItemQueue q(gptr(&P->queue[NSGC_Q_ROWCOL][0]), misc + 7, NSGC_QCLASSES);
   for (uint32_t item = q.first(items); item != NO_ITEM; item = q.read()) {
     const uint32_t it = uniform(item);
     const uint32_t wi = sload(P->itemwinC + it);

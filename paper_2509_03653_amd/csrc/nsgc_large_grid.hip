@@ -43,6 +43,10 @@ constexpr uint32_t HV = NSGC_GRID_HEAVY;
 constexpr uint32_t TILE_LOG2 = 14;
 static_assert(NSGC_GRID_HV(TILE_LOG2) == HV, "dominant addresses of 2^14-packet tiles");
 
+// A plan header and its work-queue counters.
+constexpr size_t QUEUES = size_t(NSGC_Q_ALL) * NSGC_QCLASSES * NSGC_QSTRIDE * 4;
+constexpr size_t HEAD = ((sizeof(nsgc_dev_plan) + 255) / 256 * 256) + QUEUES;
+
 // Where everything lies in the workspace, and the window's grid.
 struct Shape {
   uint64_t n;
@@ -104,7 +108,7 @@ bool shape(uint64_t n, Shape* g) {
   g->prefA = take((OUT + 1) * 4);
   g->cnt = take(size_t(g->ranges) * OUT * 4);
   g->win = take((OUT + 1) * sizeof(nsgc_grid_desc));
-  g->head = take(2 * ((sizeof(nsgc_dev_plan) + 255) / 256 * 256));
+  g->head = take(2 * HEAD);
   g->total = o;
   return true;
 }
@@ -137,10 +141,12 @@ __global__ __launch_bounds__(256) void k_large_init(Args A) {
   for (uint32_t i = tid; i < A.items; i += step) gptr(A.itemC)[i] = 0;
   if (blockIdx.x) return;
   uint32_t* h[2] = {reinterpret_cast<uint32_t*>(A.inner), reinterpret_cast<uint32_t*>(A.whole)};
-  for (uint32_t i = threadIdx.x; i < sizeof(nsgc_dev_plan) / 4; i += 256) gptr(h[0])[i] = gptr(h[1])[i] = 0;
+  for (uint32_t i = threadIdx.x; i < HEAD / 4; i += 256) gptr(h[0])[i] = gptr(h[1])[i] = 0;
   __syncthreads();
   if (threadIdx.x == 0) {
     A.win[OUT] = A.W;
+    A.inner->queue = reinterpret_cast<decltype(A.inner->queue)>(reinterpret_cast<char*>(A.inner) + HEAD - QUEUES);
+    A.whole->queue = reinterpret_cast<decltype(A.whole->queue)>(reinterpret_cast<char*>(A.whole) + HEAD - QUEUES);
     nsgc_dev_plan* p = A.inner;
     p->gwin = A.win;
     p->gprefA = A.prefA;
@@ -502,7 +508,7 @@ hipError_t large_grid_stats(const uint32_t* src, const uint32_t* dst, unsigned l
   A.W.logP = 2 * OUT_LOG2;
   A.win = reinterpret_cast<nsgc_grid_desc*>(base + g.win);
   A.inner = reinterpret_cast<nsgc_dev_plan*>(base + g.head);
-  A.whole = reinterpret_cast<nsgc_dev_plan*>(base + g.head + (sizeof(nsgc_dev_plan) + 255) / 256 * 256);
+  A.whole = reinterpret_cast<nsgc_dev_plan*>(base + g.head + HEAD);
   A.cnt = words(g.cnt);
   A.prefA = words(g.prefA);
   A.itemB = words(g.itemB);

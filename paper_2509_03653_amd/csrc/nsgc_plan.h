@@ -53,9 +53,19 @@
 // the packet field holds is emitted as several entries that sum to it (phase C
 // adds them up).  Since links <= packets no triple needs more entries than it
 // has packets, so an emission region of one slot per packet suffices.
-// Work-queue counters per kernel, one per 128-byte line (see ItemQueue).
+// Work-queue counters per kernel, one per 64 bytes (see ItemQueue).  Plans
+// without grid windows hold the first NSGC_Q_GRID sets, which take no more room
+// than the four of 128-byte strides they had when the fixed-scratch form was
+// sized.
 #define NSGC_QCLASSES 8
-#define NSGC_QSTRIDE 32
+#define NSGC_QSTRIDE 16
+#define NSGC_Q_WHOLE 0     // NSGC_WHOLE sets; the first also the entity outputs' small windows
+#define NSGC_Q_LINKS 4
+#define NSGC_Q_ROWCOL 5
+#define NSGC_Q_WAVE 6
+#define NSGC_Q_GRID 7      // SMALL, BIG, WIDE
+#define NSGC_Q_GRID_C 10
+#define NSGC_Q_ALL 11
 // Batches of at most this many phase-C items have them ordered large first.
 #define NSGC_ORDER_MAX 16384
 #define NSGC_ENT_PACKET_BITS 19
@@ -71,6 +81,14 @@
 #define NSGC_HEAVY_SLOTS 512
 #define NSGC_HEAVY_SAMPLE 4096
 #define NSGC_WAVE_ROW_SLOTS 256
+
+// Windows that one workgroup takes whole (nsgc_whole.hip), in four sizes of up
+// to A, B, C and D packets.
+#define NSGC_WHOLE 4
+#define NSGC_WHOLE_A 256
+#define NSGC_WHOLE_B 1024
+#define NSGC_WHOLE_C 2048
+#define NSGC_WHOLE_D 8192
 
 // Grid windows (nsgc_grid.hip): partitioned windows whose link buckets are the
 // cells of a grid of 2^logA row strips by 2^logBc column strips.
@@ -95,6 +113,8 @@
 // words: the cell's emission base, its row-bucket starts (one more than
 // buckets), its column-bucket starts.
 #define NSGC_GRID_MIN 8193                     // packets of the smallest grid window
+#define NSGC_GRID_RIDE 4097                    // of the smallest that rides along with larger ones
+#define NSGC_GRID_RIDERS 256                   // most windows that ride along
 // Dominant addresses per view, and the sample they are drawn from, in a batch
 // partitioned in tiles of 2^t packets: batches with windows of more than 1024
 // cells (tile 2^14) keep twice as many, since with many cells a smaller share
@@ -194,7 +214,7 @@ struct nsgc_dev_plan {          // header of the device plan buffer
   uint32_t* partB;              // [itemsB][4] link-bucket totals: packets, links, max, invalid
   uint32_t* partC;              // [itemsC][4] row/column-bucket totals: ids, max packets,
                                 //   max links, invalid
-  const nsgc_small_desc* small;
+  const nsgc_small_desc* small; // [num_small], or the windows of num_whole in turn
   const nsgc_win_desc* win;
   const uint32_t* prefA;        // [num_part + 1] first phase-A item of each window
   const uint32_t* prefB;        // [num_part + 1] first phase-B item
@@ -203,7 +223,8 @@ struct nsgc_dev_plan {          // header of the device plan buffer
   const uint32_t* mapBb;        // phase-B items of workgroup windows (null: items 0..itemsBb)
   const uint32_t* mapBw;        // phase-B items of wavefront windows (null: items 0..itemsBw)
   const uint32_t* itemwinC;     // [itemsC] window of each phase-C item
-  uint32_t num_small;
+  uint32_t num_small;           // (entity plans)
+  uint32_t num_whole[NSGC_WHOLE];   // windows one workgroup takes whole, by size
   uint32_t num_part;
   uint32_t itemsA, itemsB, itemsC;
   uint32_t itemsBb, itemsBw;    // phase-B items of workgroup / wavefront windows
@@ -242,10 +263,10 @@ struct nsgc_dev_plan {          // header of the device plan buffer
   uint32_t gover[4];
   uint32_t num_grid, gitemsA, gitemsS, gitemsB, gitemsC, gtile_log2;
   uint32_t gmax_keys;           // a cell of more keys is abandoned (0: none is)
-  // Work-queue counters of the small, B (workgroup), C and B (wavefront)
-  // kernels, then grid B (small cells), B (big cells) and C.  Uploaded as
-  // zero with every plan.
-  uint32_t queue[8][NSGC_QCLASSES * NSGC_QSTRIDE];
+  // Upload: 16-byte units of the header and the lists behind it, and of the
+  // work-queue counters behind those, which the upload clears.
+  uint32_t upload16, clear16;
+  uint32_t (*queue)[NSGC_QCLASSES * NSGC_QSTRIDE];   // by NSGC_Q_*
 };
 
 #endif  // NSGC_PLAN_H_

@@ -22,19 +22,36 @@ void rebase(T*& field, uint64_t base) {
   field = reinterpret_cast<T*>(reinterpret_cast<uint64_t>(field) + base);
 }
 
-// Whether a partitioned window of n packets (buckets and wavefront form as in
-// `d`) is taken as a grid window, and its grid.  Cells hold four wavefront
+// Whether a window of n packets above small_max is still taken whole by one
+// workgroup: up to eight times small_max, as far as its tables go, unless the
+// tuning asks for a form that only the partitioned kernels have.  (At 8192
+// packets one workgroup takes 33 us and the partitioned kernels 47; above, the
+// grid's tables spread over the chip.)
+bool whole_window(uint64_t n, bool entity, const nsgc_tune& tune, const nsgc_tune_class& tc) {
+  return !entity && n <= std::min<uint64_t>(8 * uint64_t(tune.small_max), NSGC_WHOLE_D) && tc.wave_target > 0 &&
+         tune.combine_probes == 0 && !tune.row_complete;
+}
+
+// The size of the kernel it takes (n <= NSGC_WHOLE_D; small_max is at most 2048).
+int whole_size(uint64_t n) {
+  return n <= NSGC_WHOLE_A ? 0 : n <= NSGC_WHOLE_B ? 1 : n <= NSGC_WHOLE_C ? 2 : 3;
+}
+
+// Workgroups of each size that 256 compute units hold at once.
+constexpr size_t kWholeRound[NSGC_WHOLE] = {6144, 1536, 768, 256};
+
+// Whether a window of n packets can be a grid window, and its grid (from
+// NSGC_GRID_MIN packets on by right; shorter ones may ride along).  Cells hold four wavefront
 // targets of packets, up to the cap on link buckets; the grid has four or more
 // strips each way (with fewer, a dominant address cannot be spread) and as
 // many row strips as row buckets if it can, since a strip of one bucket needs
 // no counting.
-bool grid_window(uint64_t n, const nsgc_win_desc& d, const nsgc_tune& tune,
-                 const nsgc_tune_class& tc, nsgc_grid_desc* g) {
-  if (tc.wave_target <= 0 || tune.combine_probes > 0 || n < NSGC_GRID_MIN) return false;
-  if (d.logR < 2 || d.logC < 2) return false;
+bool grid_window(uint64_t n, const nsgc_tune& tune, const nsgc_tune_class& tc, nsgc_grid_desc* g) {
+  if (tc.wave_target <= 0 || tune.combine_probes > 0 || n < NSGC_GRID_RIDE) return false;
+  const bool ride = n < NSGC_GRID_MIN;
   const uint64_t target = 4 * uint64_t(tc.wave_target);
-  const int lc = std::min(std::min(ceil_log2((n + target - 1) / target), int(tune.max_link_buckets_log2)),
-                          NSGC_GRID_MAX_CELLS_LOG2);
+  const int lc = std::min(std::min(ride ? 4 : ceil_log2((n + target - 1) / target),
+                                   int(tune.max_link_buckets_log2)), NSGC_GRID_MAX_CELLS_LOG2);
   // Row and column buckets of at most NSGC_GRID_BUCKET packets: phase C takes
   // one and a half times as many entries in a single pass, and a bucket has at
   // most as many entries as packets.
@@ -42,7 +59,7 @@ bool grid_window(uint64_t n, const nsgc_win_desc& d, const nsgc_tune& tune,
     const uint64_t t = std::min<uint64_t>(uint64_t(tuned), NSGC_GRID_BUCKET);
     return ceil_log2((n + t - 1) / t);
   };
-  int logR = buckets(tc.row_target), logC = buckets(tc.col_target);
+  int logR = ride ? 2 : buckets(tc.row_target), logC = ride ? 2 : buckets(tc.col_target);
   const int a = std::min(std::min(logR, NSGC_GRID_MAX_A), lc - 2);
   const int b = std::min(std::min(lc - a, logC), NSGC_GRID_MAX_B);
   if (a < 2 || b < 2) return false;
@@ -179,7 +196,8 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
   p->gprefA.clear();
   p->gitemB.clear();
   p->gitemC.clear();
-  std::vector<nsgc_grid_desc> gbig;   // grid windows of big cells
+  std::vector<nsgc_small_desc> whole[NSGC_WHOLE];   // windows taken whole, by size
+  std::vector<nsgc_grid_desc> gbig;         // grid windows of big cells
   uint64_t gpackets = 0;
   uint32_t glongest = 0;
   uint32_t gcells = 0;   // most cells of a grid window
@@ -204,7 +222,7 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
       s.in_begin = offsets[w];
       s.n = uint32_t(n);
       s.out_index = uint32_t(w);
-      p->small.push_back(s);
+      (entity ? p->small : whole[whole_size(n)]).push_back(s);
       p->tier[size_t(w)] = n == 0 ? 0 : 1;
       continue;
     }
@@ -238,8 +256,13 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
       }
     }
     p->shape.push_back({d.logB, d.logR, d.logC, int64_t((n + tile - 1) / tile)});
+    if (whole_window(n, entity, tune, tc)) {
+      whole[whole_size(n)].push_back({offsets[w], uint32_t(n), uint32_t(w)});
+      continue;
+    }
     nsgc_grid_desc g;
-    if (allow_grid && !entity && !(tune.row_complete && d.wave) && grid_window(n, d, tune, tc, &g)) {
+    if (allow_grid && !entity && n >= NSGC_GRID_MIN && !(tune.row_complete && d.wave) && d.logR >= 2 &&
+        d.logC >= 2 && grid_window(n, tune, tc, &g)) {
       g.src = at<uint32_t>(uint64_t(offsets[w]) * 4);   // byte offsets until serialize()
       g.out_index = uint32_t(w);
       (grid_big(g) ? gbig : p->gwin).push_back(g);
@@ -276,6 +299,39 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
     c += R + C;
     if (a > 0xFFFFFFFFull || b > 0xFFFFFFFFull || c > 0xFFFFFFFFull) return NSGC_ERR_INVALID_ARG;
     p->win.push_back(d);
+  }
+  // Beside grid windows up to NSGC_GRID_RIDERS of the longer ones join them, to
+  // spare their own launch (windows of 20698 and 7074 packets: 67 us apart, 48
+  // on the grid).
+  if (!p->gwin.empty() || !gbig.empty()) {
+    std::vector<nsgc_small_desc> stay;
+    size_t riders = 0;
+    for (const nsgc_small_desc& s : whole[3]) {
+      nsgc_grid_desc g;
+      if (riders == NSGC_GRID_RIDERS || !grid_window(s.n, tune, tune.cls[ceil_log2(s.n + 1) - 1], &g)) {
+        stay.push_back(s);
+        continue;
+      }
+      ++riders;
+      g.src = at<uint32_t>(uint64_t(s.in_begin) * 4);
+      g.out_index = s.out_index;
+      gpackets += g.n;
+      p->gwin.push_back(g);
+    }
+    whole[3].swap(stay);
+  }
+  // A launch more costs 6 to 10 us: sizes that fit the chip at once in a larger
+  // size's kernel go there (180 windows of 6 .. 524 packets: 25 us in two
+  // launches, 15 in one).
+  for (int k = 0; k < NSGC_WHOLE; ++k) {
+    int next = k + 1;
+    while (next < NSGC_WHOLE && whole[next].empty()) ++next;
+    if (next < NSGC_WHOLE && whole[k].size() + whole[next].size() <= kWholeRound[next]) {
+      whole[next].insert(whole[next].end(), whole[k].begin(), whole[k].end());
+      whole[k].clear();
+    }
+    p->num_whole[k] = uint32_t(whole[k].size());
+    p->small.insert(p->small.end(), whole[k].begin(), whole[k].end());
   }
   // grid windows: tile size, then tiles, cells and phase-C items in order
   p->gtile_log2 = grid_tile_log2(gpackets, gcells, glongest, tune);
@@ -401,33 +457,43 @@ PlanOffsets plan_offsets(size_t ns, size_t nm, size_t nb, size_t nc, size_t nbb 
 }
 }  // namespace
 
-size_t HostPlan::plan_bytes() const {
+constexpr size_t kQueueSet = size_t(NSGC_QCLASSES) * NSGC_QSTRIDE * 4;
+
+size_t HostPlan::queue_bytes() const { return (gwin.empty() ? NSGC_Q_GRID : NSGC_Q_ALL) * kQueueSet; }
+
+size_t HostPlan::upload_bytes() const {
   return plan_offsets(small.size(), win.size(), itemwinB.size(), itemwinC.size(), mapBb.size(),
                       mapBw.size(), ent_cur.size(), gwin.size(), gitemB.size(), gitemC.size()).total;
 }
 
 namespace {
+// Grid windows of a batch of P packets in W windows: by right, and riding along.
+void grid_windows_bound(uint64_t P, uint64_t W, uint64_t* gw, uint64_t* riders) {
+  *gw = std::min<uint64_t>(W, P / NSGC_GRID_MIN);
+  *riders = *gw ? std::min<uint64_t>(std::min<uint64_t>(W, NSGC_GRID_RIDERS), P / NSGC_GRID_RIDE) : 0;
+}
+
 // Most cells of `gw` grid windows of P packets in all: a window of n packets
-// has fewer than 2 n / target + 2, and at most the cap.
-uint64_t grid_cells_bound(uint64_t P, uint64_t gw, const nsgc_tune& t) {
+// has fewer than 2 n / target + 2, and at most the cap; one that rides along 16.
+uint64_t grid_cells_bound(uint64_t P, uint64_t gw, uint64_t riders, const nsgc_tune& t) {
   uint64_t wt = ~uint64_t(0);
   for (int k = 0; k <= 32; ++k)
     if (t.cls[k].wave_target > 0) wt = std::min<uint64_t>(wt, uint64_t(t.cls[k].wave_target));
   if (wt == ~uint64_t(0)) return 0;
   const int cap = std::min(int(t.max_link_buckets_log2), NSGC_GRID_MAX_CELLS_LOG2);
-  return std::min<uint64_t>(P / (2 * wt) + 2 * gw, gw << cap);
+  return std::min<uint64_t>(P / (2 * wt) + 2 * gw, gw << cap) + riders * 16;
 }
 
 // Likewise their phase-C items: R + C < 4 n / target + 4 and at most
 // 2^(strips + sub-buckets) each.
-uint64_t grid_citems_bound(uint64_t P, uint64_t gw, const nsgc_tune& t) {
+uint64_t grid_citems_bound(uint64_t P, uint64_t gw, uint64_t riders, const nsgc_tune& t) {
   uint64_t rt = NSGC_GRID_BUCKET;
   for (int k = 0; k <= 32; ++k)
     rt = std::min<uint64_t>(rt, uint64_t(std::min(t.cls[k].row_target, t.cls[k].col_target)));
   return std::min<uint64_t>(4 * P / rt + 4 * gw,
                             gw * ((uint64_t(1) << (NSGC_GRID_MAX_A + NSGC_GRID_MAX_SUB_LOG2)) +
                                   (uint64_t(1) << (NSGC_GRID_MAX_B + NSGC_GRID_MAX_SUB_LOG2)))) +
-         gw * NSGC_GRID_CITEMS(NSGC_GRID_HEAVY);
+         riders * 8 + (gw + riders) * NSGC_GRID_CITEMS(NSGC_GRID_HEAVY);
 }
 }  // namespace
 
@@ -453,30 +519,33 @@ size_t plan_bound(int64_t max_packets, int64_t max_windows, const nsgc_tune& t) 
     if (t.cls[k].wave_target > 0) wt = std::min<uint64_t>(wt, uint64_t(t.cls[k].wave_target));
   const uint64_t nbw = wt == ~uint64_t(0) ? 0 : std::min<uint64_t>(2 * P / wt + 2 * W, W * capB);
   const uint64_t nb_all = std::max(nb, nbw);
-  const uint64_t gw = std::min<uint64_t>(W, P / NSGC_GRID_MIN);
+  uint64_t gw, riders;
+  grid_windows_bound(P, W, &gw, &riders);
   return plan_offsets(size_t(W), size_t(W), size_t(nb_all), size_t(nc), size_t(nb_all),
-                      size_t(nb_all), 0, size_t(gw), size_t(grid_cells_bound(P, gw, t)),
-                      size_t(grid_citems_bound(P, gw, t))).total + 1024;
+                      size_t(nb_all), 0, size_t(gw + riders), size_t(grid_cells_bound(P, gw, riders, t)),
+                      size_t(grid_citems_bound(P, gw, riders, t))).total +
+         NSGC_Q_ALL * kQueueSet + 1024;
 }
 
 size_t grid_workspace_bound(int64_t max_packets, int64_t max_windows, const nsgc_tune& t) {
   const uint64_t P = uint64_t(std::max<int64_t>(max_packets, 0));
-  const uint64_t gw = std::min<uint64_t>(uint64_t(std::max<int64_t>(max_windows, 1)), P / NSGC_GRID_MIN);
+  uint64_t gw, riders;
+  grid_windows_bound(P, uint64_t(std::max<int64_t>(max_windows, 1)), &gw, &riders);
   if (gw == 0) return 0;
-  const uint64_t cells = grid_cells_bound(P, gw, t);
+  const uint64_t cells = grid_cells_bound(P, gw, riders, t);
   // tile records: windows of up to 1024 cells in tiles of 2^13 packets (or the
   // tuning's, if smaller; smaller still only below 2 * kGridTiles tiles in all),
   // batches with larger ones in tiles of 2^14
   const uint64_t c13 = std::min<uint64_t>(cells, NSGC_GRID_TILE13_CELLS);
   const uint64_t c14 = std::min<uint64_t>(cells, uint64_t(1) << NSGC_GRID_MAX_CELLS_LOG2);
   const uint64_t tile_words =
-      std::max((P >> std::min(t.tile_log2, 13)) * c13, (P >> 14) * c14) + (2 * kGridTiles + gw) * c14;
-  const uint64_t citems = grid_citems_bound(P, gw, t);
+      std::max((P >> std::min(t.tile_log2, 13)) * c13, (P >> 14) * c14) + (2 * kGridTiles + gw + riders) * c14;
+  const uint64_t citems = grid_citems_bound(P, gw, riders, t);
   // a cell record has at most 2 NSGC_GRID_MAX_SUB + 3 words, and per window
   // cells * (R / strips + C / strips + 3) <= cells * 3 + (R + C) * max strips
   const uint64_t rec = std::min<uint64_t>(cells * (2 * NSGC_GRID_MAX_SUB + 3),
                                           cells * 3 + (citems << NSGC_GRID_MAX_B));
-  return size_t((tile_words + rec + gw * NSGC_GRID_HV_WORDS(NSGC_GRID_HEAVY)) * 4 +
+  return size_t((tile_words + rec + (gw + riders) * NSGC_GRID_HV_WORDS(NSGC_GRID_HEAVY)) * 4 +
                 cells * (2 * NSGC_GRID_HEAVY * 8 + 24) + citems * 24 + 9 * 256);
 }
 
@@ -524,6 +593,9 @@ void HostPlan::serialize(void* buf, uint64_t dev_plan, uint64_t dev_ws, const ui
     h.goverW = reinterpret_cast<uint32_t*>(dev_ws + L.goverW);
     h.goverC = reinterpret_cast<uint32_t*>(dev_ws + L.goverC);
   }
+  h.upload16 = uint32_t(upload_bytes() / 16);
+  h.clear16 = uint32_t(queue_bytes() / 16);
+  h.queue = reinterpret_cast<decltype(h.queue)>(dev_plan + upload_bytes());
   h.num_grid = uint32_t(gwin.size());
   h.gitemsA = gitemsA;
   h.gitemsS = gitemsS;
@@ -532,7 +604,8 @@ void HostPlan::serialize(void* buf, uint64_t dev_plan, uint64_t dev_ws, const ui
   h.gtile_log2 = gtile_log2;
   h.itemsBb = itemsBb;
   h.itemsBw = itemsBw;
-  h.num_small = uint32_t(small.size());
+  h.num_small = entity ? uint32_t(small.size()) : 0u;
+  for (int k = 0; k < NSGC_WHOLE; ++k) h.num_whole[k] = num_whole[k];
   h.num_part = uint32_t(win.size());
   h.itemsA = itemsA;
   h.itemsB = itemsB;

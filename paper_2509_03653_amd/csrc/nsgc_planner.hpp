@@ -59,6 +59,7 @@ struct HostPlan {
   uint32_t tile_log2 = 14, link_slots_log2 = 12, rc_slots_log2 = 12, small_slots_log2 = 11;
   uint32_t max_sweeps_log2 = 24;
   uint32_t combine_probes = 0;
+  uint32_t num_whole[NSGC_WHOLE] = {};   // of `small`, unless entity: the windows of nsgc_whole.hip by size
   std::vector<int32_t> tier;   // per window: 0 empty, 1 small, 2 partitioned, 3 large
   // Entity outputs (make_plan with entity = true): per window and list the
   // first and the end row, and the caller's device arrays.
@@ -70,9 +71,11 @@ struct HostPlan {
   void* ent_counts = nullptr;
 
   WsLayout layout() const;
-  size_t plan_bytes() const;
+  size_t upload_bytes() const;   // the plan as serialize() writes it, a multiple of 16
+  size_t queue_bytes() const;    // the counters behind it, which the upload clears
+  size_t plan_bytes() const { return upload_bytes() + queue_bytes(); }
   // Write the device plan (header + arrays) into host memory `buf` (at least
-  // plan_bytes()), with array pointers relative to the device address
+  // upload_bytes()), with array pointers relative to the device address
   // `dev_plan` and workspace pointers relative to `dev_ws`.
   void serialize(void* buf, uint64_t dev_plan, uint64_t dev_ws, const uint32_t* src,
                  const uint32_t* dst, void* out) const;
