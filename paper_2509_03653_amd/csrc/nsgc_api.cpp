@@ -35,8 +35,8 @@ hipError_t launch_heavy(const nsgc_dev_plan* P, uint32_t grid, hipStream_t s);
 size_t lds_heavy_bytes();
 hipError_t launch_order(const nsgc_dev_plan* P, hipStream_t s);
 hipError_t launch_finish(const nsgc_dev_plan* P, uint32_t grid, hipStream_t s);
-hipError_t launch_rowcol_ent(const nsgc_dev_plan* P, uint32_t grid, size_t lds, hipStream_t s);
-size_t lds_rc_ent_bytes(uint32_t slots_log2);
+hipError_t launch_rowcol_ent(const nsgc_dev_plan* P, bool lists, uint32_t grid, size_t lds, hipStream_t s);
+size_t lds_rc_ent_bytes(uint32_t slots_log2, bool lists);
 hipError_t launch_rowcol(const nsgc_dev_plan* P, uint32_t grid, size_t lds, hipStream_t s);
 size_t lds_small_bytes(uint32_t slots_log2);
 size_t lds_part_bytes(uint32_t max_link_buckets, uint32_t tile_log2, uint32_t max_rc_buckets);
@@ -217,11 +217,11 @@ constexpr uint32_t kWaveHist[2] = {64 + 1, NSGC_WAVE_MAX_RC + 1};
 inline int wave_class(uint32_t rc_max) { return rc_max <= 64 ? 0 : 1; }
 
 struct Launch {
-  uint32_t grid_small, grid_part, grid_link, grid_rc, grid_finish, grid_rce;  // persistent grids
+  uint32_t grid_small, grid_part, grid_link, grid_rc, grid_finish, grid_rce[2];  // persistent grids
   uint32_t grid_linkw[2][2];                           // per wave_class, row tables
   uint32_t grid_heavy;
   bool combine;                                        // phase-B emission combines per id
-  size_t lds_small, lds_part, lds_link, lds_rc, lds_rce;
+  size_t lds_small, lds_part, lds_link, lds_rc, lds_rce[2];   // rce: counts, lists
   size_t lds_linkw[2][2];
   uint32_t max_link_buckets, max_rc_buckets;
   // grid windows: heavy sample, partition by tile size (2^11 ..), link
@@ -297,11 +297,13 @@ int launch_params(DevCtx* c, const nsgc_tune& t, Launch* out) {
   L.grid_finish = uint32_t(c->cus) * 4;
   L.grid_heavy = uint32_t(c->cus);   // one workgroup per row-complete window
   // the entity outputs' phase C (two tables per workgroup)
-  L.lds_rce = lds_rc_ent_bytes(uint32_t(std::min(t.rc_slots_log2, 12)));
-  L.grid_rce = 0;
-  if (L.lds_rce <= c->lds_limit &&
-      (rc = resident_cap(c, 6, tile, L.lds_rce, want, &L.grid_rce)) != NSGC_OK)
-    return rc;
+  for (int k = 0; k < 2; ++k) {
+    L.lds_rce[k] = lds_rc_ent_bytes(uint32_t(std::min(t.rc_slots_log2, 12)), k != 0);
+    L.grid_rce[k] = 0;
+    if (L.lds_rce[k] <= c->lds_limit &&
+        (rc = resident_cap(c, k ? 8 : 6, tile, L.lds_rce[k], want, &L.grid_rce[k])) != NSGC_OK)
+      return rc;
+  }
   *out = L;
   return NSGC_OK;
 }
@@ -393,7 +395,8 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
     NSGC_HIP(launch_grid_sweeps(dplan, grid(hp.gitemsC, L.gover), L.lds_grc, s));
   }
   if (part && hp.entity) {
-    NSGC_HIP(launch_rowcol_ent(dplan, grid(hp.itemsC, L.grid_rce), L.lds_rce, s));
+    const int k = hp.ent_links || hp.ent_src || hp.ent_dst ? 1 : 0;
+    NSGC_HIP(launch_rowcol_ent(dplan, k != 0, grid(hp.itemsC, L.grid_rce[k]), L.lds_rce[k], s));
   } else if (part) {
     if (!order_in_b) NSGC_HIP(launch_order(dplan, s));
     NSGC_HIP(launch_rowcol(dplan, grid(hp.itemsC, L.grid_rc), L.lds_rc, s));
@@ -807,7 +810,7 @@ int entities_call(const uint32_t* src, const uint32_t* dst, const int64_t* windo
     hp.ent_dst = lists[2];
   }
   hp.ent_counts = counts;
-  if (!hp.win.empty() && cc.L.grid_rce == 0) return NSGC_ERR_INVALID_ARG;
+  if (!hp.win.empty() && (cc.L.grid_rce[0] == 0 || cc.L.grid_rce[1] == 0)) return NSGC_ERR_INVALID_ARG;
   return run_plan(cc.c, cc.sl, hp, cc.L, src, dst, nullptr, s);
 }
 

@@ -87,24 +87,6 @@ __device__ __forceinline__ bool insert_keys(K* tk, uint32_t mask, const K (&key)
   return failed;
 }
 
-// Second half of a find-or-insert of one key per lane in an open-addressing
-// LDS table (linear probing): `old` is what the compare-and-swap on the home
-// slot returned, `slot` goes in as the home slot and out as the slot last
-// tried.  Returns what that slot held: the table's marker if the key was
-// inserted, the key if it was there, anything else if it found no place.
-// (Plain values, no flags: flags carried through a divergent loop cost scalar
-// instructions per step.)
-template <class K>
-__device__ __forceinline__ K probe_on(K* tk, uint32_t mask, K key, K old, uint32_t& slot) {
-  constexpr K EMPTY = K(~K(0));
-  for (uint32_t left = NSGC_MAX_PROBES - 1; old != EMPTY && old != key && left; --left) {
-    slot = (slot + 1) & mask;
-    if constexpr (sizeof(K) == 8) old = lds_cas64(reinterpret_cast<u64*>(tk) + slot, EMPTY64, key);
-    else old = lds_cas32(reinterpret_cast<uint32_t*>(tk) + slot, EMPTY32, key);
-  }
-  return old;
-}
-
 constexpr uint32_t NO_SLOT = 0xFFFFFFFFu;
 
 // Work queue of phases B and C: like ItemQueue, but the item after the next is

@@ -1889,45 +1889,45 @@ __global__ __launch_bounds__(NSGC_BLOCK) __attribute__((amdgpu_waves_per_eu(6)))
 // ---------------------------------------------------------------------------
 // Phase C for the entity outputs: item b of a window aggregates row bucket b
 // and column bucket b together (in entity mode destinations are hashed like
-// sources and R = C, so both buckets cover the same hashed addresses).  Two
-// LDS tables, one per view, give the bucket totals as in k_rowcol, the rows
-// of the source and destination lists, and the bucket's share of the union
-// |sources U destinations|: its sources plus its destinations that are not
-// also sources.  Overflow sweeps split both views by the same id bits.  The
-// lists are written only by a pass whose sweeps all fit: a single sweep
-// writes as it goes; with more sweeps, a second pass over the final sweeps
-// writes after a first one has found how many are needed.  The column
-// positions of the queue have no work of their own.
+// sources and R = C, so both buckets cover the same hashed addresses) in one
+// LDS table of ids, whose occupied slots are the bucket's share of the union
+// |sources U destinations|.  For the lists (LISTS) a slot has the packets and
+// links of both views, for the counts alone a mark per view.  Overflow sweeps
+// split both views by the same id bits.  The lists are written only by a pass
+// whose sweeps all fit: a single sweep writes as it goes; with more sweeps, a
+// second pass over the final sweeps writes after a first one has found how many
+// are needed.  The column positions of the queue have no work of their own.
+//
+// Bound by the latency of its chain (records, entries, table), so the tables are
+// kept small for more workgroups to hide it: 49 KB for the counts, 82 KB for the
+// lists.  Counts of 64 windows of 2^17 packets: 300 us, against 498 with two
+// tables of both values (98 KB).
 // ---------------------------------------------------------------------------
 
-size_t lds_rc_ent_bytes(uint32_t slots_log2) {
-  const size_t S = size_t(1) << slots_log2;
-  return align16(S * 4) * 6 + 256;
+// Slots (log2) for the counts: twice the lists'.
+constexpr uint32_t ent_slots_log2(uint32_t slots_log2, bool lists) { return slots_log2 + (lists ? 0 : 1); }
+
+// One workgroup of 16 wavefronts fits a compute unit beside the lists' table, two
+// of 8 beside the counts' (by registers).
+constexpr int ent_threads(bool lists) { return lists ? 1024 : 512; }
+
+size_t lds_rc_ent_bytes(uint32_t slots_log2, bool lists) {
+  const size_t S = size_t(1) << ent_slots_log2(slots_log2, lists);
+  return S * (lists ? 20 : 6) + 512;
 }
 
-__global__ __launch_bounds__(NSGC_BLOCK) void k_rowcol_ent(nsgc_dev_plan* P) {
+template <bool LISTS>
+__global__ __launch_bounds__(ent_threads(LISTS)) void k_rowcol_ent(nsgc_dev_plan* P) {
+  constexpr int NT = ent_threads(LISTS);
   extern __shared__ __align__(16) unsigned char smem[];
-  const uint32_t S = 1u << P->rc_slots_log2;
-  unsigned char* p = smem;
-  uint32_t* tkv[2];
-  uint32_t* tav[2];
-  uint32_t* tbv[2];
-  for (int v = 0; v < 2; ++v) {
-    tkv[v] = reinterpret_cast<uint32_t*>(p);  p += align16(S * 4);
-    tav[v] = reinterpret_cast<uint32_t*>(p);  p += align16(S * 4);
-    tbv[v] = reinterpret_cast<uint32_t*>(p);  p += align16(S * 4);
-  }
-  uint32_t* misc = reinterpret_cast<uint32_t*>(p);   // [0] fail flag, [2,3] special row,
-                                                     // [4,5] special column, [7] queue slot
+  const uint32_t S = 1u << ent_slots_log2(P->rc_slots_log2, LISTS);
+  u64* tv = reinterpret_cast<u64*>(smem);                                    // LISTS: [2][S] links << 32 | packets
+  uint32_t* tk = reinterpret_cast<uint32_t*>(smem + (LISTS ? S * 16 : 0));   // [S] ids
+  uint8_t* mark = reinterpret_cast<uint8_t*>(tk + S);                        // else: [2][S]
+  uint32_t* misc = reinterpret_cast<uint32_t*>(smem + S * (LISTS ? 20 : 6));   // 0 failed, 2 / 3 special row's
+                                                        // packets / links, 4 / 5 column's, 7 queue slot
   uint32_t* red = misc + 8;
-
-  for (uint32_t i = threadIdx.x; i < S; i += NSGC_BLOCK) {
-    for (int v = 0; v < 2; ++v) {
-      tkv[v][i] = EMPTY32;
-      tav[v][i] = 0;
-      tbv[v][i] = 0;
-    }
-  }
+  const uint32_t tid = threadIdx.x;
 
   const uint32_t items = P->itemsC;
   ItemQueue q(gptr(&P->queue[NSGC_Q_ROWCOL][0]), misc + 7, NSGC_QCLASSES);
@@ -1946,92 +1946,105 @@ __global__ __launch_bounds__(NSGC_BLOCK) void k_rowcol_ent(nsgc_dev_plan* P) {
     const uint32_t logK = W.logR;
     const NSGC_GLOBAL uint32_t* rec = gptr(P->lbmeta) + W.lbmeta;
 
-    // Table of view v (0 rows, 1 columns) for sweep sw of 2^logS; an insert
-    // gives up after `probes` probes.
+    // View v (0 rows, 1 columns) into the table for sweep sw of 2^logS; an
+    // insert gives up after `probes` probes.
     auto build = [&](int v, uint32_t logS, uint32_t sw, uint32_t probes) {
       const NSGC_GLOBAL uint32_t* st0 = rec + B + (v == 0 ? u64(k) * B : u64(R + 1) * B + u64(k) * B);
       const NSGC_GLOBAL uint32_t* st1 = st0 + B;
       const NSGC_GLOBAL u64* em = gptr(v == 0 ? P->emit_row : P->emit_col) + W.ws;
-      uint32_t* tk = tkv[v];
-      uint32_t* ta = tav[v];
-      uint32_t* tb = tbv[v];
       uint32_t* spc = misc + 2 + 2 * v;
       auto seg = [&](uint32_t lb, u64& base, uint32_t& len) {
         const uint32_t s0 = st0[lb], s1 = st1[lb];
         base = u64(rec[lb]) + s0;
         len = s1 - s0;
       };
-      gather_by_wave<RC_MAXU>(B, seg, [&](const auto& pos, const auto& okin) {
+      gather_by_wave<RC_MAXU, NT / 64>(B, seg, [&](const auto& pos, const auto& okin) {
         constexpr int U = array_len<decltype(pos)>();
-        uint32_t id[U], h[U], pk[U], ln[U];
-        bool ok[U];
+        u64 x[U], add[U];
+        uint32_t old[U], at[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = em[okin[u] ? pos[u] : 0ull];   // position 0 exists; masked below
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const u64 ee = em[okin[u] ? pos[u] : 0ull];   // position 0 exists; masked below
-          const u64 e = okin[u] ? ee : 0ull;
-          id[u] = uint32_t(e >> 32);
-          pk[u] = uint32_t(e) & ENT_PMAX;
-          ln[u] = uint32_t(e) >> NSGC_ENT_PACKET_BITS;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          h[u] = id[u];
+          const uint32_t id = uint32_t(x[u] >> 32), pk = uint32_t(x[u]) & ENT_PMAX;
+          add[u] = (u64(uint32_t(x[u]) >> NSGC_ENT_PACKET_BITS) << 32) | pk;
           // (an entry with no packets is an unused slot of a swept link bucket)
-          ok[u] = okin[u] && pk[u] != 0 && !(logS && next32(h[u], logK, logS) != sw);
-          if (ok[u] && id[u] == EMPTY32) {
-            lds_add(&spc[0], pk[u]);
-            lds_add(&spc[1], ln[u]);
-            ok[u] = false;
+          bool ok = okin[u] && pk != 0 && !(logS && next32(id, logK, logS) != sw);
+          if (ok && id == EMPTY32) {
+            lds_add(&spc[0], pk);
+            lds_add(&spc[1], uint32_t(x[u]) >> NSGC_ENT_PACKET_BITS);
+            ok = false;
           }
+          // Lanes with the first lane's id leave it to that lane: a dominant
+          // address fills whole segments, and LDS takes atomics on one
+          // address one after another.
+          const u64 vm = __ballot(ok);
+          if (vm) {
+            const int f = __ffsll(static_cast<unsigned long long>(vm)) - 1;
+            const bool same = ok && id == readlane(id, f);
+            if (__popcll(__ballot(same)) > 4) {
+              if constexpr (LISTS) {
+                const uint32_t packets = wave_sum(same ? pk : 0u);
+                const uint32_t links = wave_sum(same ? uint32_t(add[u] >> 32) : 0u);
+                if (int(lane_id()) == f) add[u] = (u64(links) << 32) | packets;
+              }
+              ok = ok && (!same || int(lane_id()) == f);
+            }
+          }
+          at[u] = ok ? id & (S - 1) : ~0u;
+          if (ok) old[u] = lds_cas32(&tk[at[u]], EMPTY32, id);
         }
-        int slot[U];
-        bool fresh[U];
-        if (!cas_insert<U>(tk, S - 1, id, h, ok, slot, fresh, probes))
-          lds_store(&misc[0], 1);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          if (slot[u] >= 0) {
-            lds_add(&ta[slot[u]], pk[u]);
-            lds_add(&tb[slot[u]], ln[u]);
+          if (at[u] != ~0u) {
+            const uint32_t id = uint32_t(x[u] >> 32);
+            const uint32_t o = probe_on<uint32_t>(tk, S - 1, id, old[u], at[u], probes);
+            if (o != EMPTY32 && o != id) lds_store(&misc[0], 1);   // (such a sweep is thrown away)
+            else if constexpr (LISTS) lds_add64(&tv[v * S + at[u]], add[u]);
+            else mark[v * S + at[u]] = 1;
           }
         }
-        (void)fresh;
       });
     };
 
-    // One pass over both tables: the totals (when `stats`), the list rows
-    // and the union share (when `write`), and emptying the tables.
-    uint32_t nr = 0, mr = 0, mf = 0, nc = 0, mc = 0, mg = 0, uni = 0;
+    // One pass over the table: the counts (when `stats`), the list rows (when
+    // `write`).
+    uint32_t nr = 0, nc = 0, uni = 0;
     auto harvest = [&](bool stats, bool write) {
-      for (uint32_t i0 = 0; i0 < S; i0 += NSGC_BLOCK) {
-        const uint32_t i = i0 + threadIdx.x;
-        const uint32_t rid = tkv[0][i], cid = tkv[1][i];
-        const bool r = rid != EMPTY32, c = cid != EMPTY32;
-        if (stats) {
-          if (r) { ++nr; mr = max(mr, tav[0][i]); mf = max(mf, tbv[0][i]); }
-          if (c) { ++nc; mc = max(mc, tav[1][i]); mg = max(mg, tbv[1][i]); }
+      for (uint32_t i = tid; i < S; i += NT) {   // (S is a multiple of the workgroup)
+        const uint32_t id = tk[i];
+        u64 r, c;
+        if constexpr (LISTS) {
+          r = tv[i];
+          c = tv[S + i];
+        } else {
+          r = mark[i];
+          c = mark[S + i];
         }
-        if (write) {
-          if (r) ++uni;
-          if (c && !lds_find32(tkv[0], S - 1, cid)) ++uni;
+        if (stats) {
+          uni += id != EMPTY32;
+          nr += r != 0;
+          nc += c != 0;
+        }
+        if (LISTS && write) {
           if (P->ent_src) {
-            const u64 row = ent_reserve(P, w, 1, r);
-            if (r) ent_row(P, P->ent_src, w, 1, row, row_unhash(rid), tav[0][i], tbv[0][i]);
+            const u64 row = ent_reserve(P, w, 1, r != 0);
+            if (r) ent_row(P, P->ent_src, w, 1, row, row_unhash(id), uint32_t(r), r >> 32);
           }
           if (P->ent_dst) {
-            const u64 row = ent_reserve(P, w, 2, c);
-            if (c) ent_row(P, P->ent_dst, w, 2, row, row_unhash(cid), tav[1][i], tbv[1][i]);
+            const u64 row = ent_reserve(P, w, 2, c != 0);
+            if (c) ent_row(P, P->ent_dst, w, 2, row, row_unhash(id), uint32_t(c), c >> 32);
           }
         }
       }
-      if (threadIdx.x == 0) {   // the hashed id EMPTY32 lives outside the tables
+      if (tid == 0) {   // the hashed id EMPTY32 lives outside the table
         if (stats) {
-          if (misc[3]) { ++nr; mr = max(mr, misc[2]); mf = max(mf, misc[3]); }
-          if (misc[5]) { ++nc; mc = max(mc, misc[4]); mg = max(mg, misc[5]); }
+          nr += misc[3] != 0;
+          nc += misc[5] != 0;
+          uni += misc[3] || misc[5];
         }
-        if (write) {
+        if (LISTS && write) {
           const uint32_t xe = row_unhash(EMPTY32);
-          if (misc[3] || misc[5]) ++uni;
           if (misc[3] && P->ent_src) {
             const u64 row = __hip_atomic_fetch_add(P->ent_cur + u64(w) * 3 + 1, 1ull,
                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2044,33 +2057,32 @@ __global__ __launch_bounds__(NSGC_BLOCK) void k_rowcol_ent(nsgc_dev_plan* P) {
           }
         }
       }
-      __syncthreads();   // lookups done before the tables are emptied
-      for (uint32_t i = threadIdx.x; i < S; i += NSGC_BLOCK) {
-        for (int v = 0; v < 2; ++v) {
-          tkv[v][i] = EMPTY32;
-          tav[v][i] = 0;
-          tbv[v][i] = 0;
-        }
-      }
-      __syncthreads();
     };
 
     auto sweep = [&](uint32_t logS, uint32_t sw, uint32_t probes) -> bool {
-      if (threadIdx.x < 6) misc[threadIdx.x] = 0;
+      __syncthreads();   // the table has been read
+      const v4u32 e4 = {EMPTY32, EMPTY32, EMPTY32, EMPTY32}, z4 = {0u, 0u, 0u, 0u};
+      for (uint32_t i = tid; i < S / 4; i += NT) reinterpret_cast<v4u32*>(tk)[i] = e4;
+      if constexpr (LISTS)
+        for (uint32_t i = tid; i < S; i += NT) reinterpret_cast<v4u32*>(tv)[i] = z4;
+      else
+        for (uint32_t i = tid; i < S / 8; i += NT) reinterpret_cast<v4u32*>(mark)[i] = z4;
+      if (tid < 6) misc[tid] = 0;
       __syncthreads();
       build(0, logS, sw, probes);
-      build(1, logS, sw, probes);   // ends with a barrier
+      build(1, logS, sw, probes);
+      __syncthreads();
       return misc[0] == 0;
     };
 
     bool abandoned = false;
     uint32_t logS = 0;
-    for (;; ++logS) {   // the totals, and the lists when a single sweep fits
+    for (;; ++logS) {   // the counts, and the lists when a single sweep fits
       if (logS > P->max_sweeps_log2) { abandoned = true; break; }
-      nr = mr = mf = nc = mc = mg = uni = 0;
+      nr = nc = uni = 0;
       bool failed = false;
       for (uint32_t sw = 0; sw < (1u << logS); ++sw) {
-        if (!sweep(logS, sw, NSGC_MAX_PROBES)) { failed = true; harvest(false, false); break; }
+        if (!sweep(logS, sw, NSGC_MAX_PROBES)) { failed = true; break; }
         harvest(true, logS == 0);
       }
       if (!failed) break;
@@ -2078,20 +2090,18 @@ __global__ __launch_bounds__(NSGC_BLOCK) void k_rowcol_ent(nsgc_dev_plan* P) {
     // The lists over the sweeps now known to fit.  Probe chains depend on the
     // order of concurrent inserts, so a rebuild may probe the whole table: it
     // then always succeeds, as each sweep holds at most S ids.
-    if (!abandoned && logS > 0)
+    if (LISTS && !abandoned && logS > 0)
       for (uint32_t sw = 0; sw < (1u << logS); ++sw) {
         sweep(logS, sw, S);
         harvest(false, true);
       }
-    uint32_t zero = 0;
-    block_sum_max2_to0(nr, mr, mf, red);
+    uint32_t none = 0, zero = 0;
+    block_sum2_max_to0<NT / 64>(nr, nc, none, red);
     __syncthreads();
-    block_sum_max2_to0(nc, mc, mg, red);
-    __syncthreads();
-    block_sum_max2_to0(uni, zero, zero, red);
-    if (threadIdx.x == 0) {
-      const v4u32 pr = {nr, mr, mf, abandoned ? 1u : 0u};
-      const v4u32 pc = {nc, mc, mg, abandoned ? 1u : 0u};
+    block_sum2_max_to0<NT / 64>(uni, zero, none, red);
+    if (tid == 0) {   // (the maxima of the statistics are not asked for)
+      const v4u32 pr = {nr, 0u, 0u, abandoned ? 1u : 0u};
+      const v4u32 pc = {nc, 0u, 0u, abandoned ? 1u : 0u};
       gptr(reinterpret_cast<v4u32*>(P->partC))[it] = pr;
       gptr(reinterpret_cast<v4u32*>(P->partC))[it + R] = pc;
       gptr(P->partU)[it] = uni;
@@ -2278,8 +2288,13 @@ hipError_t launch_heavy(const nsgc_dev_plan* P, uint32_t grid, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_rowcol_ent(const nsgc_dev_plan* P, uint32_t grid, size_t lds, hipStream_t s) {
-  hipLaunchKernelGGL(k_rowcol_ent, dim3(grid), dim3(NSGC_BLOCK), lds, s, const_cast<nsgc_dev_plan*>(P));
+hipError_t launch_rowcol_ent(const nsgc_dev_plan* P, bool lists, uint32_t grid, size_t lds, hipStream_t s) {
+  if (lists)
+    hipLaunchKernelGGL((k_rowcol_ent<true>), dim3(grid), dim3(ent_threads(true)), lds, s,
+                       const_cast<nsgc_dev_plan*>(P));
+  else
+    hipLaunchKernelGGL((k_rowcol_ent<false>), dim3(grid), dim3(ent_threads(false)), lds, s,
+                       const_cast<nsgc_dev_plan*>(P));
   return hipGetLastError();
 }
 
@@ -2318,11 +2333,13 @@ hipError_t resident_blocks(int which, uint32_t tile_log2, size_t lds, int* block
     case 3: f = reinterpret_cast<const void*>(&k_rowcol); break;
     case 5: f = reinterpret_cast<const void*>(&k_links_wave<false>); break;
     case 7: f = reinterpret_cast<const void*>(&k_links_wave<true>); break;
-    case 6: f = reinterpret_cast<const void*>(&k_rowcol_ent); break;
+    case 6: f = reinterpret_cast<const void*>(&k_rowcol_ent<false>); break;
+    case 8: f = reinterpret_cast<const void*>(&k_rowcol_ent<true>); break;
     default: return hipErrorInvalidValue;
   }
   const int threads = which == 1 && tile_log2 == 14 ? NSGC_BLOCK * PART14_SCALE
                       : which == 5 || which == 7    ? WAVE_NT
+                      : which == 8                  ? ent_threads(true)
                                                     : NSGC_BLOCK;
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, threads, lds);
 }
@@ -2333,7 +2350,8 @@ hipError_t allow_large_lds(size_t bytes) {
       reinterpret_cast<const void*>(&k_small),         reinterpret_cast<const void*>(&k_links<false>),
       reinterpret_cast<const void*>(&k_links<true>),   reinterpret_cast<const void*>(&k_links_wave<false>),
       reinterpret_cast<const void*>(&k_links_wave<true>),
-      reinterpret_cast<const void*>(&k_rowcol_ent),    reinterpret_cast<const void*>(&k_heavy),
+      reinterpret_cast<const void*>(&k_rowcol_ent<true>), reinterpret_cast<const void*>(&k_rowcol_ent<false>),
+      reinterpret_cast<const void*>(&k_heavy),
       reinterpret_cast<const void*>(&k_rowcol),        reinterpret_cast<const void*>(&k_partition<4>),
       reinterpret_cast<const void*>(&k_partition<8>),  reinterpret_cast<const void*>(&k_partition<16>),
       reinterpret_cast<const void*>(&k_partition<32 / PART14_SCALE, NSGC_BLOCK * PART14_SCALE>),

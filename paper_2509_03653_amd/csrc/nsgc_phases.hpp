@@ -17,6 +17,26 @@ __host__ __device__ constexpr int array_len() {
 // Probes before an insert of phases B and C gives up; the caller then splits
 // the keys into sweeps, so giving up never changes a result.
 constexpr uint32_t NSGC_MAX_PROBES = 64;
+
+// Second half of a find-or-insert of one key per lane in an open-addressing
+// LDS table (linear probing): `old` is what the compare-and-swap on the home
+// slot returned, `slot` goes in as the home slot and out as the slot last
+// tried.  Returns what that slot held: the table's marker if the key was
+// inserted, the key if it was there, anything else if it found no place within
+// `most` probes.
+// (Plain values, no flags: flags carried through a divergent loop cost scalar
+// instructions per step.)
+template <class K>
+__device__ __forceinline__ K probe_on(K* tk, uint32_t mask, K key, K old, uint32_t& slot,
+                                      uint32_t most = NSGC_MAX_PROBES) {
+  constexpr K EMPTY = K(~K(0));
+  for (uint32_t left = most - 1; old != EMPTY && old != key && left; --left) {
+    slot = (slot + 1) & mask;
+    if constexpr (sizeof(K) == 8) old = lds_cas64(reinterpret_cast<u64*>(tk) + slot, EMPTY64, key);
+    else old = lds_cas32(reinterpret_cast<uint32_t*>(tk) + slot, EMPTY32, key);
+  }
+  return old;
+}
 constexpr uint32_t ENT_PMAX = (1u << NSGC_ENT_PACKET_BITS) - 1;
 constexpr uint32_t ENT_LMAX = (1u << NSGC_ENT_LINK_BITS) - 1;
 static_assert(NSGC_ENT_PACKET_BITS + NSGC_ENT_LINK_BITS == 32, "entry fields");
