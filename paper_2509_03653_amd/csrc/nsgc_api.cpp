@@ -226,7 +226,7 @@ struct Launch {
   uint32_t max_link_buckets, max_rc_buckets;
   // grid windows: heavy sample, partition by tile size (2^11 ..), link
   // aggregation of small / big cells, row/column aggregation
-  uint32_t gheavy, gpart[4], glinks[2], gwhole[NSGC_WHOLE], gwide, gover, grc;
+  uint32_t gheavy, gpart[4], glinks[2], gwhole[NSGC_WHOLE], gwide, gover, grc, gent;
   size_t lds_grc;
 };
 
@@ -292,6 +292,7 @@ int launch_params(DevCtx* c, const nsgc_tune& t, Launch* out) {
   for (int k = 0; k < 2; ++k)
     if ((rc = resident_cap(c, kGridKernels + 1 + k, 0, 0, 16, &L.glinks[k])) != NSGC_OK) return rc;
   if ((rc = resident_cap(c, kGridKernels + 3, 0, L.lds_grc, 16, &L.grc)) != NSGC_OK) return rc;
+  if ((rc = resident_cap(c, kGridKernels + 4, 0, 0, 16, &L.gent)) != NSGC_OK) return rc;
   for (int k = 0; k < NSGC_WHOLE; ++k)
     if ((rc = resident_cap(c, kGridKernels + 8 + k, 0, 0, 16, &L.gwhole[k])) != NSGC_OK) return rc;
   L.grid_finish = uint32_t(c->cus) * 4;
@@ -390,7 +391,9 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
     NSGC_HIP(launch_links(dplan, L.combine && !hp.entity, L.max_rc_buckets,
                           grid(hp.itemsBb, L.grid_link), L.lds_link, s));
   NSGC_HIP(mark(3));
-  if (gsmall || gbig) {
+  if ((gsmall || gbig) && hp.entity) {
+    NSGC_HIP(launch_grid_ent(dplan, grid(hp.gitemsC, L.gent), s));
+  } else if (gsmall || gbig) {
     NSGC_HIP(launch_grid_rowcol(dplan, grid(hp.gitemsC, L.grc), L.lds_grc, s));
     NSGC_HIP(launch_grid_sweeps(dplan, grid(hp.gitemsC, L.gover), L.lds_grc, s));
   }
@@ -796,7 +799,8 @@ int entities_call(const uint32_t* src, const uint32_t* dst, const int64_t* windo
   if ((rc = begin_call(s, &cc, true)) != NSGC_OK) return rc;
   std::lock_guard<std::mutex> lock(cc.sl->mu);
   HostPlan hp;
-  if ((rc = make_plan(window_offsets, num_windows, cc.t, &hp, true)) != NSGC_OK) return rc;
+  // (the grid counts entities; the lists come from the other form)
+  if ((rc = make_plan(window_offsets, num_windows, cc.t, &hp, true, true, !list_off)) != NSGC_OK) return rc;
   hp.ent_cur.assign(size_t(num_windows) * 3, 0);
   hp.ent_end.assign(size_t(num_windows) * 3, 0);
   if (list_off) {

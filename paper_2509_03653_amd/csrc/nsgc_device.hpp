@@ -108,6 +108,25 @@ constexpr uint32_t odd_inverse(uint32_t m) {
 static_assert(0x897EA68Du * odd_inverse(0x897EA68Du) == 1u, "multiplier inverse");
 static_assert(0x3EA9E261u * odd_inverse(0x3EA9E261u) == 1u, "multiplier inverse");
 
+// Destinations hashed like sources (`same`) or by col_hash, with the choice in
+// registers.
+struct ColHash {
+  uint32_t key, m1, m2;
+  __device__ explicit ColHash(bool same)
+      : key(same ? 0x421E9A93u : 0x3F4760C9u),
+        m1(same ? 0x897EA68Du : 0xE8F25BB3u),
+        m2(same ? 0x3EA9E261u : 0xA84F7BAFu) {}
+  __device__ __forceinline__ uint32_t operator()(uint32_t x) const {
+    x ^= key;
+    x ^= x >> 16;
+    x *= m1;
+    x ^= x >> 15;
+    x *= m2;
+    x ^= x >> 16;
+    return x;
+  }
+};
+
 // row_hash^-1: the steps of row_hash undone in reverse order (x ^= x >> 16
 // is its own inverse on 32 bits; x ^= x >> 15 is undone by x ^= x >> 15 ^ x >> 30).
 __device__ __forceinline__ uint32_t row_unhash(uint32_t x) {

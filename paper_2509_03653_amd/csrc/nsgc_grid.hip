@@ -89,6 +89,10 @@ __device__ __forceinline__ bool insert_keys(K* tk, uint32_t mask, const K (&key)
 
 constexpr uint32_t NO_SLOT = 0xFFFFFFFFu;
 
+// Home slot of a link, from low bits that its cell leaves free (shifted, so that
+// links of an address with itself spread where both views hash alike).
+__device__ __forceinline__ uint32_t link_home(u64 k) { return uint32_t(k >> 32) ^ (uint32_t(k) >> 1); }
+
 // Work queue of phases B and C: like ItemQueue, but the item after the next is
 // requested as soon as the next one is announced, so that the answer is in
 // before the item's stores go out (memory operations complete in order: a
@@ -162,6 +166,7 @@ __global__ __launch_bounds__(GH_NT) void k_grid_heavy(const nsgc_dev_plan* __res
   __shared__ uint32_t lost[2][HEAVY_SHIFTS];   // hits of the candidates without an entry
   __shared__ uint32_t ncand[2];
   const uint32_t v = threadIdx.x >= GH_VT ? 1u : 0u;   // view: sources, destinations
+  const ColHash dst_hash(P->entity != 0);
   const uint32_t tid = threadIdx.x & (GH_VT - 1);
   uint32_t* const k = table[v][0];
   uint32_t* const c = table[v][1];
@@ -188,7 +193,7 @@ __global__ __launch_bounds__(GH_NT) void k_grid_heavy(const nsgc_dev_plan* __res
     lds_barrier();
 #pragma unroll
     for (uint32_t u = 0; u < GH_PER; ++u) {
-      const uint32_t id = v ? col_hash(x[u]) : row_hash(x[u]);
+      const uint32_t id = v ? dst_hash(x[u]) : row_hash(x[u]);
       if (id == EMPTY32) continue;   // the tables' marker keeps its own path
       uint32_t sl = id & (GH_TABLE - 1);
       for (;;) {   // ends: the table holds twice the sample
@@ -281,6 +286,7 @@ __global__ __launch_bounds__(NT) void k_grid_partition(const nsgc_dev_plan* __re
   uint8_t* ids = reinterpret_cast<uint8_t*>(idt + 2 * HT);         // [2][HT] their slots
   uint32_t* red = reinterpret_cast<uint32_t*>(ids + 2 * HT);       // [NW]
   const uint32_t tid = threadIdx.x, w = tid >> 6;
+  const ColHash dst_hash(sload(&P->entity) != 0);
   const uint32_t items = P->gitemsA;
   const uint32_t per = (items + gridDim.x - 1) / gridDim.x;
   const uint32_t beg = min(items, blockIdx.x * per), end = min(items, beg + per);
@@ -359,7 +365,7 @@ __global__ __launch_bounds__(NT) void k_grid_partition(const nsgc_dev_plan* __re
     for (int k = 0; k < PER; ++k) {
       if constexpr (!KEYS) {
         r[k] = row_hash(r[k]);
-        c[k] = col_hash(c[k]);
+        c[k] = dst_hash(c[k]);
       }
       const bool hs = idt[heavy_index(r[k], sh)] == r[k], hd = idt[HT + heavy_index(c[k], dh)] == c[k];
       const bool ok = len == T || uint32_t((k >> 2) * NT + tid) * 4 + (k & 3) < len;
@@ -611,7 +617,7 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
   auto col_bin = [&](uint32_t c) { return (c >> (32 - W.logC)) & (csub - 1u); };
   auto row_light = [&](uint32_t r) { return (r >> (32 - a)) == ci; };
   auto col_light = [&](uint32_t c) { return (c >> (32 - b)) == cj; };
-  auto home = [&](u64 k) { return (uint32_t(k >> 32) ^ uint32_t(k)) & uint32_t(SL - 1); };
+  auto home = [&](u64 k) { return link_home(k) & uint32_t(SL - 1); };
   auto add_heavy = [&](uint32_t v, uint32_t id, uint32_t n) {
     lds_add64(&acc[v * HV + (id & (HV - 1))], (u64(1) << 32) | n);
   };
@@ -860,7 +866,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
     bool done = false;
     uint32_t links = 0, mx = 0;
     if (total <= ROOM) {
-      auto home = [&](u64 k) { return (uint32_t(k >> 32) ^ uint32_t(k)) & uint32_t(SL - 1); };
+      auto home = [&](u64 k) { return link_home(k) & uint32_t(SL - 1); };
       NSGC_GLOBAL u64* keys = gptr(W.keys);
       // only the last cell can hold the key that equals the table's marker
       const bool marker = ((W.strip_i + (cell >> W.subB) + 1u) >> W.logA) != 0 &&
@@ -1426,6 +1432,214 @@ __global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void
 }
 
 // ---------------------------------------------------------------------------
+// Phase C for the entity counts (nsgc_window_entity_counts): destinations are
+// hashed like sources and both views have the same buckets, so item k takes row
+// bucket k and column bucket k into one table of ids with a mark per view; its
+// marked slots are the item's share of sources, destinations and their union.
+// The bucket's dominant addresses, which emit no entries, are put in by hand.
+// In sweeps over the ids, streaming the entries, where a bucket has more
+// entries than the threads hold or more ids than the table.  Bound by its chain
+// like k_grid_rowcol; nothing but marks is kept, so the table costs 49 KB.
+// Counts of 64 windows of 2^17 packets 50 us (300 by k_rowcol_ent, whose item
+// reads one segment per link bucket), whole calls 451 -> 186 us; one window of
+// 2000 packets 46 -> 31, so every window above small_max takes the grid.
+// ---------------------------------------------------------------------------
+
+constexpr int GE_NT = 512;
+constexpr int GE_E = 8;
+constexpr uint32_t GE_S = 8192;
+
+__global__ __launch_bounds__(GE_NT) __attribute__((amdgpu_waves_per_eu(6))) void k_grid_ent(nsgc_dev_plan* P) {
+  constexpr int NT = GE_NT, E = GE_E, NW = NT / 64;
+  constexpr uint32_t S = GE_S, ROOM = NT * E;
+  __shared__ __align__(16) uint32_t tk[S];        // ids; before them the positions of a view's entries
+  __shared__ __align__(16) uint8_t mark[2][S];
+  __shared__ uint32_t tab[2 * NT + 2 * NW];
+  __shared__ uint32_t misc[8];   // 0 failed, 1 / 2 the tables' marker seen as source / destination, 6 next item
+  __shared__ uint32_t red[3 * NW];
+  static_assert(S / 16 == NT, "a thread per 16 slots");
+  const uint32_t items = sload(&P->gitemsC), HV = NSGC_GRID_HV(sload(&P->gtile_log2));
+  GridQueue q(gptr(&sload(&P->queue)[NSGC_Q_GRID_C][0]), items);
+  for (uint32_t item = blockIdx.x < items ? blockIdx.x : NO_ITEM; item != NO_ITEM;) {
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // (as in phase B)
+    const uint32_t it = uniform(item);
+    const nsgc_grid_desc W = sload_words(sload(&P->gwin) + sload(sload(&P->gitemC) + it));
+    const uint32_t k = it - W.itemC, H = NSGC_GRID_CITEMS(HV);
+    q.announce(misc + 6, items);
+    v4u32 part = {0u, 0u, 0u, 0u};
+    if (k < H) {
+      if (k == H - 1) {   // links between dominant addresses: packets, links, maximum
+        const NSGC_GLOBAL uint32_t* m = gptr(W.heavy) + 2 * HV;
+        uint32_t n = 0, l = 0, mx = 0;
+        for (uint32_t i = tid; i < HV * HV; i += NT) {
+          const uint32_t x = m[i];
+          n += x;
+          l += x ? 1u : 0u;
+          mx = max(mx, x);
+        }
+        block_sum2_max_to0<NW>(n, l, mx, red);
+        part.x = n;
+        part.y = l;
+        part.z = mx;
+      }
+    } else {
+      const uint32_t bucket = k - H, logK = W.logR;
+      const bool last = bucket + 1u == (1u << logK);   // holds the id that equals the table's marker
+      const NSGC_GLOBAL uint32_t* rec = gptr(W.rec);
+      // segment s of the bucket's entries in view v
+      auto segment = [&](uint32_t v, uint32_t s, uint32_t& base, uint32_t& len) {
+        BucketItem B;
+        const uint32_t low = W.logR - (v ? W.logBc : W.logA);
+        B.row = v == 0;
+        B.strip = bucket >> low;
+        B.sub = bucket & ((1u << low) - 1u);
+        const NSGC_GLOBAL uint32_t* x = rec + bucket_record(W, B, s);
+        const NSGC_GLOBAL uint32_t* y = x + (v ? 2u + (1u << (W.logR - W.logA)) : 1u) + B.sub;
+        base = x[0] + y[0];
+        len = y[1] - y[0];
+      };
+      auto insert = [&](uint32_t v, uint32_t id, uint32_t probes) {
+        if (last && id == EMPTY32) {
+          misc[1 + v] = 1;
+          return;
+        }
+        uint32_t s = id & (S - 1);
+        const uint32_t o = probe_on<uint32_t>(tk, S - 1, id, lds_cas32(&tk[s], EMPTY32, id), s, probes);
+        if (o == EMPTY32 || o == id) mark[v][s] = 1;
+        else misc[0] = 1;
+      };
+      auto clear = [&]() {
+        const v4u32 e4 = {EMPTY32, EMPTY32, EMPTY32, EMPTY32}, z4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (uint32_t i = 0; i < S / 4 / NT; ++i) reinterpret_cast<v4u32*>(tk)[i * NT + tid] = e4;
+#pragma unroll
+        for (uint32_t i = 0; i < S / 8 / NT; ++i) reinterpret_cast<v4u32*>(&mark[0][0])[i * NT + tid] = z4;
+        if (tid < 3) misc[tid] = 0;
+      };
+      uint32_t nr = 0, nc = 0, uni = 0;
+      auto harvest = [&]() {
+        const v4u32 a = reinterpret_cast<const v4u32*>(mark[0])[tid], b = reinterpret_cast<const v4u32*>(mark[1])[tid];
+        nr += __popc(a.x) + __popc(a.y) + __popc(a.z) + __popc(a.w);
+        nc += __popc(b.x) + __popc(b.y) + __popc(b.z) + __popc(b.w);
+        uni += __popc(a.x | b.x) + __popc(a.y | b.y) + __popc(a.z | b.z) + __popc(a.w | b.w);
+        if (tid == 0) {
+          nr += misc[1];
+          nc += misc[2];
+          uni += misc[1] | misc[2];
+        }
+      };
+      // the dominant addresses of the bucket (each occurs in the window), and
+      // those of sweep sw of 2^logS
+      auto dominant = [&](uint32_t logS, uint32_t sw) {
+        if (tid < 2 * HV) {
+          const uint32_t id = gptr(W.heavy)[tid];
+          if (id != EMPTY32 && (id >> (32 - logK)) == bucket && !(logS && next32(id, logK, logS) != sw))
+            insert(tid < HV ? 0u : 1u, id, S);
+        }
+      };
+      bool done = false;
+      u64 e[2][E];
+      uint32_t total[2];
+      auto read = [&](uint32_t v) {   // a view's entries into registers
+        const uint32_t nseg = 1u << (v ? W.logA : W.logBc);
+        const uint32_t s = nseg <= 64 ? tid & 63u : tid;
+        uint32_t base = 0, len = 0, none = 0;
+        if (s < nseg) segment(v, s, base, len);
+        lds_barrier();   // the last list has been read
+        const uint32_t n = nseg <= 64 ? spread_by_wave<NT>(tid, nseg, base, len, none, tk, ROOM)
+                                      : spread_segments<NT>(tid, nseg, base, len, none, tab, tk, ROOM);
+        lds_barrier();
+        const NSGC_GLOBAL u64* em = gptr(v ? W.emit_col : W.emit_row);
+        if (n <= ROOM) {
+#pragma unroll
+          for (int j = 0; j < E; ++j) {
+            const uint32_t x = uint32_t(j * NT) + tid;
+            e[v][j] = 0;
+            if (uint32_t(j * NT) < n) e[v][j] = em[x < n ? tk[x] : 0u];   // masked when it is used
+          }
+        }
+        total[v] = n;
+      };
+      read(0);
+      read(1);
+      if (total[0] <= ROOM && total[1] <= ROOM) {
+        lds_barrier();
+        clear();
+        lds_barrier();
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+          for (int j = 0; j < E; ++j)
+            // (an entry with no packets is an unused slot of a cell that took rounds)
+            if (uint32_t(j * NT) + tid < total[v] && (uint32_t(e[v][j]) & ENT_PMAX) != 0)
+              insert(uint32_t(v), uint32_t(e[v][j] >> 32), NSGC_MAX_PROBES);
+        dominant(0, 0);
+        lds_barrier();
+        done = misc[0] == 0;
+        if (done) harvest();
+      }
+      bool abandoned = false;
+      for (uint32_t logS = 0; !done; ++logS) {
+        if (logS > sload(&P->max_sweeps_log2)) { abandoned = true; break; }
+        nr = nc = uni = 0;
+        bool failed = false;
+        for (uint32_t sw = 0; sw < (1u << logS) && !failed; ++sw) {
+          __syncthreads();
+          clear();
+          __syncthreads();
+          for (uint32_t v = 0; v < 2; ++v) {
+            const NSGC_GLOBAL u64* em = gptr(v ? W.emit_col : W.emit_row);
+            auto seg = [&](uint32_t s, u64& base, uint32_t& len) {
+              uint32_t b;
+              segment(v, s, b, len);
+              base = b;
+            };
+            gather_by_wave<4, NW>(1u << (v ? W.logA : W.logBc), seg, [&](const auto& pos, const auto& okin) {
+              constexpr int U = array_len<decltype(pos)>();
+              u64 x[U];
+#pragma unroll
+              for (int u = 0; u < U; ++u) x[u] = em[okin[u] ? pos[u] : 0ull];
+#pragma unroll
+              for (int u = 0; u < U; ++u) {
+                const uint32_t id = uint32_t(x[u] >> 32);
+                bool ok = okin[u] && (uint32_t(x[u]) & ENT_PMAX) != 0 && !(logS && next32(id, logK, logS) != sw);
+                // one of the lanes with the first valid lane's id
+                const u64 vm = __ballot(ok);
+                if (vm) {
+                  const int f = __ffsll(static_cast<unsigned long long>(vm)) - 1;
+                  ok = ok && (int(lane_id()) == f || id != readlane(id, f));
+                }
+                if (ok) insert(v, id, NSGC_MAX_PROBES);
+              }
+            });
+          }
+          dominant(logS, sw);
+          __syncthreads();
+          failed = misc[0] != 0;
+          if (!failed) harvest();
+        }
+        done = !failed;
+      }
+      uint32_t none = 0, zero = 0;
+      block_sum2_max_to0<NW>(nr, nc, none, red);
+      lds_barrier();
+      block_sum2_max_to0<NW>(uni, zero, none, red);
+      part.x = nr;
+      part.y = nc;
+      part.z = uni;
+      part.w = abandoned ? 1u : 0u;
+    }
+    lds_barrier();
+    item = uniform(misc[6]);
+    loads_arrived();
+    arrived(q.pending);
+    if (tid == 0) gptr(reinterpret_cast<v4u32*>(W.partC))[k] = part;
+    lds_barrier();
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Host-side launchers.
 // ---------------------------------------------------------------------------
 
@@ -1490,6 +1704,11 @@ hipError_t launch_grid_rowcol(const nsgc_dev_plan* P, uint32_t grid, size_t lds,
   return hipGetLastError();
 }
 
+hipError_t launch_grid_ent(const nsgc_dev_plan* P, uint32_t grid, hipStream_t s) {
+  hipLaunchKernelGGL(k_grid_ent, dim3(grid), dim3(GE_NT), 0, s, const_cast<nsgc_dev_plan*>(P));
+  return hipGetLastError();
+}
+
 hipError_t grid_resident_blocks(int which, uint32_t tile_log2, size_t lds, int* blocks) {
   int threads = 0;
   const void* f = nullptr;
@@ -1498,6 +1717,7 @@ hipError_t grid_resident_blocks(int which, uint32_t tile_log2, size_t lds, int* 
     case 1: f = reinterpret_cast<const void*>(links_kernels[0]); threads = GB_NT[0]; break;
     case 2: f = reinterpret_cast<const void*>(links_kernels[1]); threads = GB_NT[1]; break;
     case 3: f = reinterpret_cast<const void*>(&k_grid_rowcol); threads = GC_NT; break;
+    case 4: f = reinterpret_cast<const void*>(&k_grid_ent); threads = GE_NT; break;
     default: break;
   }
   if (!f) return hipErrorInvalidValue;

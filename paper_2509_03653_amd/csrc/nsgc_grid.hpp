@@ -16,7 +16,7 @@ size_t lds_grid_rc_bytes(uint32_t slots_log2);
 
 // Workgroups per compute unit that can be resident.  which: 0 partition (by
 // tile_log2), 1 / 2 link aggregation of small / big cells, 3 row/column
-// aggregation.
+// aggregation, 4 that of the entity counts.
 hipError_t grid_resident_blocks(int which, uint32_t tile_log2, size_t lds, int* blocks);
 hipError_t grid_allow_large_lds(size_t bytes);
 
@@ -30,6 +30,8 @@ hipError_t launch_grid_rounds(const nsgc_dev_plan* P, bool after_wide, uint32_t 
 hipError_t launch_grid_rowcol(const nsgc_dev_plan* P, uint32_t grid, size_t lds, hipStream_t s);
 // k_finish (nsgc_kernels.hip) of a plan of one grid window.
 hipError_t launch_grid_finish(const nsgc_dev_plan* P, hipStream_t s);
+// Instead of the row/column aggregation and its sweeps, for entity counts.
+hipError_t launch_grid_ent(const nsgc_dev_plan* P, uint32_t grid, hipStream_t s);
 hipError_t launch_grid_sweeps(const nsgc_dev_plan* P, uint32_t grid, size_t lds, hipStream_t s);
 
 }  // namespace nsgc

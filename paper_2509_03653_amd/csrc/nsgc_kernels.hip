@@ -1900,7 +1900,7 @@ __global__ __launch_bounds__(NSGC_BLOCK) __attribute__((amdgpu_waves_per_eu(6)))
 //
 // Bound by the latency of its chain (records, entries, table), so the tables are
 // kept small for more workgroups to hide it: 49 KB for the counts, 82 KB for the
-// lists.  Counts of 64 windows of 2^17 packets: 300 us, against 498 with two
+// lists.  (The counts usually come from k_grid_ent.)  Counts of 64 windows of 2^17 packets: 300 us, against 498 with two
 // tables of both values (98 KB).
 // ---------------------------------------------------------------------------
 
@@ -2138,6 +2138,7 @@ __global__ __launch_bounds__(256) void k_finish(nsgc_dev_plan* P) {
       partB = G.partB;
       gh = NSGC_GRID_CITEMS(NSGC_GRID_HV(P->gtile_log2));
       partC = G.partC + 4 * gh;   // (the dominant addresses' items come first)
+      if (P->entity) C = 0;   // (k_grid_ent: sources, destinations and their union per item)
       out_index = G.out_index;
     } else {
       const nsgc_win_desc W = gload(P->win + w);
@@ -2148,6 +2149,7 @@ __global__ __launch_bounds__(256) void k_finish(nsgc_dev_plan* P) {
     }
     const NSGC_GLOBAL v4u32* pb = gptr(reinterpret_cast<const v4u32*>(partB)) + b0;
     const NSGC_GLOBAL v4u32* pc = gptr(reinterpret_cast<const v4u32*>(partC)) + c0;
+    uint32_t uni = 0;
     // every sum is at most the window's packet count, below 2^32
     uint32_t v[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     for (uint32_t i = tid; i < B; i += 256) {
@@ -2168,11 +2170,17 @@ __global__ __launch_bounds__(256) void k_finish(nsgc_dev_plan* P) {
     }
     for (uint32_t i = tid; i < R + C; i += 256) {
       const v4u32 x = pc[i];
+      v[9] |= x.w;
+      if (gridw && P->entity) {
+        v[2] += x.x;
+        v[3] += x.y;
+        uni += x.z;
+        continue;
+      }
       const bool row = i < R;
       v[row ? 2 : 3] += x.x;
       v[row ? 5 : 7] = max(v[row ? 5 : 7], x.y);
       v[row ? 6 : 8] = max(v[row ? 6 : 8], x.z);
-      v[9] |= x.w;
     }
     if (tid < gh) {   // dominant sources, destinations, links between them
       const v4u32 x = (pc - gh)[tid];
@@ -2187,10 +2195,10 @@ __global__ __launch_bounds__(256) void k_finish(nsgc_dev_plan* P) {
         v[row ? 6 : 8] = max(v[row ? 6 : 8], x.z);
       }
     }
-    uint32_t uni = 0;
     if (P->entity) {
       const NSGC_GLOBAL uint32_t* pu = gptr(P->partU) + c0;
-      for (uint32_t i = tid; i < R; i += 256) uni += pu[i];
+      if (!gridw)
+        for (uint32_t i = tid; i < R; i += 256) uni += pu[i];
       uni = wave_sum(uni);
     }
 #pragma unroll

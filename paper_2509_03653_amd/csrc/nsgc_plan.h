@@ -114,6 +114,7 @@
 // buckets), its column-bucket starts.
 #define NSGC_GRID_MIN 8193                     // packets of the smallest grid window
 #define NSGC_GRID_RIDE 4097                    // of the smallest that rides along with larger ones
+#define NSGC_GRID_ENTITY 1025                  // of the smallest for the entity counts
 #define NSGC_GRID_RIDERS 256                   // most windows that ride along
 // Dominant addresses per view, and the sample they are drawn from, in a batch
 // partitioned in tiles of 2^t packets: batches with windows of more than 1024

@@ -46,8 +46,8 @@ constexpr size_t kWholeRound[NSGC_WHOLE] = {6144, 1536, 768, 256};
 // strips each way (with fewer, a dominant address cannot be spread) and as
 // many row strips as row buckets if it can, since a strip of one bucket needs
 // no counting.
-bool grid_window(uint64_t n, const nsgc_tune& tune, const nsgc_tune_class& tc, nsgc_grid_desc* g) {
-  if (tc.wave_target <= 0 || tune.combine_probes > 0 || n < NSGC_GRID_RIDE) return false;
+bool grid_window(uint64_t n, bool entity, const nsgc_tune& tune, const nsgc_tune_class& tc, nsgc_grid_desc* g) {
+  if (tc.wave_target <= 0 || tune.combine_probes > 0 || n < (entity ? NSGC_GRID_ENTITY : NSGC_GRID_RIDE)) return false;
   const bool ride = n < NSGC_GRID_MIN;
   const uint64_t target = 4 * uint64_t(tc.wave_target);
   const int lc = std::min(std::min(ride ? 4 : ceil_log2((n + target - 1) / target),
@@ -62,9 +62,10 @@ bool grid_window(uint64_t n, const nsgc_tune& tune, const nsgc_tune_class& tc, n
   int logR = ride ? 2 : buckets(tc.row_target), logC = ride ? 2 : buckets(tc.col_target);
   const int a = std::min(std::min(logR, NSGC_GRID_MAX_A), lc - 2);
   const int b = std::min(std::min(lc - a, logC), NSGC_GRID_MAX_B);
-  if (a < 2 || b < 2) return false;
+  if (a < 2 || b < 2 || (entity && std::max(a, b) > std::min(a, b) + NSGC_GRID_MAX_SUB_LOG2)) return false;
   logR = std::min(logR, a + NSGC_GRID_MAX_SUB_LOG2);
   logC = std::min(logC, b + NSGC_GRID_MAX_SUB_LOG2);
+  if (entity) logR = logC = std::max(std::min(logR, logC), std::max(a, b));   // merged phase-C items
   std::memset(g, 0, sizeof *g);
   g->n = uint32_t(n);
   g->logA = uint8_t(a);
@@ -77,7 +78,7 @@ bool grid_window(uint64_t n, const nsgc_tune& tune, const nsgc_tune_class& tc, n
   // A phase-C item takes one bucket in windows below 2^19 packets and several
   // neighbours in larger ones, which have fewer links per packet; it splits
   // them again where they do not fit one pass.
-  const int gi = n < (uint64_t(1) << 19) ? 0 : ceil_log2(NSGC_GRID_GROUP / NSGC_GRID_BUCKET);
+  const int gi = entity || n < (uint64_t(1) << 19) ? 0 : ceil_log2(NSGC_GRID_GROUP / NSGC_GRID_BUCKET);
   g->logRi = uint8_t(std::max(logR - gi, a));
   g->logCi = uint8_t(std::max(logC - gi, b));
   return true;
@@ -261,8 +262,9 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
       continue;
     }
     nsgc_grid_desc g;
-    if (allow_grid && !entity && n >= NSGC_GRID_MIN && !(tune.row_complete && d.wave) && d.logR >= 2 &&
-        d.logC >= 2 && grid_window(n, tune, tc, &g)) {
+    if (allow_grid && !(tune.row_complete && d.wave) &&
+        (entity ? capB >= 4 && capRC >= 2 : n >= NSGC_GRID_MIN && d.logR >= 2 && d.logC >= 2) &&
+        grid_window(n, entity, tune, tc, &g)) {
       g.src = at<uint32_t>(uint64_t(offsets[w]) * 4);   // byte offsets until serialize()
       g.out_index = uint32_t(w);
       (grid_big(g) ? gbig : p->gwin).push_back(g);
@@ -308,7 +310,7 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
     size_t riders = 0;
     for (const nsgc_small_desc& s : whole[3]) {
       nsgc_grid_desc g;
-      if (riders == NSGC_GRID_RIDERS || !grid_window(s.n, tune, tune.cls[ceil_log2(s.n + 1) - 1], &g)) {
+      if (riders == NSGC_GRID_RIDERS || !grid_window(s.n, false, tune, tune.cls[ceil_log2(s.n + 1) - 1], &g)) {
         stay.push_back(s);
         continue;
       }
@@ -347,7 +349,7 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
     const uint64_t cells = uint64_t(1) << (g.logA + g.logBc);
     const uint64_t R = uint64_t(1) << g.logR, C = uint64_t(1) << g.logC;
     const uint64_t hv = NSGC_GRID_HV(p->gtile_log2);
-    const uint64_t items = (uint64_t(1) << g.logRi) + (uint64_t(1) << g.logCi) + NSGC_GRID_CITEMS(hv);
+    const uint64_t items = (uint64_t(1) << g.logRi) + (entity ? 0 : uint64_t(1) << g.logCi) + NSGC_GRID_CITEMS(hv);
     g.keys = at<unsigned long long>(uint64_t(p->ws_elems) * 8);
     g.tile = at<uint32_t>(uint64_t(p->gtile_words) * 4);
     g.rec = at<uint32_t>(uint64_t(p->grec_words) * 4);

@@ -146,3 +146,43 @@ def test_large_windows(n, rbits, cbits):
     assert int(nsgc.plan_inspect(off)["tier"][0]) == 3
     say(f"[gpu] large grid {n} {rbits}/{cbits}")
     assert_same(gpu_stats(src, dst, off), oracle.window_stats(src, dst, off), f"large {n} {rbits}/{cbits}")
+
+
+# entity counts on the grid: links of an address with itself, ids that fill one
+# bucket (sweeps) or one cell, dominant addresses in one view or both, the
+# tables' marker
+@pytest.mark.parametrize("n", [1025, 4096, 8193, 50000, 1100000])
+@pytest.mark.parametrize("kind", ["loops", "zipf", "crowded", "dominant", "marker", "distinct"])
+def test_entity_counts(n, kind):
+    import torch
+    rng = np.random.default_rng(n)
+    ids = rng.integers(0, 1 << 32, n, dtype=np.uint64).astype(np.uint32)
+    src, dst = heavy_tailed(rng, n), heavy_tailed(rng, n)
+    if kind == "loops":
+        dst = np.where(rng.random(n) < 0.7, src, dst)
+        src[::3] = ids[::3]
+        dst[::3] = ids[::3]
+    elif kind == "crowded":
+        few = rng.integers(0, 1 << 22, n).astype(np.uint64)   # top ten bits zero, or all ones
+        src, dst = hashed(few, ROW), hashed(np.uint64(0xFFFFFFFF) - rng.permutation(few), ROW)
+    elif kind == "dominant":
+        src = np.where(rng.random(n) < 0.8, ids[rng.integers(0, 40, n)], ids)
+        dst = np.where(rng.random(n) < 0.6, ids[20 + rng.integers(0, 90, n)], rng.permutation(ids))
+    elif kind == "marker":
+        src[::5], dst[::7] = SOURCE_MARKER, SOURCE_MARKER     # (destinations are hashed like sources)
+        dst[1::50] = 0xFFFFFFFF
+    elif kind == "distinct":
+        src, dst = np.arange(n), n // 2 + np.arange(n)
+    src, dst = src.astype(np.uint32), dst.astype(np.uint32)
+    half = n // 2 + 1
+    off = np.array([0, n, n + half], np.int64)
+    src, dst = np.concatenate([src, dst[:half]]), np.concatenate([dst, src[:half]])
+    want = []
+    for a, b in zip(off[:-1], off[1:]):
+        e = oracle.window_entities(src, dst, int(a), int(b))
+        want.append([len(e["link_keys"]), len(e["row_ids"]), len(e["col_ids"]), e["unique_ips"]])
+    say(f"[gpu] entity counts {kind} n={n}")
+    s, d = (torch.from_numpy(x.view(np.int32)).cuda() for x in (src, dst))
+    got = nsgc.window_entity_counts(s, d, off)
+    torch.cuda.synchronize()
+    assert got.cpu().numpy().tolist() == want
