@@ -151,6 +151,7 @@ int get_ctx(DevCtx** out) {
   NSGC_HIP(allow_large_lds(c->lds_limit));
   NSGC_HIP(grid_allow_large_lds(c->lds_limit));
   NSGC_HIP(large_grid_allow_lds(c->lds_limit));
+  NSGC_HIP(anonymize_allow_lds());
   g_devs[dev] = c;
   *out = c;
   return NSGC_OK;
@@ -848,14 +849,12 @@ int nsgc_anonymize(const uint32_t* src, const uint32_t* dst, int64_t num_packets
   CallCtx cc;
   int rc;
   if ((rc = begin_call(s, &cc, false, false)) != NSGC_OK) return rc;
-  DevCtx* c = cc.c;
   Slot* sl = cc.sl;
   std::lock_guard<std::mutex> lock(sl->mu);
   const unsigned long long n = (unsigned long long)num_packets;
   if ((rc = ensure_device(&sl->ws, &sl->ws_cap, anonymize_bytes(n), s)) != NSGC_OK) return rc;
   NSGC_HIP(anonymize(src, dst, n, seed, anon_src, anon_dst,
-                     reinterpret_cast<unsigned long long*>(num_addresses), sl->ws,
-                     uint32_t(c->cus) * 8, s));
+                     reinterpret_cast<unsigned long long*>(num_addresses), sl->ws, s));
   return NSGC_OK;
 }
 

@@ -222,7 +222,7 @@ __global__ void k_lw_counts(u64* out, u64 n, const uint32_t* nl, const uint32_t*
 
 size_t large_window_bytes(u64 n) {
   const size_t words = 16 + 4 * size_t(n + 1) +
-                       std::max(radix_sort_scratch_words(n), 2 * scan_scratch_words(n)) + 256;
+                       std::max(radix_sort_scratch_words(), 2 * scan_scratch_words(n)) + 256;
   return 2 * size_t(n) * 8 + words * 4 + 1024;
 }
 
@@ -246,7 +246,7 @@ hipError_t large_window_stats(const uint32_t* src, const uint32_t* dst, u64 n, v
   hipLaunchKernelGGL(k_lw_keys, dim3(g), dim3(LT), 0, s, src, dst, n, K);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   u64* S = nullptr;
-  if ((e = radix_sort_u64(K, T, n, 0, 64, scratch, grid, s, &S)) != hipSuccess) return e;
+  if ((e = radix_sort_u64(K, T, n, nullptr, 0, 64, scratch, s, &S)) != hipSuccess) return e;
   u64* O = S == K ? T : K;   // free for the column elements
 
   // link runs (A) and source runs (B): flags, then run numbers
@@ -279,7 +279,7 @@ hipError_t large_window_stats(const uint32_t* src, const uint32_t* dst, u64 n, v
   if (links == 0 || links > n) return hipErrorInvalidValue;
   const uint32_t gl = uint32_t(std::min<u64>((u64(links) + LT - 1) / LT, grid));
   u64* C = nullptr;
-  if ((e = radix_sort_u64(O, S, links, 32, 64, scratch, grid, s, &C)) != hipSuccess) return e;
+  if ((e = radix_sort_u64(O, S, links, nullptr, 32, 64, scratch, s, &C)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_lw_colflags, dim3(gl), dim3(LT), 0, s, C, nl2, A, Bv);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = exclusive_scan_u32(A, links, scratch, s)) != hipSuccess) return e;

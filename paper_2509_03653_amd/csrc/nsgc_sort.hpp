@@ -14,8 +14,8 @@ typedef unsigned long long u64;
 
 // u32 words of scratch an exclusive scan of n elements needs.
 size_t scan_scratch_words(u64 n);
-// u32 words of scratch radix_sort_u64 needs for n keys.
-size_t radix_sort_scratch_words(u64 n);
+// u32 words of scratch radix_sort_u64 needs.
+size_t radix_sort_scratch_words();
 
 // In-place exclusive prefix sum of a[0..n) (the total must fit 32 bits);
 // bsum holds scan_scratch_words(n) words, and afterwards the total at
@@ -25,10 +25,10 @@ uint32_t* scan_total(uint32_t* bsum, u64 n);
 
 // Stable sort of keys[0..n) by bits [lo, hi), ping-ponging with tmp (n keys);
 // *sorted is set to the buffer that holds the result (keys or tmp).  scratch
-// holds radix_sort_scratch_words(n) words; grid caps the workgroups of the
-// tile kernels.  Asynchronous on s.
-hipError_t radix_sort_u64(u64* keys, u64* tmp, u64 n, uint32_t lo, uint32_t hi, uint32_t* scratch,
-                          uint32_t grid, hipStream_t s, u64** sorted);
+// holds radix_sort_scratch_words() words.  If ndev is not null, the number of
+// keys is *ndev (device, at most n) when the kernels run.  Asynchronous on s.
+hipError_t radix_sort_u64(u64* keys, u64* tmp, u64 n, const uint32_t* ndev, uint32_t lo, uint32_t hi,
+                          uint32_t* scratch, hipStream_t s, u64** sorted);
 
 }  // namespace nsgc
 
