@@ -46,11 +46,12 @@ constexpr size_t kWholeRound[NSGC_WHOLE] = {6144, 1536, 768, 256};
 // strips each way (with fewer, a dominant address cannot be spread) and as
 // many row strips as row buckets if it can, since a strip of one bucket needs
 // no counting.
-bool grid_window(uint64_t n, bool entity, const nsgc_tune& tune, const nsgc_tune_class& tc, nsgc_grid_desc* g) {
+bool grid_window(uint64_t n, bool entity, int finer, const nsgc_tune& tune, const nsgc_tune_class& tc,
+                 nsgc_grid_desc* g) {
   if (tc.wave_target <= 0 || tune.combine_probes > 0 || n < (entity ? NSGC_GRID_ENTITY : NSGC_GRID_RIDE)) return false;
   const bool ride = n < NSGC_GRID_MIN;
   const uint64_t target = 4 * uint64_t(tc.wave_target);
-  const int lc = std::min(std::min(ride ? 4 : ceil_log2((n + target - 1) / target),
+  const int lc = std::min(std::min(ride ? 4 : ceil_log2((n + target - 1) / target) + finer,
                                    int(tune.max_link_buckets_log2)), NSGC_GRID_MAX_CELLS_LOG2);
   // Row and column buckets of at most NSGC_GRID_BUCKET packets: phase C takes
   // one and a half times as many entries in a single pass, and a bucket has at
@@ -83,6 +84,13 @@ bool grid_window(uint64_t n, bool entity, const nsgc_tune& tune, const nsgc_tune
   g->logCi = uint8_t(std::max(logC - gi, b));
   return true;
 }
+
+// A batch of fewer packets leaves compute units idle with full cells, and each
+// cell is a serial chain: it takes up to four times as many.  (One window of
+// 2^17 packets: 45 us with 128 cells, 38 with 512, 48 with 1024; of 2^18 49, 43
+// with 512 and 51 with 1024; eight windows of 2^17 do not care.)
+constexpr uint64_t kFinerPackets = uint64_t(512) << 10;
+constexpr int kFinerMost = 2;
 
 // Cells of more than 1280 packets on average take the kernel with 4096-slot
 // tables (a 2048-slot one would be more than half full).
@@ -216,6 +224,9 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
 
   const uint64_t tile = uint64_t(1) << tune.tile_log2;
   uint64_t a = 0, b = 0, c = 0;
+  const uint64_t packets = num_windows > 0 ? uint64_t(offsets[num_windows] - offsets[0]) : 0;
+  int finer = 0;
+  while (finer < kFinerMost && (packets << finer) < kFinerPackets) ++finer;
   for (int64_t w = 0; w < num_windows; ++w) {
     const uint64_t n = uint64_t(offsets[w + 1] - offsets[w]);
     if (n <= uint64_t(tune.small_max)) {
@@ -264,7 +275,7 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
     nsgc_grid_desc g;
     if (allow_grid && !(tune.row_complete && d.wave) &&
         (entity ? capB >= 4 && capRC >= 2 : n >= NSGC_GRID_MIN && d.logR >= 2 && d.logC >= 2) &&
-        grid_window(n, entity, tune, tc, &g)) {
+        grid_window(n, entity, finer, tune, tc, &g)) {
       g.src = at<uint32_t>(uint64_t(offsets[w]) * 4);   // byte offsets until serialize()
       g.out_index = uint32_t(w);
       (grid_big(g) ? gbig : p->gwin).push_back(g);
@@ -310,7 +321,7 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
     size_t riders = 0;
     for (const nsgc_small_desc& s : whole[3]) {
       nsgc_grid_desc g;
-      if (riders == NSGC_GRID_RIDERS || !grid_window(s.n, false, tune, tune.cls[ceil_log2(s.n + 1) - 1], &g)) {
+      if (riders == NSGC_GRID_RIDERS || !grid_window(s.n, false, 0, tune, tune.cls[ceil_log2(s.n + 1) - 1], &g)) {
         stay.push_back(s);
         continue;
       }
@@ -476,14 +487,15 @@ void grid_windows_bound(uint64_t P, uint64_t W, uint64_t* gw, uint64_t* riders) 
 }
 
 // Most cells of `gw` grid windows of P packets in all: a window of n packets
-// has fewer than 2 n / target + 2, and at most the cap; one that rides along 16.
+// has fewer than 2 n / target + 2, and at most the cap; one that rides along 16;
+// and a batch below kFinerPackets a few thousand more.
 uint64_t grid_cells_bound(uint64_t P, uint64_t gw, uint64_t riders, const nsgc_tune& t) {
   uint64_t wt = ~uint64_t(0);
   for (int k = 0; k <= 32; ++k)
     if (t.cls[k].wave_target > 0) wt = std::min<uint64_t>(wt, uint64_t(t.cls[k].wave_target));
   if (wt == ~uint64_t(0)) return 0;
   const int cap = std::min(int(t.max_link_buckets_log2), NSGC_GRID_MAX_CELLS_LOG2);
-  return std::min<uint64_t>(P / (2 * wt) + 2 * gw, gw << cap) + riders * 16;
+  return std::min<uint64_t>(P / (2 * wt) + 2 * gw, gw << cap) + riders * 16 + 6 * (kFinerPackets >> 10);
 }
 
 // Likewise their phase-C items: R + C < 4 n / target + 4 and at most
