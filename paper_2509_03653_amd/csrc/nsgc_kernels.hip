@@ -102,6 +102,16 @@ __device__ __forceinline__ u64 ent_reserve(const nsgc_dev_plan* P, uint32_t w, i
   return b + rank_below(m);
 }
 
+// The same for `rows` rows of the whole wavefront: the first one.  (Device-wide
+// atomics on one counter take tens of ns each, one after another.)
+__device__ __forceinline__ u64 ent_reserve_rows(const nsgc_dev_plan* P, uint32_t w, int which, uint32_t rows) {
+  u64 base = 0;
+  if (lane_id() == 0 && rows)
+    base = __hip_atomic_fetch_add(P->ent_cur + u64(w) * 3 + which, u64(rows), __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+  return (u64(readlane(uint32_t(base >> 32), 0)) << 32) | readlane(uint32_t(base), 0);
+}
+
 __device__ __forceinline__ void ent_row(const nsgc_dev_plan* P, long long* list, uint32_t w,
                                         int which, u64 row, u64 a, u64 b, u64 c) {
   if (row < P->ent_end[u64(w) * 3 + which]) {
@@ -1506,6 +1516,7 @@ __global__ __launch_bounds__(WAVE_NT) void k_links_wave(nsgc_dev_plan* P, uint32
     auto emit = [&]() {
       NSGC_GLOBAL u64* er = gptr(P->emit_row) + W.ws + below;
       NSGC_GLOBAL u64* ec = gptr(P->emit_col) + W.ws + below;
+      const u64 link0 = P->ent_links ? ent_reserve_rows(P, W.out_index, 0, n) : 0ull;
       for (uint32_t i = lane; i < n; i += 64) {
         const uint32_t s = occ[i];
         const u64 key = tk[s];
@@ -1519,11 +1530,9 @@ __global__ __launch_bounds__(WAVE_NT) void k_links_wave(nsgc_dev_plan* P, uint32
         }
         const uint32_t ac = lds_add(&histC[top32(uint32_t(key), W.logC)], parts);
         write_entry(ec, ac, uint32_t(key), cnt, 1, parts);
-        if (P->ent_links) {   // entity outputs: the links themselves
-          const u64 row = ent_reserve(P, W.out_index, 0, true);
-          ent_row(P, P->ent_links, W.out_index, 0, row, row_unhash(uint32_t(key >> 32)),
+        if (P->ent_links)   // entity outputs: the links themselves
+          ent_row(P, P->ent_links, W.out_index, 0, link0 + i, row_unhash(uint32_t(key >> 32)),
                   row_unhash(uint32_t(key)), cnt);
-        }
       }
       if (lane == 0 && special) {
         if (P->ent_links) {
@@ -2011,29 +2020,52 @@ __global__ __launch_bounds__(ent_threads(LISTS)) void k_rowcol_ent(nsgc_dev_plan
     // `write`).
     uint32_t nr = 0, nc = 0, uni = 0;
     auto harvest = [&](bool stats, bool write) {
-      for (uint32_t i = tid; i < S; i += NT) {   // (S is a multiple of the workgroup)
-        const uint32_t id = tk[i];
-        u64 r, c;
+      uint32_t rows = 0, cols = 0, both = 0;   // this thread's
+      for (uint32_t i = tid; i < S; i += NT) {
+        both += tk[i] != EMPTY32;
         if constexpr (LISTS) {
-          r = tv[i];
-          c = tv[S + i];
+          rows += tv[i] != 0;
+          cols += tv[S + i] != 0;
         } else {
-          r = mark[i];
-          c = mark[S + i];
+          rows += mark[i];
+          cols += mark[S + i];
         }
-        if (stats) {
-          uni += id != EMPTY32;
-          nr += r != 0;
-          nc += c != 0;
-        }
-        if (LISTS && write) {
-          if (P->ent_src) {
-            const u64 row = ent_reserve(P, w, 1, r != 0);
-            if (r) ent_row(P, P->ent_src, w, 1, row, row_unhash(id), uint32_t(r), r >> 32);
+      }
+      if (stats) {
+        uni += both;
+        nr += rows;
+        nc += cols;
+      }
+      if constexpr (LISTS) {
+        if (write) {   // rows for the whole workgroup with one atomic per list
+          const uint32_t ir = wave_inclusive_scan(rows), ic = wave_inclusive_scan(cols), wv = tid >> 6;
+          u64* const first = reinterpret_cast<u64*>(red + 48);
+          if (lane_id() == 63) {
+            red[wv] = ir;
+            red[16 + wv] = ic;
           }
-          if (P->ent_dst) {
-            const u64 row = ent_reserve(P, w, 2, c != 0);
-            if (c) ent_row(P, P->ent_dst, w, 2, row, row_unhash(id), uint32_t(c), c >> 32);
+          __syncthreads();
+          uint32_t br = ir - rows, bc = ic - cols, tr = 0, tc = 0;
+          for (uint32_t k = 0; k < NT / 64; ++k) {
+            if (k < wv) {
+              br += red[k];
+              bc += red[16 + k];
+            }
+            tr += red[k];
+            tc += red[16 + k];
+          }
+          if (tid < 2)
+            first[tid] = __hip_atomic_fetch_add(P->ent_cur + u64(w) * 3 + 1 + tid, u64(tid ? tc : tr),
+                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __syncthreads();
+          u64 row = first[0] + br, col = first[1] + bc;
+          for (uint32_t i = tid; i < S; i += NT) {
+            const u64 r = tv[i], c = tv[S + i];
+            const uint32_t a = row_unhash(tk[i]);
+            if (r && P->ent_src) ent_row(P, P->ent_src, w, 1, row, a, uint32_t(r), r >> 32);
+            if (c && P->ent_dst) ent_row(P, P->ent_dst, w, 2, col, a, uint32_t(c), c >> 32);
+            row += r != 0;
+            col += c != 0;
           }
         }
       }
