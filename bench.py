@@ -313,7 +313,7 @@ def single_large_leg(nsgc, torch, seed, steps=3):
     nsgc.release()
     return {"workload": "1 window x 2^30 packets, 10% from one super-source, 1% to one "
                         "super-destination, rest Zipf(1.3) over 2^26 addresses",
-            "packets": n, "tier": "large (radix sort)", "ms_per_call": ms,
+            "packets": n, "tier": "large", "ms_per_call": ms,
             "packets_per_s": n / (ms * 1e-3), "phase_ms": ph,
             "algorithmic_frac": 8 * n / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
             "stats": [int(x) for x in a]}
