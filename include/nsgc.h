@@ -153,7 +153,8 @@ int nsgc_window_stats_timed(const uint32_t* src, const uint32_t* dst,
  * it reads).  Overlapping calls would race on it, so the library serialises
  * them: a call on another stream than the previous call waits on the device
  * for that call to finish.  Calls on different streams therefore never run
- * concurrently in this form.  Not usable under stream capture
+ * concurrently in this form (except calls of a few short windows, which use
+ * none of the array).  Not usable under stream capture
  * (NSGC_ERR_CAPTURING).
  */
 #define NSGC_NOALLOC_SCRATCH_BYTES (128ull << 20)
