@@ -33,6 +33,7 @@
 
 #include "nsgc_anon.hpp"
 #include "nsgc_device.hpp"
+#include "nsgc_ranges.hpp"
 #include "nsgc_sort.hpp"
 
 namespace nsgc {
@@ -133,15 +134,9 @@ __global__ __launch_bounds__(NT) void k_an_tiles(const uint32_t* __restrict__ sr
   }
 }
 
-// The sorted list in ranges of whole steps of 64 elements per wavefront.
-struct Range {
-  uint32_t beg, end;
-  __device__ explicit Range(uint32_t m) {
-    const uint32_t steps = (m + VT - 1) / VT, per = (steps + gridDim.x - 1) / gridDim.x;
-    beg = uint32_t(min(u64(m), u64(blockIdx.x) * per * VT));
-    end = uint32_t(min(u64(m), u64(beg) + u64(per) * VT));
-  }
-};
+// This workgroup's part of the sorted list (up to 2^32 - 2 elements), in whole
+// steps of 64 elements per wavefront.
+__device__ __forceinline__ ListRange my_range(uint32_t m) { return list_range(m, VT, gridDim.x, blockIdx.x); }
 
 // Whether element i of the sorted list starts a run of equal addresses.
 __device__ __forceinline__ bool run_start(const u64* s, uint32_t i) {
@@ -151,10 +146,10 @@ __device__ __forceinline__ bool run_start(const u64* s, uint32_t i) {
 __global__ __launch_bounds__(VT) void k_an_starts(const u64* __restrict__ s, const uint32_t* __restrict__ total,
                                                   uint32_t* __restrict__ starts) {
   __shared__ uint32_t red[VT / 64];
-  const Range R(*total);
+  const ListRange R = my_range(*total);
   uint32_t c = 0;
 #pragma unroll 4
-  for (u64 i = u64(R.beg) + threadIdx.x; i < R.end; i += VT) c += run_start(s, uint32_t(i));
+  for (u64 i = R.beg + threadIdx.x; i < R.end; i += VT) c += run_start(s, uint32_t(i));
   c = block_sum(c, red);
   if (threadIdx.x == 0) starts[blockIdx.x] = c;
 }
@@ -204,7 +199,7 @@ __global__ __launch_bounds__(VT) void k_an_values(const u64* __restrict__ s, con
   }
   uint32_t h = 1;                       // b = 2h: the smallest even b with 2^b >= max(N, 4)
   while ((u64(1) << (2 * h)) < N) ++h;
-  const Range R(*total);
+  const ListRange R = my_range(*total);
   for (u64 i0 = R.beg; i0 < R.end; i0 += VU * VT) {
     u64 x[VU], m[VU];
     bool in[VU], start[VU];

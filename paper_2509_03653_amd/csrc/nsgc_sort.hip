@@ -25,6 +25,7 @@
 #include <utility>
 
 #include "nsgc_device.hpp"
+#include "nsgc_ranges.hpp"
 #include "nsgc_sort.hpp"
 
 namespace nsgc {
@@ -44,21 +45,15 @@ __device__ __forceinline__ uint32_t digit_of(u64 k, uint32_t shift, uint32_t mas
 
 // Keys, and the range of this workgroup: whole tiles, the same for every
 // kernel of a pass.
-struct Range {
-  u64 beg, end;
-  __device__ Range(u64 n, const uint32_t* ndev, uint32_t chunk) {
-    if (ndev) n = *ndev;
-    const u64 tiles = (n + chunk - 1) / chunk, per = (tiles + gridDim.x - 1) / gridDim.x;
-    beg = min(n, u64(blockIdx.x) * per * chunk);
-    end = min(n, beg + per * chunk);
-  }
-};
+__device__ __forceinline__ ListRange my_range(u64 n, const uint32_t* ndev, uint32_t chunk) {
+  return list_range(ndev ? *ndev : n, chunk, gridDim.x, blockIdx.x);
+}
 
 __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const u64* __restrict__ keys, u64 n,
                                                         const uint32_t* ndev, uint32_t chunk, uint32_t shift,
                                                         uint32_t bits, uint32_t* __restrict__ counts) {
   __shared__ uint32_t hist[RS_WAVES][256];
-  const Range R(n, ndev, chunk);
+  const ListRange R = my_range(n, ndev, chunk);
   const uint32_t mask = (1u << bits) - 1u, tid = threadIdx.x;
   for (uint32_t i = tid; i < RS_WAVES * 256; i += RS_THREADS) (&hist[0][0])[i] = 0;
   __syncthreads();
@@ -182,7 +177,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const u64* __restrict
   __shared__ uint32_t cnt[RS_WAVES][256];
   __shared__ uint32_t to[256];      // output position of the digit's next key, less its place in the tile
   __shared__ uint32_t red[4];
-  const Range R(n, ndev, CHUNK);
+  const ListRange R = my_range(n, ndev, CHUNK);
   const uint32_t mask = (1u << bits) - 1u, tid = threadIdx.x, w = tid >> 6, lane = lane_id();
   uint32_t pos = 0;                 // of digit `tid`: the range's next position
   if (tid < 256) {
