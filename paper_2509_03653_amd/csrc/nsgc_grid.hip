@@ -562,11 +562,135 @@ __device__ __forceinline__ void publish_starts(NSGC_GLOBAL uint32_t* rec, const 
 
 // ---------------------------------------------------------------------------
 // The cells that are too large for the single passes (more keys than their
-// threads hold, or more links than their tables take), by rounds.
+// threads hold, or more links than their tables take), a workgroup each.
+//
+// By rounds: each fills the table with as many links as it takes, which are
+// counted, emitted and overwritten with the marker, so that the next round sees
+// only the others.  A round reads the cell's keys twice, so a cell of k links
+// costs k / GR_FULL readings: the cells that are left over in ordinary traffic
+// have a few thousand links to a few tens of thousands.  A cell of more than
+// GR_KEYS keys, or whose table was full after less than one key in GR_ROUNDS, is
+// sorted instead: eight passes over its keys whatever they are (cells are chosen
+// by the top bits of the hashed addresses, so traffic can be made that puts a
+// whole window in one).
 // ---------------------------------------------------------------------------
 
 constexpr int GR_NT = 512;
 constexpr int GR_SL = 4096;
+constexpr uint32_t GR_FULL = GR_SL * 3 / 4;   // links in the table when no more are taken
+constexpr uint32_t GR_ROUNDS = 12;
+constexpr uint32_t GR_KEYS = 1u << 16;
+
+// The n keys that `each` visits (in any order) into `a` in ascending order, by way of `b`: a radix sort by bytes.
+// `lds` is scratch of 4096 words.  Ends with a barrier.
+template <int NT, class Each>
+__device__ __forceinline__ void sort_cell(uint32_t n, NSGC_GLOBAL u64* a, NSGC_GLOBAL u64* b, uint32_t* lds,
+                                          const Each& each) {
+  constexpr uint32_t NW = NT / 64, R = 8, TILE = NT * R;
+  static_assert(NW == 8, "a wavefront per digit scans its counts");
+  uint32_t* const hist = lds;          // [8][256] of each digit: counts, then the next position
+  uint32_t* const cnt = lds + 2048;    // [NW][256]
+  const uint32_t tid = threadIdx.x, w = tid >> 6, lane = lane_id();
+  auto digit = [](u64 k, uint32_t d) { return uint32_t(k >> (8 * d)) & 255u; };
+  __syncthreads();
+  for (uint32_t i = tid; i < 2048; i += NT) hist[i] = 0;
+  __syncthreads();
+  each([&](u64 k) {
+#pragma unroll
+    for (uint32_t d = 0; d < 8; ++d) lds_add(&hist[d * 256 + digit(k, d)], 1);
+  });
+  __syncthreads();
+  {
+    uint32_t x[4], s = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      x[k] = s;
+      s += hist[w * 256 + lane * 4 + k];
+    }
+    const uint32_t before = wave_inclusive_scan(s) - s;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) hist[w * 256 + lane * 4 + k] = before + x[k];
+  }
+  __syncthreads();
+  each([&](u64 k) { b[lds_add(&hist[digit(k, 0)], 1)] = k; });   // (any order within a digit)
+  __syncthreads();
+  for (uint32_t d = 1; d < 8; ++d) {
+    const NSGC_GLOBAL u64* in = d & 1u ? b : a;
+    NSGC_GLOBAL u64* out = d & 1u ? a : b;
+    uint32_t pos = hist[d * 256 + (tid & 255u)];   // of digit `tid`, as it runs through the tiles
+    for (uint32_t base = 0; base < n; base += min(TILE, n - base)) {
+      for (uint32_t i = lane; i < 256; i += 64) cnt[w * 256 + i] = 0;
+      const uint32_t len = min(TILE, n - base), w0 = w * (R * 64) + lane;
+      u64 key[R];
+      uint32_t rk[R];
+#pragma unroll
+      for (uint32_t r = 0; r < R; ++r) key[r] = w0 + r * 64 < len ? in[base + w0 + r * 64] : 0ull;
+#pragma unroll
+      for (uint32_t r = 0; r < R; ++r) {   // rank among the wavefront's keys with this digit, in order
+        const bool ok = w0 + r * 64 < len;
+        const uint32_t x = digit(key[r], d);
+        u64 m = __ballot(ok);
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) {
+          const u64 mb = __ballot((x >> k) & 1u);
+          m &= ((x >> k) & 1u) ? mb : ~mb;
+        }
+        const uint32_t leader = ok ? uint32_t(__ffsll(static_cast<unsigned long long>(m)) - 1) : 0u;
+        uint32_t old = 0;
+        if (ok && lane == leader) old = lds_add(&cnt[w * 256 + x], uint32_t(__popcll(m)));
+        rk[r] = lane_take(old, leader) + rank_below(m);
+      }
+      __syncthreads();
+      if (tid < 256) {
+#pragma unroll
+        for (uint32_t k = 0; k < NW; ++k) {
+          const uint32_t c = cnt[k * 256 + tid];
+          cnt[k * 256 + tid] = pos;
+          pos += c;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (uint32_t r = 0; r < R; ++r)
+        if (w0 + r * 64 < len) out[cnt[w * 256 + digit(key[r], d)] + rk[r]] = key[r];
+      __syncthreads();
+    }
+  }
+}
+
+// Visits the runs of equal keys of the sorted a[0 .. n), n >= 1: fn(key, length),
+// by the thread that meets a run's last key.  When it is called, every thread has
+// read all keys up to that one (and those of later runs up to the end of its 512
+// are in registers), so it may write where they were.  `lds` is scratch of 2 * NT
+// / 64 words.  Begins and ends with a barrier.
+template <int NT, class Fn>
+__device__ __forceinline__ void sorted_runs(uint32_t n, const NSGC_GLOBAL u64* a, uint32_t* lds, const Fn& fn) {
+  constexpr uint32_t NW = NT / 64;
+  const uint32_t tid = threadIdx.x, w = tid >> 6, lane = lane_id();
+  uint32_t carry = 0, side = 0;   // start of the run that the next keys belong to
+  __syncthreads();
+  for (uint32_t base = 0; base < n; base += min(uint32_t(NT), n - base)) {
+    const uint32_t left = n - base, i = min(tid, left - 1u);
+    const u64 key = a[base + i], next = a[base + min(i + 1u, left - 1u)];
+    const bool end = tid < left && (tid + 1u == left || next != key);
+    const u64 m = __ballot(end);
+    uint32_t* const after = lds + side * NW;   // key after the wavefront's last run, 0 if none ends in it
+    if (lane == 0) after[w] = m ? base + w * 64 + 64u - uint32_t(__clzll(static_cast<long long>(m))) : 0u;
+    __syncthreads();
+    uint32_t start = carry;
+#pragma unroll
+    for (uint32_t k = 0; k < NW; ++k) {
+      const uint32_t x = after[k];
+      if (k < w) start = max(start, x);
+      carry = max(carry, x);
+    }
+    const u64 mine = m & ((u64(1) << lane) - 1u);
+    if (mine) start = base + w * 64 + 64u - uint32_t(__clzll(static_cast<long long>(mine)));
+    if (end) fn(key, base + tid + 1u - start);
+    side ^= 1u;
+  }
+  __syncthreads();
+}
 
 __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_t after_wide) {
   constexpr int NT = GR_NT, SL = GR_SL, NW = NT / 64;
@@ -575,6 +699,7 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
   __shared__ u64 acc[2 * HVM];
   __shared__ uint32_t bin[2 * NSGC_GRID_MAX_SUB];   // rows, columns
   __shared__ uint32_t misc[4];   // 0 failed, 1 special packets, 2 links, 3 max packets
+  __shared__ uint32_t fill[3];   // of a round: links in the table, keys read by then, keys left over
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t items = P->gover[after_wide ? 2 : 0];
   for (uint32_t x = blockIdx.x; x < items; x += gridDim.x) {
@@ -622,14 +747,27 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
     lds_add64(&acc[v * HV + (id & (HV - 1))], (u64(1) << 32) | n);
   };
   auto clear_table = [&]() { clear_cell_table<NT, SL, SL>(tid, tk, tc, bin, misc); };
-  auto starts = [&](uint32_t& xr, uint32_t& xc) { publish_starts(rec, bin, rsub, csub, W.base + below, xr, xc); };
+  // The bins' counts to starts, published and left in `bin` as emission cursors.
+  auto starts = [&]() {
+    __syncthreads();
+    uint32_t xr, xc;
+    publish_starts(rec, bin, rsub, csub, W.base + below, xr, xc);
+    __syncthreads();
+    if (tid < 64) {
+      if (lane < rsub) bin[lane] = xr;
+      if (lane < csub) bin[NSGC_GRID_MAX_SUB + lane] = xc;
+    }
+    __syncthreads();
+  };
+  auto emit_row = [&](uint32_t r, uint32_t n) {
+    const uint32_t parts = entry_parts(n, 1);
+    if (row_light(r)) write_entry(er, lds_add(&bin[row_bin(r)], parts), r, n, 1, parts);
+  };
+  auto emit_col = [&](uint32_t c, uint32_t n) {
+    const uint32_t parts = entry_parts(n, 1);
+    if (col_light(c)) write_entry(ec, lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(c)], parts), c, n, 1, parts);
+  };
 
-  // Rounds: each fills the table with as many links as it takes, counts
-  // all their packets and emits them.  If a key found no place, the keys
-  // that did are overwritten with the marker before the next round, which
-  // then sees only the others.  With more than one round a bin's segment
-  // gets one slot per packet of the bin, the most entries it can receive;
-  // slots left over hold empty entries (no packets), which phase C skips.
   uint32_t links = 0, mx = 0;
   const uint32_t most = sload(&P->gmax_keys);
   bool abandoned = most && total > most;
@@ -645,13 +783,16 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
     __syncthreads();
     const uint32_t keep = round && tid < 2 * NSGC_GRID_MAX_SUB ? bin[tid] : 0u;
     clear_table();
+    if (tid < 3) fill[tid] = 0;
     if (round && tid < 2 * NSGC_GRID_MAX_SUB) bin[tid] = keep;   // cursors stay
     __syncthreads();
     gather_by_wave<4, NW>(nt, seg, [&](const auto& pos, const auto& okin) {
       constexpr int U = array_len<decltype(pos)>();
+      if (lds_load(&misc[0])) return;   // the table takes no more
       u64 key[U];
       uint32_t at[U], add[U];
       bool ok[U], fr[U];
+      uint32_t read = 0;
 #pragma unroll
       for (int u = 0; u < U; ++u) key[u] = keys[okin[u] ? pos[u] : 0ull];
 #pragma unroll
@@ -665,6 +806,7 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
         }
         // combine the lanes holding the first valid lane's key
         const u64 vm = __ballot(ok[u]);
+        read += __popcll(vm);
         if (vm) {
           const int f = __ffsll(static_cast<unsigned long long>(vm)) - 1;
           const bool same = ok[u] && key[u] == readlane64(key[u], uint32_t(f));
@@ -675,19 +817,55 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
           }
         }
       }
-      if (insert_keys<U>(tk, uint32_t(SL - 1), key, at, ok, fr)) {
-        lds_store(&misc[0], 1);
+      if (insert_keys<U>(tk, uint32_t(SL - 1), key, at, ok, fr)) lds_store(&misc[0], 1);
+      uint32_t fresh = 0;
 #pragma unroll
-        for (int u = 0; u < U; ++u)   // a key without a slot is left to the next round
-          if (ok[u] && tk[at[u]] != key[u]) ok[u] = false;
+      for (int u = 0; u < U; ++u) {
+        if (ok[u]) lds_add(&tc[at[u]], add[u]);   // (a failed round counts again, what the table holds)
+        fresh += __popcll(__ballot(fr[u]));
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (ok[u]) lds_add(&tc[at[u]], add[u]);
+      if (lane_id() == 0) {
+        lds_add(&fill[1], read);
+        if (fresh && lds_add(&fill[0], fresh) + fresh > GR_FULL) lds_store(&misc[0], 1);
+      }
     });
     const bool failed = misc[0] != 0;
-    if (round == 0) special = misc[1];
-    if (failed) {   // mark the keys the table holds; round 0 also sizes the bins' segments
+    if (failed && round == 0 && (total > GR_KEYS || total > GR_ROUNDS * fill[1])) {
+      // (it stands for GR_ROUNDS rounds where their number is limited)
+      if (max_rounds <= GR_ROUNDS) { abandoned = true; break; }
+      sort_cell<NT>(total, er, ec, reinterpret_cast<uint32_t*>(tk), [&](const auto& fn) {
+        for (uint32_t t = uniform(tid >> 6); t < nt; t += NW) {
+          u64 base;
+          uint32_t len;
+          seg(t, base, len);
+          for (uint32_t i = lane; i < len; i += 64) fn(keys[base + i]);
+        }
+      });
+      if (tid < 2 * NSGC_GRID_MAX_SUB) bin[tid] = 0;
+      sorted_runs<NT>(total, er, tc, [&](u64 k, uint32_t n) {
+        const uint32_t r = uint32_t(k >> 32), c = uint32_t(k), parts = entry_parts(n, 1);
+        ++links;
+        mx = max(mx, n);
+        if (row_light(r)) lds_add(&bin[row_bin(r)], parts);
+        else add_heavy(0, r, n);
+        if (col_light(c)) lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(c)], parts);
+        else add_heavy(1, c, n);
+      });
+      starts();
+      // The row entries go where the keys were: the light sources' keys are
+      // together and in the order of their bins, and a link has no more entries
+      // than keys, so no entry lies behind the last key of its link.
+      sorted_runs<NT>(total, er, tc, [&](u64 k, uint32_t n) {
+        emit_row(uint32_t(k >> 32), n);
+        emit_col(uint32_t(k), n);
+      });
+      break;
+    }
+    uint32_t left = 0;   // this thread's keys that found no place
+    if (failed) {   // count the packets of the links that the table holds, and mark them
+      for (uint32_t i = tid; i < SL; i += NT) tc[i] = 0;
+      if (tid == 0) misc[1] = 0;
+      __syncthreads();
       gather_by_wave<4, NW>(nt, seg, [&](const auto& pos, const auto& okin) {
         constexpr int U = array_len<decltype(pos)>();
         u64 key[U];
@@ -696,23 +874,30 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           if (!okin[u]) continue;
-          if (round == 0) {
+          if (round == 0) {   // a bin's segment: one slot per packet, the most entries it can receive
             if (row_light(uint32_t(key[u] >> 32))) lds_add(&bin[row_bin(uint32_t(key[u] >> 32))], 1);
             if (col_light(uint32_t(key[u]))) lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(uint32_t(key[u]))], 1);
           }
-          if (key[u] == EMPTY64) continue;
+          if (key[u] == EMPTY64) {
+            if (round == 0) lds_add(&misc[1], 1);
+            continue;
+          }
           uint32_t s = home(key[u]);
-          for (uint32_t p = 0; p < NSGC_MAX_PROBES; ++p) {
-            const u64 cur = tk[s];
-            if (cur == key[u]) {
-              keys[pos[u]] = EMPTY64;
-              break;
-            }
-            if (cur == EMPTY64) break;
+          u64 cur = tk[s];
+          for (uint32_t p = 1; cur != key[u] && cur != EMPTY64 && p < NSGC_MAX_PROBES; ++p) {
             s = (s + 1) & uint32_t(SL - 1);
+            cur = tk[s];
+          }
+          if (cur == key[u]) {
+            lds_add(&tc[s], 1);
+            keys[pos[u]] = EMPTY64;
+          } else {
+            ++left;
           }
         }
       });
+      left = wave_sum(left);
+      if (lane == 0 && left) lds_add(&fill[2], left);
     } else if (round == 0) {   // everything fits: count the entries per bin
       for (uint32_t s = tid; s < SL; s += NT) {
         const u64 k = tk[s];
@@ -721,50 +906,35 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
         if (row_light(uint32_t(k >> 32))) lds_add(&bin[row_bin(uint32_t(k >> 32))], parts);
         if (col_light(uint32_t(k))) lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(uint32_t(k))], parts);
       }
-      if (tid == 0 && special) {
-        const uint32_t parts = entry_parts(special, 1);
+      if (tid == 0 && misc[1]) {
+        const uint32_t parts = entry_parts(misc[1], 1);
         lds_add(&bin[row_bin(EMPTY32)], parts);
         lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(EMPTY32)], parts);
       }
     }
     if (round == 0) {
-      __syncthreads();
-      uint32_t xr, xc;
-      starts(xr, xc);
-      __syncthreads();
-      if (tid < 64) {   // the starts become the emission cursors
-        if (lane < rsub) bin[lane] = xr;
-        if (lane < csub) bin[NSGC_GRID_MAX_SUB + lane] = xc;
-      }
-      if (failed)
+      special = misc[1];
+      starts();
+      if (failed)   // slots left over hold empty entries (no packets), which phase C skips
         for (uint32_t i = tid; i < total; i += NT) {
           er[i] = 0ull;
           ec[i] = 0ull;
         }
-      __threadfence_block();   // the empty entries land before any emission
-      __syncthreads();
     }
+    __syncthreads();   // (the empty entries land before any emission)
     auto emit = [&](u64 k, uint32_t n) {
-      const uint32_t r = uint32_t(k >> 32), c = uint32_t(k), parts = entry_parts(n, 1);
-      if (row_light(r)) write_entry(er, lds_add(&bin[row_bin(r)], parts), r, n, 1, parts);
-      else add_heavy(0, r, n);
-      if (col_light(c)) write_entry(ec, lds_add(&bin[NSGC_GRID_MAX_SUB + col_bin(c)], parts), c, n, 1, parts);
-      else add_heavy(1, c, n);
-    };
-    for (uint32_t s = tid; s < SL; s += NT) {
-      const u64 k = tk[s];
-      if (k == EMPTY64) continue;
-      const uint32_t n = tc[s];
+      const uint32_t r = uint32_t(k >> 32), c = uint32_t(k);
       ++links;
       mx = max(mx, n);
-      emit(k, n);
-    }
-    if (tid == 0 && special && round == 0) {
-      ++links;
-      mx = max(mx, special);
-      emit(EMPTY64, special);
-    }
-    if (!failed) break;
+      emit_row(r, n);
+      emit_col(c, n);
+      if (!row_light(r)) add_heavy(0, r, n);
+      if (!col_light(c)) add_heavy(1, c, n);
+    };
+    for (uint32_t s = tid; s < SL; s += NT)
+      if (tk[s] != EMPTY64) emit(tk[s], tc[s]);
+    if (tid == 0 && special && round == 0) emit(EMPTY64, special);
+    if (fill[2] == 0) break;
   }
   __syncthreads();
   if (abandoned) {   // empty segments, so that phase C reads nothing here
