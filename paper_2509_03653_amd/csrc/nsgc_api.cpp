@@ -227,7 +227,7 @@ struct Launch {
   uint32_t max_link_buckets, max_rc_buckets;
   // grid windows: heavy sample, partition by tile size (2^11 ..), link
   // aggregation of small / big cells, row/column aggregation
-  uint32_t gheavy, gpart[4], glinks[2], gwhole[NSGC_WHOLE], gwide, gover, grc, gent;
+  uint32_t gheavy, gpart[4], glinks[2], gwhole[NSGC_WHOLE], gwide, gover, grounds, grc, gent;
   size_t lds_grc;
 };
 
@@ -286,6 +286,7 @@ int launch_params(DevCtx* c, const nsgc_tune& t, Launch* out) {
   L.gheavy = uint32_t(c->cus) * 2;
   L.gwide = uint32_t(c->cus);
   L.gover = uint32_t(c->cus) * 3;
+  L.grounds = uint32_t(c->cus);
   for (uint32_t k = 0; k < 4; ++k)
     if ((rc = resident_cap(c, kGridKernels, 11 + k, lds_grid_part_bytes(11 + k, grid_max_cells(11 + k)), 16,
                            &L.gpart[k])) != NSGC_OK)
@@ -376,7 +377,7 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
   // what these leave over is known on the device only: small persistent grids
   // (small cells alone are left over too seldom to be worth the wide pass)
   if (gbig) NSGC_HIP(launch_grid_links(dplan, 2, grid(hp.gitemsB, L.gwide), s));
-  if (gsmall || gbig) NSGC_HIP(launch_grid_rounds(dplan, gbig, grid(hp.gitemsB, L.gover), s));
+  if (gsmall || gbig) NSGC_HIP(launch_grid_rounds(dplan, gbig, grid(hp.gitemsB, L.grounds), s));
   // The phase-C order depends only on the partition's sizes: with wavefront
   // phase-B items it is computed by an extra workgroup of that kernel, beside
   // phase B, instead of by k_order after it.
@@ -411,7 +412,7 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
   if (!hp.large.empty()) {
     if (!la) return NSGC_ERR_INTERNAL;
     char* region = la->ws + hp.layout().large;
-    const LargeGridLaunch lg = {la->grid / 8, L.glinks[1], L.gwide, L.gover, L.grc, L.lds_grc,
+    const LargeGridLaunch lg = {la->grid / 8, L.glinks[1], L.gwide, L.gover, L.grounds, L.grc, L.lds_grc,
                                 hp.rc_slots_log2};
     for (const LargeWindow& lw : hp.large) {
       const uint32_t* src = la->src + lw.in_begin;

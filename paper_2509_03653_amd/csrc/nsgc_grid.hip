@@ -567,27 +567,30 @@ __device__ __forceinline__ void publish_starts(NSGC_GLOBAL uint32_t* rec, const 
 // By rounds: each fills the table with as many links as it takes, which are
 // counted, emitted and overwritten with the marker, so that the next round sees
 // only the others.  A round reads the cell's keys twice, so a cell of k links
-// costs k / GR_FULL readings: the cells that are left over in ordinary traffic
-// have a few thousand links to a few tens of thousands.  A cell of more than
-// GR_KEYS keys, or whose table was full after less than one key in GR_ROUNDS, is
-// sorted instead: eight passes over its keys whatever they are (cells are chosen
-// by the top bits of the hashed addresses, so traffic can be made that puts a
-// whole window in one).
+// costs 2 k / GR_FULL readings: the cells that are left over in ordinary traffic
+// have a few thousand to a few tens of thousands.  A cell of more than GR_KEYS
+// keys, or whose table was full after less than one key in GR_ROUNDS, is sorted
+// instead: eight passes over its keys whatever they are (cells are chosen by the
+// top bits of the hashed addresses, so traffic can be made that puts a whole
+// window in one).
+// One workgroup of 1024 threads with 8192 slots per compute unit: against two of
+// 512 with 4096, one window of 2^26 packets among 4096 addresses (8192 links in
+// each cell) takes 3.8 ms instead of 6.2, one of 2^25 2.3 instead of 3.2.
 // ---------------------------------------------------------------------------
 
-constexpr int GR_NT = 512;
-constexpr int GR_SL = 4096;
+constexpr int GR_NT = 1024;
+constexpr int GR_SL = 8192;
 constexpr uint32_t GR_FULL = GR_SL * 3 / 4;   // links in the table when no more are taken
 constexpr uint32_t GR_ROUNDS = 12;
 constexpr uint32_t GR_KEYS = 1u << 16;
 
 // The n keys that `each` visits (in any order) into `a` in ascending order, by way of `b`: a radix sort by bytes.
-// `lds` is scratch of 4096 words.  Ends with a barrier.
+// `lds` is scratch of 2048 + 4 NT words.  Ends with a barrier.
 template <int NT, class Each>
 __device__ __forceinline__ void sort_cell(uint32_t n, NSGC_GLOBAL u64* a, NSGC_GLOBAL u64* b, uint32_t* lds,
                                           const Each& each) {
   constexpr uint32_t NW = NT / 64, R = 8, TILE = NT * R;
-  static_assert(NW == 8, "a wavefront per digit scans its counts");
+  static_assert(NW >= 8, "a wavefront per digit scans its counts");
   uint32_t* const hist = lds;          // [8][256] of each digit: counts, then the next position
   uint32_t* const cnt = lds + 2048;    // [NW][256]
   const uint32_t tid = threadIdx.x, w = tid >> 6, lane = lane_id();
@@ -600,7 +603,7 @@ __device__ __forceinline__ void sort_cell(uint32_t n, NSGC_GLOBAL u64* a, NSGC_G
     for (uint32_t d = 0; d < 8; ++d) lds_add(&hist[d * 256 + digit(k, d)], 1);
   });
   __syncthreads();
-  {
+  if (w < 8) {
     uint32_t x[4], s = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {

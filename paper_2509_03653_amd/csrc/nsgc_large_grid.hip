@@ -540,7 +540,7 @@ hipError_t large_grid_stats(const uint32_t* src, const uint32_t* dst, unsigned l
     return e;
   if ((e = launch_grid_links(A.inner, 1, L.links, s)) != hipSuccess) return e;
   if ((e = launch_grid_links(A.inner, 2, L.wide, s)) != hipSuccess) return e;
-  if ((e = launch_grid_rounds(A.inner, true, L.over, s)) != hipSuccess) return e;
+  if ((e = launch_grid_rounds(A.inner, true, L.rounds, s)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_large_reduce, dim3(OUT), dim3(512), 0, s, A);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_grid_rowcol(A.whole, L.rowcol, L.lds_rowcol, s)) != hipSuccess) return e;
