@@ -371,8 +371,8 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
     NSGC_HIP(launch_partition(dplan, tile_log2, L.max_link_buckets, rows, grid(hp.itemsA, L.grid_part),
                               L.lds_part, s));
   NSGC_HIP(mark(2));
-  if (gbig)
-    NSGC_HIP(launch_grid_links(dplan, 1, grid(hp.gitemsB - hp.gitemsS, L.glinks[1]), s));
+  if (gbig && (fixed_grid || hp.gitemsW > hp.gitemsS))
+    NSGC_HIP(launch_grid_links(dplan, 1, grid(hp.gitemsW - hp.gitemsS, L.glinks[1]), s));
   if (gsmall) NSGC_HIP(launch_grid_links(dplan, 0, grid(hp.gitemsS, L.glinks[0]), s));
   // what these leave over is known on the device only: small persistent grids
   // (small cells alone are left over too seldom to be worth the wide pass)

@@ -962,8 +962,9 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
 }
 
 // The phase in three sizes: SMALL and BIG for windows of smaller and of larger
-// cells, and WIDE for the cells that BIG listed as too large for it, with three
-// times the keys and twice the table (one workgroup per compute unit).  Cells
+// cells, and WIDE for the cells that the others listed as too large for them and
+// for windows whose cells have more packets on average than BIG's threads hold,
+// with three times the keys and twice the table (one workgroup per compute unit).  Cells
 // that SMALL or WIDE list go to k_grid_rounds.  Sixteen windows of 2^23 packets
 // among 4096 addresses, half of whose cells overflow BIG, took 8.2 ms without
 // WIDE and take 3.8 ms with it.
@@ -977,18 +978,22 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
   static_assert(ROOM * 4 <= SL * 8, "the positions share the key table");
   static_assert((2 * NT + 2 * NW) * 4 <= SL * 2, "the segment table shares the counts");
   static_assert(ROOM < 65536, "16-bit counts");
+  static_assert(KIND != BIG || (ROOM == NSGC_GRID_BIG_KEYS && NT == NSGC_GRID_BIG_TILES), "see the planner's classes");
+  static_assert(KIND != SMALL || NT == NSGC_GRID_SMALL_TILES, "see the planner's classes");
   __shared__ __align__(16) u64 tk[SL];
   __shared__ __align__(16) uint32_t tc[SL / 2];   // 16-bit counts, two to a word
   __shared__ u64 acc[2 * HVM];
   __shared__ uint32_t bin[2 * NSGC_GRID_MAX_SUB];   // rows, columns
   __shared__ uint32_t misc[8];   // 0 failed, 1 special packets, 2 links, 3 max packets, 7 queue slot
   const uint32_t lane = lane_id();
-  const uint32_t items = KIND == WIDE ? gptr(&P->gover[0])[0]
-                       : KIND == BIG  ? sload(&P->gitemsB) - sload(&P->gitemsS)
-                                      : sload(&P->gitemsS);
+  // WIDE: the cells of its own windows, then the listed ones
+  const uint32_t own = KIND == WIDE  ? sload(&P->gitemsB) - sload(&P->gitemsW)
+                       : KIND == BIG ? sload(&P->gitemsW) - sload(&P->gitemsS)
+                                     : sload(&P->gitemsS);
+  const uint32_t items = own + (KIND == WIDE ? gptr(&P->gover[0])[0] : 0u);
   auto item_at = [&](uint32_t pos) -> uint32_t {
-    if (KIND == WIDE) return uniform(gptr(sload(&P->goverB))[pos]);
-    return uniform(KIND == BIG ? sload(&P->gitemsS) + pos : pos);
+    if (KIND == WIDE && pos >= own) return uniform(gptr(sload(&P->goverB))[pos - own]);
+    return uniform((KIND == WIDE ? sload(&P->gitemsW) : KIND == BIG ? sload(&P->gitemsS) : 0u) + pos);
   };
   const uint32_t T = 1u << sload(&P->gtile_log2);
 
@@ -1028,9 +1033,22 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
     if (nt <= 64)
       total = spread_by_wave<NT>(tid, nt, lane * T + (x & 0xFFFFu), x >> 16, below,
                                  reinterpret_cast<uint32_t*>(tk), ROOM);
-    else if (nt <= NT)
+    else if (KIND == WIDE) {   // a thread per tile, in turns where there are more
+      total = 0;
+      for (uint32_t t = 0; t < nt && total <= ROOM; t += NT) {
+        if (t) {
+          lds_barrier();   // the last turn's scratch has been read
+          x = record(W, it, t + tid);
+        }
+        uint32_t more = x & 0xFFFFu;
+        total += spread_segments<NT>(tid, min(nt - t, uint32_t(NT)), (t + tid) * T + (x & 0xFFFFu), x >> 16, more,
+                                     tc, reinterpret_cast<uint32_t*>(tk) + total, ROOM - total);
+        below = t ? below + more : more;
+      }
+    } else if (nt <= NT) {   // (an outer cell of a large window may have more: left to WIDE)
       total = spread_segments<NT>(tid, nt, tid * T + (x & 0xFFFFu), x >> 16, below, tc,
                                   reinterpret_cast<uint32_t*>(tk), ROOM);
+    }
     lds_barrier();
     const uint32_t ahead = uniform(misc[6]);
     have = ahead != NO_ITEM;

@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void k_large_init(Args A) {
     p->goverB = A.goverB;
     p->goverW = A.goverW;
     p->num_grid = OUT;
-    p->gitemsB = A.cells;
+    p->gitemsW = p->gitemsB = A.cells;
     p->gtile_log2 = TILE_LOG2;
     p->max_sweeps_log2 = 5;
     p->gmax_keys = 1u << 22;

@@ -124,7 +124,13 @@
 #define NSGC_GRID_HV(t) ((t) >= 14 ? 64 : 32)
 #define NSGC_GRID_SAMPLE(hv) ((hv) == 64 ? 4096 : 2048)
 #define NSGC_GRID_TILE13_CELLS 1024            // most cells of a batch partitioned in 2^13-packet tiles
-#define NSGC_GRID_TILES 256                    // tiles of a window that every phase-B kernel takes in one pass
+// Phase B of a window of more packets per cell than SMALL_CELLS on average is
+// done by BIG, of more than BIG_KEYS, the keys that BIG's threads hold, by WIDE.
+// SMALL and BIG take a tile record per thread.
+#define NSGC_GRID_SMALL_CELLS 1280
+#define NSGC_GRID_BIG_KEYS 4096
+#define NSGC_GRID_SMALL_TILES 256
+#define NSGC_GRID_BIG_TILES 512
 #define NSGC_GRID_MAX_CELLS_LOG2 11
 #define NSGC_GRID_MAX_A 6                      // row strips (log2)
 #define NSGC_GRID_MAX_B 9                      // column strips (log2)
@@ -253,7 +259,7 @@ struct nsgc_dev_plan {          // header of the device plan buffer
   uint32_t* partR;              // [itemsB][4] complete sources of a bucket: count, max packets,
                                 //   max links, 0
   // Grid windows.
-  const nsgc_grid_desc* gwin;   // windows of small cells first, then those of big cells
+  const nsgc_grid_desc* gwin;   // windows by the kernel of their phase B: SMALL, BIG, WIDE
   const uint32_t* gprefA;       // [num_grid + 1] first partition tile of each window
   const uint32_t* gitemB;       // [gitemsB] window of each cell
   const uint32_t* gitemC;       // [gitemsC] window of each phase-C item
@@ -262,7 +268,8 @@ struct nsgc_dev_plan {          // header of the device plan buffer
                                 //   item, bucket within the item
   uint32_t* goverW;             // cells that the wide pass of phase B left over, gover[2] of them
   uint32_t gover[4];
-  uint32_t num_grid, gitemsA, gitemsS, gitemsB, gitemsC, gtile_log2;
+  // cells: SMALL's up to gitemsS, BIG's up to gitemsW, WIDE's up to gitemsB
+  uint32_t num_grid, gitemsA, gitemsS, gitemsW, gitemsB, gitemsC, gtile_log2;
   uint32_t gmax_keys;           // a cell of more keys is abandoned (0: none is)
   // Upload: 16-byte units of the header and the lists behind it, and of the
   // work-queue counters behind those, which the upload clears.

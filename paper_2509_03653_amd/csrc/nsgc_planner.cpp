@@ -92,23 +92,36 @@ bool grid_window(uint64_t n, bool entity, int finer, const nsgc_tune& tune, cons
 constexpr uint64_t kFinerPackets = uint64_t(512) << 10;
 constexpr int kFinerMost = 2;
 
-// Cells of more than 1280 packets on average take the kernel with 4096-slot
-// tables (a 2048-slot one would be more than half full).
-bool grid_big(const nsgc_grid_desc& g) { return (g.n >> (g.logA + g.logBc)) > 1280; }
+// The kernel of a grid window's phase B (0 SMALL, 1 BIG, 2 WIDE): a 2048-slot
+// table would be more than half full above 1280 packets per cell, and above 4096
+// BIG would leave most cells to WIDE after a reading of its own (one window of
+// 1.2 * 10^7 packets among 4096 addresses 0.77 -> 0.71 ms without it).
+int grid_kind(const nsgc_grid_desc& g) {
+  const uint32_t cells = g.logA + g.logBc;
+  return g.n > uint64_t(NSGC_GRID_BIG_KEYS) << cells ? 2 : g.n >> cells > NSGC_GRID_SMALL_CELLS ? 1 : 0;
+}
 
 // Partition tile (log2).  Tiles of 2^14 packets where a window has more than
 // 1024 cells (their runs of keys per cell are longer); else 2^13, of which two
 // fit a compute unit and overlap; smaller ones, down to 2^11, as long as the
-// batch has fewer than two tiles per compute unit and its longest window no
-// more than phase B takes in a pass (a thread per tile).
+// batch has fewer than two tiles per compute unit and its longest window few;
+// and larger ones than the tuning's if SMALL's or BIG's longest window would
+// have more tiles than their threads take.
 constexpr uint64_t kGridTiles = 512;
-uint32_t grid_tile_log2(uint64_t packets, uint32_t cells, uint32_t longest, const nsgc_tune& tune) {
+uint32_t grid_tile_log2(uint64_t packets, uint32_t cells, const uint32_t (&longest)[3], const nsgc_tune& tune) {
   uint32_t k = uint32_t(tune.tile_log2);
   if (cells > NSGC_GRID_TILE13_CELLS) return 14;
   k = std::min(k, 13u);
-  while (k > 11 && (packets >> k) < kGridTiles && (longest >> k) < NSGC_GRID_TILES / 2) --k;
+  const uint32_t most = std::max(std::max(longest[0], longest[1]), longest[2]);
+  while (k > 11 && (packets >> k) < kGridTiles && (most >> k) < NSGC_GRID_SMALL_TILES / 2) --k;
+  const auto tiles = [&](int kind) { return (uint64_t(longest[kind]) + (uint64_t(1) << k) - 1) >> k; };
+  while (tiles(0) > NSGC_GRID_SMALL_TILES || tiles(1) > NSGC_GRID_BIG_TILES) ++k;
   return k;
 }
+// (up to 1280 and 4096 packets in each of 1024 cells: 2^13-packet tiles do)
+static_assert(NSGC_GRID_TILE13_CELLS * (NSGC_GRID_SMALL_CELLS + 1) <= NSGC_GRID_SMALL_TILES << 13, "SMALL");
+static_assert(NSGC_GRID_TILE13_CELLS * NSGC_GRID_BIG_KEYS <= NSGC_GRID_BIG_TILES << 13, "BIG");
+static_assert((NSGC_GRID_BIG_KEYS << NSGC_GRID_MAX_CELLS_LOG2) <= NSGC_GRID_BIG_TILES << 14, "BIG, large tiles");
 
 }  // namespace
 
@@ -206,9 +219,9 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
   p->gitemB.clear();
   p->gitemC.clear();
   std::vector<nsgc_small_desc> whole[NSGC_WHOLE];   // windows taken whole, by size
-  std::vector<nsgc_grid_desc> gbig;         // grid windows of big cells
+  std::vector<nsgc_grid_desc> grid[3];      // grid windows by the kernel of their phase B
   uint64_t gpackets = 0;
-  uint32_t glongest = 0;
+  uint32_t glongest[3] = {0, 0, 0};
   uint32_t gcells = 0;   // most cells of a grid window
   p->itemsBb = p->itemsBw = 0;
   p->wave_rc_max = 0;
@@ -278,9 +291,10 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
         grid_window(n, entity, finer, tune, tc, &g)) {
       g.src = at<uint32_t>(uint64_t(offsets[w]) * 4);   // byte offsets until serialize()
       g.out_index = uint32_t(w);
-      (grid_big(g) ? gbig : p->gwin).push_back(g);
+      const int kind = grid_kind(g);
+      grid[kind].push_back(g);
       gpackets += n;
-      glongest = std::max(glongest, uint32_t(n));
+      glongest[kind] = std::max(glongest[kind], uint32_t(n));
       gcells = std::max(gcells, 1u << (g.logA + g.logBc));
       continue;
     }
@@ -316,7 +330,7 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
   // Beside grid windows up to NSGC_GRID_RIDERS of the longer ones join them, to
   // spare their own launch (windows of 20698 and 7074 packets: 67 us apart, 48
   // on the grid).
-  if (!p->gwin.empty() || !gbig.empty()) {
+  if (gpackets) {
     std::vector<nsgc_small_desc> stay;
     size_t riders = 0;
     for (const nsgc_small_desc& s : whole[3]) {
@@ -329,7 +343,7 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
       g.src = at<uint32_t>(uint64_t(s.in_begin) * 4);
       g.out_index = s.out_index;
       gpackets += g.n;
-      p->gwin.push_back(g);
+      grid[0].push_back(g);
     }
     whole[3].swap(stay);
   }
@@ -348,11 +362,11 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
   }
   // grid windows: tile size, then tiles, cells and phase-C items in order
   p->gtile_log2 = grid_tile_log2(gpackets, gcells, glongest, tune);
-  const size_t nsmall = p->gwin.size();
-  p->gwin.insert(p->gwin.end(), gbig.begin(), gbig.end());
+  for (const std::vector<nsgc_grid_desc>& g : grid) p->gwin.insert(p->gwin.end(), g.begin(), g.end());
+  const size_t nsmall = grid[0].size(), nbig = nsmall + grid[1].size();
   uint64_t ga = 0, gb = 0, gc = 0;
   p->gtile_words = p->grec_words = 0;
-  p->gitemsS = 0;
+  p->gitemsS = p->gitemsW = 0;
   p->gbuckets = 0;
   for (size_t i = 0; i < p->gwin.size(); ++i) {
     nsgc_grid_desc& g = p->gwin[i];
@@ -382,6 +396,7 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
     gc += items;
     if (ga > 0xFFFFFFFFull || gb > 0xFFFFFFFFull || gc > 0xFFFFFFFFull) return NSGC_ERR_INVALID_ARG;
     if (i < nsmall) p->gitemsS = uint32_t(gb);
+    if (i < nbig) p->gitemsW = uint32_t(gb);
   }
   p->gprefA.push_back(uint32_t(ga));
   p->gitemsA = uint32_t(ga);
@@ -613,6 +628,7 @@ void HostPlan::serialize(void* buf, uint64_t dev_plan, uint64_t dev_ws, const ui
   h.num_grid = uint32_t(gwin.size());
   h.gitemsA = gitemsA;
   h.gitemsS = gitemsS;
+  h.gitemsW = gitemsW;
   h.gitemsB = gitemsB;
   h.gitemsC = gitemsC;
   h.gtile_log2 = gtile_log2;

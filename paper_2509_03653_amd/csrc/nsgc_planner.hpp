@@ -44,9 +44,9 @@ struct HostPlan {
   std::vector<uint32_t> itemwinB, itemwinC;   // window of each phase-B / phase-C item
   std::vector<uint32_t> mapBb, mapBw;         // phase-B items by kernel (empty: identity)
   std::vector<PartShape> shape;               // per partitioned window (tier 2), in window order
-  std::vector<nsgc_grid_desc> gwin;           // grid windows: small cells, then big cells
+  std::vector<nsgc_grid_desc> gwin;           // grid windows by the kernel of their phase B
   std::vector<uint32_t> gprefA, gitemB, gitemC;
-  uint32_t gitemsA = 0, gitemsS = 0, gitemsB = 0, gitemsC = 0, gtile_log2 = 14;
+  uint32_t gitemsA = 0, gitemsS = 0, gitemsW = 0, gitemsB = 0, gitemsC = 0, gtile_log2 = 14;
   uint32_t gbuckets = 0;       // row and column buckets of the grid windows
   int64_t gtile_words = 0, grec_words = 0;
   uint32_t itemsBb = 0, itemsBw = 0;
