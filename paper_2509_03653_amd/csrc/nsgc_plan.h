@@ -113,7 +113,8 @@
 // words: the cell's emission base, its row-bucket starts (one more than
 // buckets), its column-bucket starts.
 #define NSGC_GRID_MIN 8193                     // packets of the smallest grid window
-#define NSGC_GRID_RIDE 4097                    // of the smallest that rides along with larger ones
+#define NSGC_GRID_RIDE 1025                    // of the smallest that rides along with larger ones
+#define NSGC_GRID_RIDE_APART 4097              //   even if shorter ones need a launch of their own
 #define NSGC_GRID_ENTITY 1025                  // of the smallest for the entity counts
 #define NSGC_GRID_RIDERS 256                   // most windows that ride along
 // Dominant addresses per view, and the sample they are drawn from, in a batch

@@ -327,25 +327,31 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
     if (a > 0xFFFFFFFFull || b > 0xFFFFFFFFull || c > 0xFFFFFFFFull) return NSGC_ERR_INVALID_ARG;
     p->win.push_back(d);
   }
-  // Beside grid windows up to NSGC_GRID_RIDERS of the longer ones join them, to
-  // spare their own launch (windows of 20698 and 7074 packets: 67 us apart, 48
-  // on the grid).
+  // Beside grid windows up to NSGC_GRID_RIDERS of the longer ones join them, and
+  // all of them if that spares their launch, which stands in front of a small
+  // batch's chain of kernels (windows of 20698 and 7074 packets: 67 us apart, 48
+  // on the grid; 7 of 1947 .. 22721: 60 and 42; 45 of 1143 .. 16547: 69 and 51;
+  // but 1500 of 2700 .. 13858: 322 and 376).
   if (gpackets) {
-    std::vector<nsgc_small_desc> stay;
+    const bool all = whole[0].empty() && whole[1].empty() && whole[2].size() + whole[3].size() <= NSGC_GRID_RIDERS;
     size_t riders = 0;
-    for (const nsgc_small_desc& s : whole[3]) {
-      nsgc_grid_desc g;
-      if (riders == NSGC_GRID_RIDERS || !grid_window(s.n, false, 0, tune, tune.cls[ceil_log2(s.n + 1) - 1], &g)) {
-        stay.push_back(s);
-        continue;
+    for (int k = 2; k < NSGC_WHOLE; ++k) {
+      std::vector<nsgc_small_desc> stay;
+      for (const nsgc_small_desc& s : whole[k]) {
+        nsgc_grid_desc g;
+        if (riders == NSGC_GRID_RIDERS || (!all && s.n < NSGC_GRID_RIDE_APART) ||
+            !grid_window(s.n, false, 0, tune, tune.cls[ceil_log2(s.n + 1) - 1], &g)) {
+          stay.push_back(s);
+          continue;
+        }
+        ++riders;
+        g.src = at<uint32_t>(uint64_t(s.in_begin) * 4);
+        g.out_index = s.out_index;
+        gpackets += g.n;
+        grid[0].push_back(g);
       }
-      ++riders;
-      g.src = at<uint32_t>(uint64_t(s.in_begin) * 4);
-      g.out_index = s.out_index;
-      gpackets += g.n;
-      grid[0].push_back(g);
+      whole[k].swap(stay);
     }
-    whole[3].swap(stay);
   }
   // A launch more costs 6 to 10 us: sizes that fit the chip at once in a larger
   // size's kernel go there (180 windows of 6 .. 524 packets: 25 us in two
