@@ -278,6 +278,13 @@ int nsgc_plan_sizes(const int64_t* window_offsets, int64_t num_windows, int64_t*
                     int64_t* workspace_bound_bytes);
 
 /*
+ * How many windows of the large-window tier this process has computed so far
+ * by hash partitioning and by sorting (those out of its range, and those it
+ * gave up on).  Either pointer may be NULL.  Always returns NSGC_OK.
+ */
+int nsgc_large_window_counts(int64_t* by_grid, int64_t* by_sorting);
+
+/*
  * Graph form: a reusable hipGraph of the batched form with its own workspace
  * sized for up to max_packets packets and max_windows windows.  Launching
  * replays the captured graph (plan upload + persistent kernels, fixed grids);

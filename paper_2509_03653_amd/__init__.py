@@ -63,6 +63,7 @@ EXPORTS = (
     "nsgc_default_tune",
     "nsgc_plan_inspect",
     "nsgc_plan_sizes",
+    "nsgc_large_window_counts",
     "nsgc_graph_create",
     "nsgc_graph_launch",
     "nsgc_graph_destroy",
@@ -176,6 +177,8 @@ def _lib():
         lib.nsgc_plan_inspect.restype = i32
         lib.nsgc_plan_sizes.argtypes = [vp, i64, vp, vp, vp, vp]
         lib.nsgc_plan_sizes.restype = i32
+        lib.nsgc_large_window_counts.argtypes = [vp, vp]
+        lib.nsgc_large_window_counts.restype = i32
         lib.nsgc_graph_create.argtypes = [i64, i64, ctypes.POINTER(vp)]
         lib.nsgc_graph_create.restype = i32
         lib.nsgc_graph_launch.argtypes = [vp, vp, vp, vp, i64, vp, vp]
@@ -360,6 +363,14 @@ def plan_inspect(offsets) -> dict:
     _check(rc, "nsgc_plan_inspect")
     return {"tier": tier[:w], "log2_link_buckets": lb[:w], "log2_row_buckets": lr[:w],
             "log2_col_buckets": lc[:w], "tiles": tiles[:w], "workspace_bytes": int(wsb[0])}
+
+
+def large_window_counts() -> dict:
+    """Windows of the large tier computed so far by this process, by method
+    (``nsgc_large_window_counts``)."""
+    n = (ctypes.c_int64 * 2)()
+    _lib().nsgc_large_window_counts(ctypes.byref(n, 0), ctypes.byref(n, 8))
+    return {"grid": int(n[0]), "sorting": int(n[1])}
 
 
 def plan_sizes(offsets) -> dict:

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -119,6 +120,8 @@ std::map<int, DevCtx*> g_devs;
 nsgc_tune g_tune;
 bool g_tune_set = false;
 bool g_plain_mode = false;   // nsgc_set_plain_mode: route nsgc_window_stats through the plain form
+
+std::atomic<int64_t> g_large_windows[2];   // by grid, by sorting (nsgc_large_window_counts)
 
 const nsgc_tune& current_tune() {
   if (!g_tune_set) {
@@ -419,7 +422,8 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
       const uint32_t* dst = la->dst + lw.in_begin;
       unsigned long long* out = la->out + (unsigned long long)lw.out_index * 9;
       // By grid, and by sorting if that is out of range or gave up on the
-      // window (one wait for the stream tells).
+      // window (one wait for the stream tells).  Packets that are neither
+      // counted nor given up on are an error: sorting would hide it.
       const size_t need = large_grid_bytes(lw.n);
       bool sorted = need == 0 || need > large_window_bytes(lw.n);
       if (!sorted) {
@@ -427,8 +431,10 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
         unsigned long long packets = 0;
         NSGC_HIP(hipMemcpyAsync(&packets, out, sizeof packets, hipMemcpyDeviceToHost, s));
         NSGC_HIP(hipStreamSynchronize(s));
-        sorted = packets != lw.n;
+        sorted = (packets >> 63) != 0;
+        if (!sorted && packets != lw.n) return NSGC_ERR_INTERNAL;
       }
+      g_large_windows[sorted ? 1 : 0].fetch_add(1, std::memory_order_relaxed);
       if (sorted) NSGC_HIP(large_window_stats(src, dst, lw.n, region, out, la->grid, s));
     }
   }
@@ -717,11 +723,10 @@ int run_fixed_scratch(const uint32_t* src, const uint32_t* dst, const int64_t* w
                         uint32_t(c->cus) * 8};
   rc = enqueue_kernels(hp, reinterpret_cast<const nsgc_dev_plan*>(plan_dev), L, hp.tile_log2, s,
                        false, 0, nullptr, &la);
-  if (rc != NSGC_OK) return rc;
-  NSGC_HIP(hipEventRecord(f.done, s));
+  NSGC_HIP(hipEventRecord(f.done, s));   // (after an error too: what was enqueued uses the scratch)
   f.last_stream = s;
   f.used = true;
-  return NSGC_OK;
+  return rc;
 }
 
 }  // namespace nsgc
@@ -957,6 +962,12 @@ int nsgc_set_tune(const nsgc_tune* tune) {
   std::lock_guard<std::mutex> lock(g_mu);
   g_tune = *tune;
   g_tune_set = true;
+  return NSGC_OK;
+}
+
+int nsgc_large_window_counts(int64_t* by_grid, int64_t* by_sorting) {
+  if (by_grid) *by_grid = g_large_windows[0].load(std::memory_order_relaxed);
+  if (by_sorting) *by_sorting = g_large_windows[1].load(std::memory_order_relaxed);
   return NSGC_OK;
 }
 
