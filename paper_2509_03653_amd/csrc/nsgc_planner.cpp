@@ -509,14 +509,17 @@ void grid_windows_bound(uint64_t P, uint64_t W, uint64_t* gw, uint64_t* riders) 
 
 // Most cells of `gw` grid windows of P packets in all: a window of n packets
 // has fewer than 2 n / target + 2, and at most the cap; one that rides along 16;
-// and a batch below kFinerPackets a few thousand more.
+// those of a batch below kFinerPackets four times as many.
 uint64_t grid_cells_bound(uint64_t P, uint64_t gw, uint64_t riders, const nsgc_tune& t) {
   uint64_t wt = ~uint64_t(0);
   for (int k = 0; k <= 32; ++k)
     if (t.cls[k].wave_target > 0) wt = std::min<uint64_t>(wt, uint64_t(t.cls[k].wave_target));
   if (wt == ~uint64_t(0)) return 0;
   const int cap = std::min(int(t.max_link_buckets_log2), NSGC_GRID_MAX_CELLS_LOG2);
-  return std::min<uint64_t>(P / (2 * wt) + 2 * gw, gw << cap) + riders * 16 + 6 * (kFinerPackets >> 10);
+  const uint64_t finer = (uint64_t(1) << kFinerMost) - 1;
+  const uint64_t extra = finer * (std::min(P, kFinerPackets) / (2 * wt) +
+                                  2 * std::min<uint64_t>(gw, kFinerPackets / NSGC_GRID_MIN));
+  return std::min<uint64_t>(P / (2 * wt) + 2 * gw + extra, gw << cap) + riders * 16;
 }
 
 // Likewise their phase-C items: R + C < 4 n / target + 4 and at most
@@ -573,8 +576,8 @@ size_t grid_workspace_bound(int64_t max_packets, int64_t max_windows, const nsgc
   // batches with larger ones in tiles of 2^14
   const uint64_t c13 = std::min<uint64_t>(cells, NSGC_GRID_TILE13_CELLS);
   const uint64_t c14 = std::min<uint64_t>(cells, uint64_t(1) << NSGC_GRID_MAX_CELLS_LOG2);
-  const uint64_t tile_words =
-      std::max((P >> std::min(t.tile_log2, 13)) * c13, (P >> 14) * c14) + (2 * kGridTiles + gw + riders) * c14;
+  const uint64_t t13 = std::max(P >> std::min(t.tile_log2, 13), std::min(P >> 11, 2 * kGridTiles)) + gw + riders;
+  const uint64_t tile_words = std::max(t13 * c13, ((P >> 14) + gw + riders) * c14);
   const uint64_t citems = grid_citems_bound(P, gw, riders, t);
   // a cell record has at most 2 NSGC_GRID_MAX_SUB + 3 words, and per window
   // cells * (R / strips + C / strips + 3) <= cells * 3 + (R + C) * max strips
