@@ -1,10 +1,11 @@
 // C ABI of the window-statistics library (declared in include/nsgc.h).
 //
 // Host side of every call: validate the arguments, plan the batch (tiers,
-// bucket counts, items, workspace layout), upload the plan through a pinned
-// staging buffer with one async copy, and launch the persistent kernels on the
-// caller's stream.  Workspaces and plan buffers are cached per (device,
-// stream) so calls on different streams can overlap.
+// bucket counts, items, workspace layout), send the plan to the device in the
+// arguments of a launch or through a pinned staging buffer that a kernel reads,
+// and launch the persistent kernels on the caller's stream.  Workspaces and plan
+// buffers are cached per (device, stream) so calls on different streams can
+// overlap.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -570,35 +571,45 @@ int begin_call(hipStream_t s, CallCtx* cc, bool entity = false, bool launch = tr
   return launch ? launch_params(cc->c, cc->t, &cc->L) : NSGC_OK;
 }
 
+// Calls run(allow_grid), which plans and runs, and once more without grid windows
+// if the workspace for them is not to be had: they take up to a tenth more
+// beside the keys than the other form (nothing has been enqueued then).
+template <class Run>
+int with_or_without_grid(const Run& run) {
+  const int rc = run(true);
+  return rc == NSGC_ERR_NO_MEMORY ? run(false) : rc;
+}
+
 // The batched form (caller holds the slot's lock, arguments validated,
-// num_windows > 0).
+// num_windows > 0).  ev: see nsgc_window_stats_timed.
 int batched_locked(const CallCtx& cc, const uint32_t* src, const uint32_t* dst,
                    const int64_t* window_offsets, int64_t num_windows, nsgc_stats* out_stats,
-                   hipStream_t s) {
-  HostPlan hp;
-  int rc;
-  if ((rc = make_plan(window_offsets, num_windows, cc.t, &hp)) != NSGC_OK) return rc;
-  return run_plan(cc.c, cc.sl, hp, cc.L, src, dst, out_stats, s);
+                   hipStream_t s, const hipEvent_t* ev = nullptr) {
+  return with_or_without_grid([&](bool grid) {
+    HostPlan hp;
+    const int rc = make_plan(window_offsets, num_windows, cc.t, &hp, false, true, grid);
+    return rc != NSGC_OK ? rc : run_plan(cc.c, cc.sl, hp, cc.L, src, dst, out_stats, s, ev);
+  });
 }
 
 // The plain form: one plan and one launch sequence per window (caller holds
 // the slot's lock, arguments validated, num_windows > 0).
 int plain_locked(const CallCtx& cc, const uint32_t* src, const uint32_t* dst,
                  const int64_t* window_offsets, int64_t num_windows, nsgc_stats* out_stats,
-                 hipStream_t s) {
+                 hipStream_t s, bool allow_grid) {
   const nsgc_tune& t = cc.t;
   DevCtx* c = cc.c;
   Slot* sl = cc.sl;
   const Launch& L = cc.L;
   int rc;
 
-  // One plan per window, all uploaded with one copy; the windows then run one
-  // launch sequence each, in order, sharing one workspace.
+  // One plan per window, all uploaded at once; the windows then run one launch
+  // sequence each, in order, sharing one workspace.
   std::vector<HostPlan> plans(static_cast<size_t>(num_windows));
   std::vector<size_t> at(static_cast<size_t>(num_windows));
   size_t pbytes = 0, wsmax = 0;
   for (int64_t w = 0; w < num_windows; ++w) {
-    if ((rc = make_plan(window_offsets + w, 1, t, &plans[size_t(w)])) != NSGC_OK) return rc;
+    if ((rc = make_plan(window_offsets + w, 1, t, &plans[size_t(w)], false, true, allow_grid)) != NSGC_OK) return rc;
     at[size_t(w)] = pbytes;
     pbytes += (plans[size_t(w)].plan_bytes() + 255) / 256 * 256;
     wsmax = std::max(wsmax, plans[size_t(w)].layout().total);
@@ -637,9 +648,11 @@ int reserve_call(int64_t max_packets, int64_t max_windows, hipStream_t s) {
   std::lock_guard<std::mutex> lock(sl->mu);
   const size_t pb = plan_bound(max_packets, max_windows, cc.t);
   if ((rc = ensure_device(&sl->plan_dev, &sl->plan_cap, pb, s)) != NSGC_OK) return rc;
-  if ((rc = ensure_device(&sl->ws, &sl->ws_cap, workspace_bound(max_packets, max_windows, cc.t), s)) !=
-      NSGC_OK)
-    return rc;
+  const size_t ws = workspace_bound(max_packets, max_windows, cc.t);
+  rc = ensure_device(&sl->ws, &sl->ws_cap, ws, s);
+  if (rc == NSGC_ERR_NO_MEMORY)   // calls then do without grid windows where they do not fit
+    rc = ensure_device(&sl->ws, &sl->ws_cap, ws - grid_workspace_bound(max_packets, max_windows, cc.t), s);
+  if (rc != NSGC_OK) return rc;
   for (int k = 0; k < kStages; ++k) {
     int idx = 0;
     if ((rc = take_stage(sl, pb, s, &idx)) != NSGC_OK) return rc;
@@ -763,7 +776,10 @@ int nsgc_window_stats(const uint32_t* src, const uint32_t* dst, const int64_t* w
   CallCtx cc;
   if ((rc = begin_call(s, &cc)) != NSGC_OK) return rc;
   std::lock_guard<std::mutex> lock(cc.sl->mu);
-  if (cc.plain) return plain_locked(cc, src, dst, window_offsets, num_windows, out_stats, s);
+  if (cc.plain)
+    return with_or_without_grid([&](bool grid) {
+      return plain_locked(cc, src, dst, window_offsets, num_windows, out_stats, s, grid);
+    });
   return batched_locked(cc, src, dst, window_offsets, num_windows, out_stats, s);
 }
 
@@ -777,7 +793,9 @@ int nsgc_window_stats_plain(const uint32_t* src, const uint32_t* dst,
   CallCtx cc;
   if ((rc = begin_call(s, &cc)) != NSGC_OK) return rc;
   std::lock_guard<std::mutex> lock(cc.sl->mu);
-  return plain_locked(cc, src, dst, window_offsets, num_windows, out_stats, s);
+  return with_or_without_grid([&](bool grid) {
+    return plain_locked(cc, src, dst, window_offsets, num_windows, out_stats, s, grid);
+  });
 }
 
 namespace {
@@ -805,24 +823,27 @@ int entities_call(const uint32_t* src, const uint32_t* dst, const int64_t* windo
   CallCtx cc;
   if ((rc = begin_call(s, &cc, true)) != NSGC_OK) return rc;
   std::lock_guard<std::mutex> lock(cc.sl->mu);
-  HostPlan hp;
-  // (the grid counts entities; the lists come from the other form)
-  if ((rc = make_plan(window_offsets, num_windows, cc.t, &hp, true, true, !list_off)) != NSGC_OK) return rc;
-  hp.ent_cur.assign(size_t(num_windows) * 3, 0);
-  hp.ent_end.assign(size_t(num_windows) * 3, 0);
-  if (list_off) {
-    for (int64_t w = 0; w < num_windows; ++w)
-      for (int k = 0; k < 3; ++k) {
-        hp.ent_cur[size_t(w) * 3 + k] = uint64_t(list_off[k][w]);
-        hp.ent_end[size_t(w) * 3 + k] = uint64_t(list_off[k][w + 1]);
-      }
-    hp.ent_links = lists[0];
-    hp.ent_src = lists[1];
-    hp.ent_dst = lists[2];
-  }
-  hp.ent_counts = counts;
-  if (!hp.win.empty() && (cc.L.grid_rce[0] == 0 || cc.L.grid_rce[1] == 0)) return NSGC_ERR_INVALID_ARG;
-  return run_plan(cc.c, cc.sl, hp, cc.L, src, dst, nullptr, s);
+  return with_or_without_grid([&](bool grid) {
+    HostPlan hp;
+    // (the grid counts entities; the lists come from the other form)
+    const int e = make_plan(window_offsets, num_windows, cc.t, &hp, true, true, grid && !list_off);
+    if (e != NSGC_OK) return e;
+    hp.ent_cur.assign(size_t(num_windows) * 3, 0);
+    hp.ent_end.assign(size_t(num_windows) * 3, 0);
+    if (list_off) {
+      for (int64_t w = 0; w < num_windows; ++w)
+        for (int k = 0; k < 3; ++k) {
+          hp.ent_cur[size_t(w) * 3 + k] = uint64_t(list_off[k][w]);
+          hp.ent_end[size_t(w) * 3 + k] = uint64_t(list_off[k][w + 1]);
+        }
+      hp.ent_links = lists[0];
+      hp.ent_src = lists[1];
+      hp.ent_dst = lists[2];
+    }
+    hp.ent_counts = counts;
+    if (!hp.win.empty() && (cc.L.grid_rce[0] == 0 || cc.L.grid_rce[1] == 0)) return int(NSGC_ERR_INVALID_ARG);
+    return run_plan(cc.c, cc.sl, hp, cc.L, src, dst, nullptr, s);
+  });
 }
 
 }  // namespace
@@ -889,11 +910,10 @@ int nsgc_window_stats_timed(const uint32_t* src, const uint32_t* dst,
   if ((rc = begin_call(s, &cc)) != NSGC_OK) return rc;
   Slot* sl = cc.sl;
   std::lock_guard<std::mutex> lock(sl->mu);
-  HostPlan hp;
-  if ((rc = make_plan(window_offsets, num_windows, cc.t, &hp)) != NSGC_OK) return rc;
   for (int i = 0; i < 6; ++i)
     if (!sl->phase_ev[i]) NSGC_HIP(hipEventCreate(&sl->phase_ev[i]));
-  if ((rc = run_plan(cc.c, sl, hp, cc.L, src, dst, out_stats, s, sl->phase_ev)) != NSGC_OK) return rc;
+  if ((rc = batched_locked(cc, src, dst, window_offsets, num_windows, out_stats, s, sl->phase_ev)) != NSGC_OK)
+    return rc;
   NSGC_HIP(hipEventSynchronize(sl->phase_ev[5]));
   for (int i = 0; i < 5; ++i)
     NSGC_HIP(hipEventElapsedTime(&phase_ms[i], sl->phase_ev[i], sl->phase_ev[i + 1]));
@@ -1040,6 +1060,7 @@ struct nsgc_graph {
   nsgc_tune tune;
   Launch L;
   int64_t max_packets = 0, max_windows = 0;
+  bool grid = true;   // grid windows are planned (the workspace for them was to be had)
   hipStream_t capture = nullptr;
   struct Captured {
     hipGraph_t graph = nullptr;
@@ -1143,9 +1164,13 @@ int nsgc_graph_create(int64_t max_packets, int64_t max_windows, nsgc_graph** out
       return hip_fail(e);
     }
   }
-  if ((rc = ensure_device(&g->ws, &g->ws_cap,
-                          workspace_bound(max_packets, max_windows, g->tune, false),
-                          g->capture)) != NSGC_OK) {
+  const size_t ws = workspace_bound(max_packets, max_windows, g->tune, false);
+  rc = ensure_device(&g->ws, &g->ws_cap, ws, g->capture);
+  if (rc == NSGC_ERR_NO_MEMORY) {
+    g->grid = false;
+    rc = ensure_device(&g->ws, &g->ws_cap, ws - grid_workspace_bound(max_packets, max_windows, g->tune), g->capture);
+  }
+  if (rc != NSGC_OK) {
     destroy_graph(g);
     return rc;
   }
@@ -1167,7 +1192,7 @@ int nsgc_graph_launch(nsgc_graph* g, const uint32_t* src, const uint32_t* dst,
   NSGC_HIP(hipGetDevice(&dev));
   if (dev != g->device) return NSGC_ERR_INVALID_ARG;
   HostPlan hp;   // a captured graph has no large-window tier (its launches are fixed)
-  if ((rc = make_plan(window_offsets, num_windows, g->tune, &hp, false, false)) != NSGC_OK)
+  if ((rc = make_plan(window_offsets, num_windows, g->tune, &hp, false, false, g->grid)) != NSGC_OK)
     return rc;
   if (hp.plan_bytes() > g->inst[0].plan_cap) return NSGC_ERR_INTERNAL;
   const size_t need = hp.layout().total;
