@@ -148,7 +148,8 @@ int nsgc_window_stats_timed(const uint32_t* src, const uint32_t* dst,
  * packet of the windows above 1024 packets, so batches of up to roughly
  * 5.2 million such packets fit; a batch that does not fit returns
  * NSGC_ERR_TOO_LARGE with nothing enqueued (nsgc_plan_sizes tells the plan
- * and workspace bytes of a batch beforehand).  All calls on one GPU share
+ * and workspace bytes of a batch beforehand; one whose grid windows do not
+ * fit is planned again without them, so up to a tenth more may still fit).  All calls on one GPU share
  * its array, which keeps the last call's contents (each call rewrites what
  * it reads).  Overlapping calls would race on it, so the library serialises
  * them: a call on another stream than the previous call waits on the device
@@ -191,6 +192,21 @@ int nsgc_release(void);
  * with 2^k <= packets < 2^(k+1); class 0 also holds empty windows).
  * Every setting gives identical statistics (max_sweeps_log2 below its
  * default aside); only speed changes.
+ *
+ * Windows above small_max take one of three forms.  With wave_target > 0,
+ * combine_probes 0 and row_complete 0, those of up to min(8 small_max, 8192)
+ * packets are computed whole by one workgroup each, and longer ones whose
+ * targets and caps give them at least four row and four column buckets are
+ * partitioned into the cells of a grid of row strips by column strips; beside
+ * grid windows some of the former take the grid too.  All others have one link
+ * bucket per hash range (row_complete windows, too, unless they would run one
+ * workgroup per bucket).  Of the knobs below the grid reads tile_log2 (windows
+ * of more than 1024 cells take 14; small batches less, and more where the
+ * kernels need it), rc_slots_log2, max_link_buckets_log2 (caps the cells, at
+ * 2^11), max_sweeps_log2, wave_target (four times as many packets per cell) and
+ * row_target and col_target (up to 4096 packets per bucket);
+ * link_target, link_slots_log2, blocks_per_cu and, but for the four buckets,
+ * max_rc_buckets_log2 matter to the third form only.
  */
 typedef struct nsgc_tune_class {
   int32_t link_target;      /* packets per link bucket (sets the bucket count) */
@@ -257,9 +273,12 @@ int nsgc_default_tune(nsgc_tune* out);
 /*
  * Host-only planner inspection (no device work, usable without a GPU).
  * Plans num_windows windows under the current tuning and writes, per window,
- * the tier (0 = empty, 1 = small/LDS, 2 = partitioned), the log2 bucket
- * counts (link, row, column) and the number of partition tiles, plus the
- * workspace bytes the batch needs.  Any output pointer may be NULL.
+ * the tier (0 = empty, 1 = small/LDS, 2 = above small_max, 3 = large), and for
+ * tier 2 the log2 bucket counts (link, row, column) and the number of partition
+ * tiles that the targets and caps give the form with one link bucket per hash
+ * range: windows that are computed whole or on the grid (see nsgc_tune) are
+ * reported alike, though they run otherwise.  workspace_bytes is what the batch
+ * as it runs needs.  Any output pointer may be NULL.
  */
 int nsgc_plan_inspect(const int64_t* window_offsets, int64_t num_windows,
                       int32_t* tier, int32_t* log2_link_buckets,
@@ -369,7 +388,7 @@ int nsgc_window_entities(const uint32_t* src, const uint32_t* dst,
  * anon_src, anon_dst: DEVICE outputs of num_packets uint32 (they may be src
  * and dst themselves); num_addresses: DEVICE pointer to one uint64 that
  * receives N.  Asynchronous on `stream`; argument errors are reported
- * synchronously with nothing enqueued.  The workspace (about 48 bytes per
+ * synchronously with nothing enqueued.  The workspace (about 36 bytes per
  * packet) comes from the stream's pool, as for nsgc_window_stats.  Not
  * usable under stream capture.
  */

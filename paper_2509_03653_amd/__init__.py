@@ -345,7 +345,10 @@ def set_tune(t: Tune):
 
 
 def plan_inspect(offsets) -> dict:
-    """Host-only view of the planner's decisions for a batch (no GPU needed)."""
+    """Host-only view of the planner's decisions for a batch (no GPU needed).
+    The bucket counts and tiles are those of the form with one link bucket per
+    hash range, which most windows do not take under the default tuning (see
+    nsgc_plan_inspect and nsgc_tune in include/nsgc.h)."""
     off = _offsets(offsets)
     w = len(off) - 1
     n = max(w, 1)

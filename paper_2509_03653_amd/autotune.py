@@ -32,8 +32,9 @@ import paper_2509_03653_amd as nsgc
 # batch (the other classes keep their defaults): link_scale the link target,
 # rc_scale the row and column targets, and row_scale the row target once more
 # (sources often repeat more than destinations, so their buckets can be
-# larger: on 64 windows of 2^17 Zipf packets, rows of 8192 packets against
-# columns of 4096 make phase C 6 us faster, where larger columns overflow).
+# larger).  While windows take the grid, as they do by default, blocks_per_cu,
+# link_slots_log2, link_scale and targets above 4096 packets change nothing
+# (include/nsgc.h); with wave_target 0 or combine_probes they do.
 SPACE = (
     ("blocks_per_cu", (1, 2, 3, 4)),
     ("link_slots_log2", (11, 12)),

@@ -158,7 +158,9 @@ void default_tune(nsgc_tune* t) {
   // measured 0.03-0.1 distinct ids per packet), and the larger phase-C items
   // and longer phase-B segments measured 11% faster per batch than twice as
   // many buckets.  Windows below 2^19 packets keep the smaller buckets, which
-  // measured faster there.
+  // measured faster there.  (That is for one link bucket per hash range; grid
+  // windows take buckets of up to 4096 packets and cells of four wavefront
+  // targets.)
   for (int k = 0; k <= 32; ++k) {
     nsgc_tune_class& c = t->cls[k];
     c.link_target = k < 19 ? 2048 : k < 23 ? 4096 : 8192;
