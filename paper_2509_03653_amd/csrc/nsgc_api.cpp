@@ -231,8 +231,8 @@ struct Launch {
   uint32_t max_link_buckets, max_rc_buckets;
   // grid windows: heavy sample, partition by tile size (2^11 ..), link
   // aggregation of small / big cells, row/column aggregation
-  uint32_t gheavy, gpart[4], glinks[2], gwhole[NSGC_WHOLE], gwide, gover, grounds, grc, gent;
-  size_t lds_grc;
+  uint32_t gheavy, gpart[4], glinks[2], gwhole[NSGC_WHOLE], gwide, gover, grc, gent;
+  size_t lds_grc, lds_gsw;
 };
 
 constexpr int kGridKernels = 16;   // kernel numbers of nsgc_grid.hip start here, eight on nsgc_whole.hip's
@@ -286,11 +286,12 @@ int launch_params(DevCtx* c, const nsgc_tune& t, Launch* out) {
         return rc;
   // grid windows: as many workgroups as fit (their kernels are sized for it)
   L.lds_grc = lds_grid_rc_bytes(uint32_t(t.rc_slots_log2));
-  if (std::max(L.lds_grc, lds_grid_part_bytes(14, grid_max_cells(14))) > c->lds_limit) return NSGC_ERR_INVALID_ARG;
+  L.lds_gsw = lds_grid_sweep_bytes(uint32_t(t.rc_slots_log2));
+  if (std::max(std::max(L.lds_grc, L.lds_gsw), lds_grid_part_bytes(14, grid_max_cells(14))) > c->lds_limit)
+    return NSGC_ERR_INVALID_ARG;
   L.gheavy = uint32_t(c->cus) * 2;
   L.gwide = uint32_t(c->cus);
-  L.gover = uint32_t(c->cus) * 3;
-  L.grounds = uint32_t(c->cus);
+  L.gover = uint32_t(c->cus);
   for (uint32_t k = 0; k < 4; ++k)
     if ((rc = resident_cap(c, kGridKernels, 11 + k, lds_grid_part_bytes(11 + k, grid_max_cells(11 + k)), 16,
                            &L.gpart[k])) != NSGC_OK)
@@ -381,7 +382,7 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
   // what these leave over is known on the device only: small persistent grids
   // (small cells alone are left over too seldom to be worth the wide pass)
   if (gbig) NSGC_HIP(launch_grid_links(dplan, 2, grid(hp.gitemsB, L.gwide), s));
-  if (gsmall || gbig) NSGC_HIP(launch_grid_rounds(dplan, gbig, grid(hp.gitemsB, L.grounds), s));
+  if (gsmall || gbig) NSGC_HIP(launch_grid_rounds(dplan, gbig, grid(hp.gitemsB, L.gover), s));
   // The phase-C order depends only on the partition's sizes: with wavefront
   // phase-B items it is computed by an extra workgroup of that kernel, beside
   // phase B, instead of by k_order after it.
@@ -401,7 +402,7 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
     NSGC_HIP(launch_grid_ent(dplan, grid(hp.gitemsC, L.gent), s));
   } else if (gsmall || gbig) {
     NSGC_HIP(launch_grid_rowcol(dplan, grid(hp.gitemsC, L.grc), L.lds_grc, s));
-    NSGC_HIP(launch_grid_sweeps(dplan, grid(hp.gitemsC, L.gover), L.lds_grc, s));
+    NSGC_HIP(launch_grid_sweeps(dplan, grid(hp.gitemsC, L.gover), L.lds_gsw, s));
   }
   if (part && hp.entity) {
     const int k = hp.ent_links || hp.ent_src || hp.ent_dst ? 1 : 0;
@@ -416,7 +417,7 @@ int enqueue_kernels(const HostPlan& hp, const nsgc_dev_plan* dplan, const Launch
   if (!hp.large.empty()) {
     if (!la) return NSGC_ERR_INTERNAL;
     char* region = la->ws + hp.layout().large;
-    const LargeGridLaunch lg = {la->grid / 8, L.glinks[1], L.gwide, L.gover, L.grounds, L.grc, L.lds_grc,
+    const LargeGridLaunch lg = {la->grid / 8, L.glinks[1], L.gwide, L.gover, L.grc, L.gover, L.lds_grc, L.lds_gsw,
                                 hp.rc_slots_log2};
     for (const LargeWindow& lw : hp.large) {
       const uint32_t* src = la->src + lw.in_begin;

@@ -37,8 +37,8 @@ namespace {
 
 constexpr uint32_t HVM = NSGC_GRID_HEAVY;   // most dominant addresses per view
 
-// Find-or-insert of U keys per lane in an open-addressing LDS table (linear
-// probing): the home slots of all U are tried together, then the keys still
+// Find-or-insert of U keys per lane in an open-addressing LDS table (probed like
+// probe_on): the home slots of all U are tried together, then the keys still
 // without a slot probe on in step, a key's turn being skipped when no lane
 // needs it.  slot[u] comes in as the home slot and goes out as the key's slot;
 // fr[u]: this call inserted the key.  Call with the whole wavefront active;
@@ -71,7 +71,7 @@ __device__ __forceinline__ bool insert_keys(K* tk, uint32_t mask, const K (&key)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (todo[u]) {
-        slot[u] = (slot[u] + 1) & mask;
+        slot[u] = (slot[u] + probe_step(key[u])) & mask;
         old[u] = cas(slot[u], key[u]);
       }
     }
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
           uint32_t s = home(key[u]);
           u64 cur = tk[s];
           for (uint32_t p = 1; cur != key[u] && cur != EMPTY64 && p < NSGC_MAX_PROBES; ++p) {
-            s = (s + 1) & uint32_t(SL - 1);
+            s = (s + probe_step(key[u])) & uint32_t(SL - 1);
             cur = tk[s];
           }
           if (cur == key[u]) {
@@ -1300,16 +1300,27 @@ __device__ __forceinline__ u64 bucket_record(const nsgc_grid_desc& W, const Buck
   return u64(cell) * ((1u << (W.logR - W.logA)) + (1u << (W.logC - W.logBc)) + 3u);
 }
 
-// The buckets that phase C's single pass listed as too large for it, by sweeps
-// over their ids by the bits that follow the bucket's.
-__global__ __launch_bounds__(GC_NT) void k_grid_sweeps(nsgc_dev_plan* P) {
+// The buckets that phase C's single pass listed as too large for it: in a table
+// twice as large, one workgroup of 1024 threads per compute unit, and beyond that
+// by sweeps over their ids by the bits that follow the bucket's.  (Where every
+// address is met once, all buckets come here.)
+constexpr int GS_NT = 1024;
+__host__ __device__ constexpr uint32_t sweep_slots_log2(uint32_t slots_log2) {
+  return slots_log2 < 12 ? slots_log2 + 1 : 13u;
+}
+
+size_t lds_grid_sweep_bytes(uint32_t slots_log2) {
+  return (size_t(12) << sweep_slots_log2(slots_log2)) + (3 * (GS_NT / 64) + 16) * 4;
+}
+
+__global__ __launch_bounds__(GS_NT) void k_grid_sweeps(nsgc_dev_plan* P) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int NT = GC_NT, NW = NT / 64;
-  const uint32_t S = 1u << sload(&P->rc_slots_log2);
+  constexpr int NT = GS_NT, NW = NT / 64;
+  const uint32_t S = 1u << sweep_slots_log2(sload(&P->rc_slots_log2));
   u64* tv = reinterpret_cast<u64*>(smem);
   uint32_t* tk = reinterpret_cast<uint32_t*>(tv + S);
   uint32_t* red = tk + S;    // [3 * NW]
-  uint32_t* misc = red + 32;
+  uint32_t* misc = red + 3 * NW;
   const uint32_t tid = threadIdx.x;
   const uint32_t items = P->gover[1], HV = NSGC_GRID_HV(sload(&P->gtile_log2));
   for (uint32_t x = blockIdx.x; x < items; x += gridDim.x) {
@@ -1539,7 +1550,7 @@ __global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void
         for (int j0 = 0; j0 < E; j0 += 4) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) at[j0 + u] = NO_SLOT;
-          if (uint32_t(j0) < kmax) {
+          if (uint32_t(j0) < kmax && !lds_load(&misc[0])) {   // (a pass that failed is thrown away)
             uint32_t id[4], lo[4], old[4], s[4];
             bool ok[4];
 #pragma unroll
@@ -1569,7 +1580,6 @@ __global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void
                 const uint32_t o = probe_on<uint32_t>(tk, S - 1, id[u], old[u], s[u]);
                 if (o == EMPTY32) at[j0 + u] = s[u];
                 else if (o != id[u]) misc[0] = 1;
-                // (a pass that failed is thrown away)
                 lds_add64(&tv[s[u]], (u64(lo[u] >> NSGC_ENT_PACKET_BITS) << 32) | (lo[u] & ENT_PMAX));
               }
             }
@@ -1886,7 +1896,7 @@ hipError_t launch_grid_rounds(const nsgc_dev_plan* P, bool after_wide, uint32_t 
 }
 
 hipError_t launch_grid_sweeps(const nsgc_dev_plan* P, uint32_t grid, size_t lds, hipStream_t s) {
-  hipLaunchKernelGGL(k_grid_sweeps, dim3(grid), dim3(GC_NT), lds, s, const_cast<nsgc_dev_plan*>(P));
+  hipLaunchKernelGGL(k_grid_sweeps, dim3(grid), dim3(GS_NT), lds, s, const_cast<nsgc_dev_plan*>(P));
   return hipGetLastError();
 }
 

@@ -13,6 +13,7 @@ namespace nsgc {
 
 size_t lds_grid_part_bytes(uint32_t tile_log2, uint32_t max_cells);
 size_t lds_grid_rc_bytes(uint32_t slots_log2);
+size_t lds_grid_sweep_bytes(uint32_t slots_log2);
 
 // Workgroups per compute unit that can be resident.  which: 0 partition (by
 // tile_log2), 1 / 2 link aggregation of small / big cells, 3 row/column

@@ -544,7 +544,7 @@ hipError_t large_grid_stats(const uint32_t* src, const uint32_t* dst, unsigned l
   hipLaunchKernelGGL(k_large_reduce, dim3(OUT), dim3(512), 0, s, A);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_grid_rowcol(A.whole, L.rowcol, L.lds_rowcol, s)) != hipSuccess) return e;
-  if ((e = launch_grid_sweeps(A.whole, L.over, L.lds_rowcol, s)) != hipSuccess) return e;
+  if ((e = launch_grid_sweeps(A.whole, L.sweeps, L.lds_sweeps, s)) != hipSuccess) return e;
   return launch_grid_finish(A.whole, s);
 }
 

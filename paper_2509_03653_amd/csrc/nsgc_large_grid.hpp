@@ -11,8 +11,8 @@ namespace nsgc {
 
 // Persistent grids and table size of the kernels it shares with the grid windows.
 struct LargeGridLaunch {
-  uint32_t cus, links, wide, over, rounds, rowcol;
-  size_t lds_rowcol;
+  uint32_t cus, links, wide, rounds, rowcol, sweeps;
+  size_t lds_rowcol, lds_sweeps;
   uint32_t rc_slots_log2;
 };
 

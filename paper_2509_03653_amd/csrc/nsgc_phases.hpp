@@ -18,12 +18,18 @@ __host__ __device__ constexpr int array_len() {
 // the keys into sweeps, so giving up never changes a result.
 constexpr uint32_t NSGC_MAX_PROBES = 64;
 
+// The tables of the grid's phases and of the entity outputs are probed in steps
+// of an odd number that the key decides, from bits that neither its bucket nor its
+// home slot takes.  (Consecutive slots would form chains: a table of 4096 slots
+// has one of more than 64 from three fifths full on, against nine tenths.)
+__device__ __forceinline__ uint32_t probe_step(u64 link) { return (uint32_t(link >> 45) ^ (uint32_t(link) >> 13)) | 1u; }
+__device__ __forceinline__ uint32_t probe_step(uint32_t id) { return (id >> 12) | 1u; }
+
 // Second half of a find-or-insert of one key per lane in an open-addressing
-// LDS table (linear probing): `old` is what the compare-and-swap on the home
-// slot returned, `slot` goes in as the home slot and out as the slot last
-// tried.  Returns what that slot held: the table's marker if the key was
-// inserted, the key if it was there, anything else if it found no place within
-// `most` probes.
+// LDS table: `old` is what the compare-and-swap on the home slot returned, `slot`
+// goes in as the home slot and out as the slot last tried.  Returns what that
+// slot held: the table's marker if the key was inserted, the key if it was there,
+// anything else if it found no place within `most` probes.
 // (Plain values, no flags: flags carried through a divergent loop cost scalar
 // instructions per step.)
 template <class K>
@@ -31,7 +37,7 @@ __device__ __forceinline__ K probe_on(K* tk, uint32_t mask, K key, K old, uint32
                                       uint32_t most = NSGC_MAX_PROBES) {
   constexpr K EMPTY = K(~K(0));
   for (uint32_t left = most - 1; old != EMPTY && old != key && left; --left) {
-    slot = (slot + 1) & mask;
+    slot = (slot + probe_step(key)) & mask;
     if constexpr (sizeof(K) == 8) old = lds_cas64(reinterpret_cast<u64*>(tk) + slot, EMPTY64, key);
     else old = lds_cas32(reinterpret_cast<uint32_t*>(tk) + slot, EMPTY32, key);
   }

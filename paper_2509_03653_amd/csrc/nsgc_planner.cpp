@@ -37,6 +37,9 @@ int whole_size(uint64_t n) {
   return n <= NSGC_WHOLE_A ? 0 : n <= NSGC_WHOLE_B ? 1 : n <= NSGC_WHOLE_C ? 2 : 3;
 }
 
+// Packets of a row or column bucket of the entity lists, at most.
+constexpr uint64_t kListBucket = 1740;
+
 // Workgroups of each size that 256 compute units hold at once.
 constexpr size_t kWholeRound[NSGC_WHOLE] = {6144, 1536, 768, 256};
 
@@ -274,6 +277,14 @@ int make_plan(const int64_t* offsets, int64_t num_windows, const nsgc_tune& tune
     d.logR = uint8_t(std::min(ceil_log2((n + uint64_t(tc.row_target) - 1) / uint64_t(tc.row_target)), capRC));
     d.logC = uint8_t(std::min(ceil_log2((n + uint64_t(tc.col_target) - 1) / uint64_t(tc.col_target)), capRC));
     if (entity) d.logR = d.logC = std::max(d.logR, d.logC);   // merged phase-C items
+    if (entity && !allow_grid) {
+      // The lists' table of 4096 slots holds the addresses of both views, as many
+      // as packets and more where all are distinct: buckets of up to 1740 packets
+      // (of 4096 it takes several sweeps, twice; see k_rowcol_ent), as far as a
+      // wavefront's counters go.
+      const int fine = ceil_log2((n + kListBucket - 1) / kListBucket);
+      d.logR = d.logC = uint8_t(std::max<int>(d.logR, std::min({fine, capRC, ceil_log2(NSGC_WAVE_MAX_RC)})));
+    }
     // one wavefront per link bucket when the window's buckets fit its tables
     if (tc.wave_target > 0 && (1u << d.logR) <= NSGC_WAVE_MAX_RC && (1u << d.logC) <= NSGC_WAVE_MAX_RC) {
       const int lw = ceil_log2((n + uint64_t(tc.wave_target) - 1) / uint64_t(tc.wave_target));
