@@ -572,7 +572,8 @@ __device__ __forceinline__ void publish_starts(NSGC_GLOBAL uint32_t* rec, const 
 // keys, or whose table was full after less than one key in GR_ROUNDS, is sorted
 // instead: eight passes over its keys whatever they are (cells are chosen by the
 // top bits of the hashed addresses, so traffic can be made that puts a whole
-// window in one).
+// window in one).  Sorting 2^16 keys takes as long as three or four rounds, but
+// links that repeat need fewer rounds than the first one lets expect.
 // One workgroup of 1024 threads with 8192 slots per compute unit: against two of
 // 512 with 4096, one window of 2^26 packets among 4096 addresses (8192 links in
 // each cell) takes 3.8 ms instead of 6.2, one of 2^25 2.3 instead of 3.2.
@@ -581,7 +582,7 @@ __device__ __forceinline__ void publish_starts(NSGC_GLOBAL uint32_t* rec, const 
 constexpr int GR_NT = 1024;
 constexpr int GR_SL = 8192;
 constexpr uint32_t GR_FULL = GR_SL * 3 / 4;   // links in the table when no more are taken
-constexpr uint32_t GR_ROUNDS = 12;
+constexpr uint32_t GR_ROUNDS = 6;
 constexpr uint32_t GR_KEYS = 1u << 16;
 
 // The n keys that `each` visits (in any order) into `a` in ascending order, by way of `b`: a radix sort by bytes.
@@ -1582,6 +1583,14 @@ __global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void
                 else if (o != id[u]) misc[0] = 1;
                 lds_add64(&tv[s[u]], (u64(lo[u] >> NSGC_ENT_PACKET_BITS) << 32) | (lo[u] & ENT_PMAX));
               }
+            }
+            // entries for more than 15/16 of the table and hardly an id met twice yet:
+            // it will overflow
+            if (j0 == 0 && total > S - S / 16) {
+              uint32_t fresh = 0;
+#pragma unroll
+              for (int u = 0; u < 4; ++u) fresh += __popcll(__ballot(at[u] != NO_SLOT));
+              if (fresh > 4 * 64 - 4) misc[0] = 1;
             }
           }
         }
