@@ -138,7 +138,6 @@
 #define NSGC_GRID_MAX_SUB_LOG2 6               // row or column buckets per strip
 #define NSGC_GRID_MAX_SUB (1 << NSGC_GRID_MAX_SUB_LOG2)
 #define NSGC_GRID_BUCKET 4096                  // packets per row or column bucket, at most
-#define NSGC_GRID_GROUP 16384                  // packets per phase-C item of large windows
 // Phase-C items of a window's dominant addresses: 16 of one view each, and one
 // for the links between them.
 #define NSGC_GRID_CITEMS(hv) ((hv) / 8 + 1)
