@@ -313,7 +313,7 @@ int nsgc_large_window_counts(int64_t* by_grid, int64_t* by_sorting);
  * launch to finish (the two instances share one workspace).  This is the
  * form to use inside a caller's own stream capture: nsgc_graph_launch is not
  * itself capturable (it plans on the host), but its work is one graph
- * launch per call.
+ * launch per call (one kernel launch for a batch of a few short windows).
  */
 typedef struct nsgc_graph nsgc_graph;
 int nsgc_graph_create(int64_t max_packets, int64_t max_windows, nsgc_graph** out);
