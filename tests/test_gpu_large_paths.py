@@ -43,7 +43,7 @@ def heavy_tailed(rng, n):
 
 
 @pytest.mark.parametrize("draw", [even, few, heavy_tailed])
-@pytest.mark.parametrize("n", [1 << 20, (1 << 20) + 16385, 2560 << 10, (2560 << 10) + 1, 5000011, (1 << 24) + 77])
+@pytest.mark.parametrize("n", [1 << 20, (1 << 20) + 16385, (2560 << 10) + 1, 5000011])
 def test_ordinary_traffic_is_partitioned(n, draw):
     rng = np.random.default_rng(n)
     assert taken(draw(rng, n), draw(rng, n), draw.__name__) == (1, 0)
