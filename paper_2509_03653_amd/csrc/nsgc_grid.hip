@@ -17,10 +17,13 @@
 // in LDS during the partition.
 //
 // Measured against that path, whole calls: 64 windows of 2^17 packets 237 ->
-// 208 us; one of 40013 packets 58 -> 45 us; nine of 2^12 .. 2^22 packets 434 ->
-// 184 us; 512 of 2^10 .. 2^23 packets 11.5 -> 7.2 ms; 128 of 2^23 14.2 -> 9.6
-// ms.  From 2^13 packets on no traffic mix was slower on the grid (two windows
-// of 10^4 packets 60 -> 53 us), and one link bucket holds smaller windows.
+// 202 us; one of 40013 packets 58 -> 39 us; nine of 2^12 .. 2^22 packets 434 ->
+// 171 us; 512 of 2^10 .. 2^23 packets 11.5 -> 7.1 ms; 128 of 2^23 14.2 -> 9.5
+// ms; one of 2^20 with all addresses distinct 680 -> 128 us, among 4096 152 ->
+// 92.  Slower is a window of 2^20 to 2^22 packets among a hundred to a thousand
+// addresses, whose few links one link bucket per range counts in fewer launches
+// (one of 2^20 among 300 56 -> 85 us, eight 150 -> 178; among 2000 150 -> 94).
+// Windows of up to 2^13 packets have one workgroup each.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -145,7 +148,7 @@ __device__ __forceinline__ void loads_arrived() { __builtin_amdgcn_s_waitcnt(0x0
 // addresses were left out, now and then a very frequent one, whose strip then
 // overfilled (128 skewed windows of 2^23 packets 10.1 -> 9.6 ms).  The matrix
 // starts at zero.  One trip to memory and a dozen barriers: bound by latency,
-// 4.5 us for one window and 8.2 us for 64.
+// 5 us for one window and 8.7 us for 64.
 // ---------------------------------------------------------------------------
 
 constexpr uint32_t GH_NT = 1024;
@@ -255,8 +258,8 @@ __global__ __launch_bounds__(GH_NT) void k_grid_heavy(const nsgc_dev_plan* __res
 // contiguous run of tiles, so that it adds its part of a window's dominant
 // matrix to memory once per window and not once per tile.  The next tile's
 // packets are loaded while the current one's keys are written.  Moves 8 bytes
-// per packet in and up to 8 out: 2^23 packets (64 windows) in 34 us, 2^30 (128
-// windows, 2048 cells) in 3.9 ms, 3.3 TB/s of the copy rate's 5.1; LDS counting
+// per packet in and up to 8 out: 2^23 packets (64 windows) in 37 us, 2^30 (128
+// windows, 2048 cells) in 3.8 ms, 3.4 TB/s of the copy rate's 5.1; LDS counting
 // and placing, one workgroup of 1024 per compute unit, is the rest.
 // ---------------------------------------------------------------------------
 
@@ -517,7 +520,7 @@ __device__ __forceinline__ uint32_t spread_by_wave(uint32_t tid, uint32_t n, uin
 // five (BIG: three) workgroups per compute unit and by loading the next item's
 // records and asking for the one after it during the current one.  Keys stay in
 // registers from the insert to the emission: reading them again, or the table,
-// is another trip through LDS for every slot.  64 windows of 2^17 packets in 77
+// is another trip through LDS for every slot.  64 windows of 2^17 packets in 76
 // us against 94 us with a wavefront per link bucket; 128 of 2^23 in 3.8 ms
 // against 8.4 ms with a workgroup per link bucket.  Measured and not taken: all
 // four home slots probing on in step (88 us), entries staged in LDS and copied
@@ -965,10 +968,10 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
 // The phase in three sizes: SMALL and BIG for windows of smaller and of larger
 // cells, and WIDE for the cells that the others listed as too large for them and
 // for windows whose cells have more packets on average than BIG's threads hold,
-// with three times the keys and twice the table (one workgroup per compute unit).  Cells
-// that SMALL or WIDE list go to k_grid_rounds.  Sixteen windows of 2^23 packets
-// among 4096 addresses, half of whose cells overflow BIG, took 8.2 ms without
-// WIDE and take 3.8 ms with it.
+// with three times the keys and twice the table (one workgroup per compute unit).
+// Cells that SMALL or WIDE list go to k_grid_rounds.  Sixteen windows of 2^23
+// packets among 4096 addresses, half of whose cells overflow BIG, took 8.2 ms
+// without WIDE and take 3.7 ms with it.
 enum GridCells { SMALL, BIG, WIDE };
 
 template <int NT, int SL, int E, GridCells KIND>
@@ -1248,7 +1251,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == WIDE
 // Phase C: the sources of one row bucket (or the destinations of one column
 // bucket, or a few neighbouring buckets).  A few more items per window add up
 // its dominant addresses.  Like phase B one pass over keys in registers, bound
-// by the same chain: 64 windows of 2^17 packets in 66 us against 81 us with one
+// by the same chain: 64 windows of 2^17 packets in 62 us against 81 us with one
 // segment per link bucket.
 // ---------------------------------------------------------------------------
 
@@ -1303,8 +1306,9 @@ __device__ __forceinline__ u64 bucket_record(const nsgc_grid_desc& W, const Buck
 
 // The buckets that phase C's single pass listed as too large for it: in a table
 // twice as large, one workgroup of 1024 threads per compute unit, and beyond that
-// by sweeps over their ids by the bits that follow the bucket's.  (Where every
-// address is met once, all buckets come here.)
+// by sweeps over their ids by the bits that follow the bucket's.  Where every
+// address is met once all buckets come here: those of 64 windows of 2^17 packets
+// in 0.27 ms, against 0.7 ms by sweeps with k_grid_rowcol's table.
 constexpr int GS_NT = 1024;
 __host__ __device__ constexpr uint32_t sweep_slots_log2(uint32_t slots_log2) {
   return slots_log2 < 12 ? slots_log2 + 1 : 13u;
@@ -1650,8 +1654,8 @@ __global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void
 // In sweeps over the ids, streaming the entries, where a bucket has more
 // entries than the threads hold or more ids than the table.  Bound by its chain
 // like k_grid_rowcol; nothing but marks is kept, so the table costs 49 KB.
-// Counts of 64 windows of 2^17 packets 50 us (300 by k_rowcol_ent, whose item
-// reads one segment per link bucket), whole calls 451 -> 186 us; one window of
+// Counts of 64 windows of 2^17 packets 48 us (300 by k_rowcol_ent, whose item
+// reads one segment per link bucket), whole calls 451 -> 179 us; one window of
 // 2000 packets 46 -> 31, so every window above small_max takes the grid.
 // ---------------------------------------------------------------------------
 

@@ -101,7 +101,7 @@ constexpr int kFinerMost = 2;
 // The kernel of a grid window's phase B (0 SMALL, 1 BIG, 2 WIDE): a 2048-slot
 // table would be more than half full above 1280 packets per cell, and above 4096
 // BIG would leave most cells to WIDE after a reading of its own (one window of
-// 1.2 * 10^7 packets among 4096 addresses 0.77 -> 0.71 ms without it).
+// 1.2 * 10^7 packets among 4096 addresses 0.74 -> 0.69 ms without it).
 int grid_kind(const nsgc_grid_desc& g) {
   const uint32_t cells = g.logA + g.logBc;
   return g.n > uint64_t(NSGC_GRID_BIG_KEYS) << cells ? 2 : g.n >> cells > NSGC_GRID_SMALL_CELLS ? 1 : 0;
