@@ -777,7 +777,7 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
 
   uint32_t links = 0, mx = 0;
   const uint32_t most = sload(&P->gmax_keys);
-  bool abandoned = most && total > most;
+  bool abandoned = most && total / 16 > most;
   uint32_t special = 0;
   const uint32_t max_rounds = 1u << min(sload(&P->max_sweeps_log2), 24u);
   auto seg = [&](uint32_t t, u64& base, uint32_t& len) {
@@ -839,7 +839,7 @@ __global__ __launch_bounds__(GR_NT) void k_grid_rounds(nsgc_dev_plan* P, uint32_
     const bool failed = misc[0] != 0;
     if (failed && round == 0 && (total > GR_KEYS || total > GR_ROUNDS * fill[1])) {
       // (it stands for GR_ROUNDS rounds where their number is limited)
-      if (max_rounds <= GR_ROUNDS) { abandoned = true; break; }
+      if (max_rounds <= GR_ROUNDS || (most && total > most)) { abandoned = true; break; }
       sort_cell<NT>(total, er, ec, reinterpret_cast<uint32_t*>(tk), [&](const auto& fn) {
         for (uint32_t t = uniform(tid >> 6); t < nt; t += NW) {
           u64 base;

@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256) void k_large_init(Args A) {
     p->gitemsW = p->gitemsB = A.cells;
     p->gtile_log2 = TILE_LOG2;
     p->max_sweeps_log2 = 5;
-    p->gmax_keys = 1u << 18;   // (more take longer than sorting the window)
+    p->gmax_keys = 1u << 18;   // (sorting more takes one workgroup longer than all of them the window)
     p = A.whole;
     p->gwin = A.win + OUT;
     p->gitemC = A.itemC;

@@ -270,7 +270,8 @@ struct nsgc_dev_plan {          // header of the device plan buffer
   uint32_t gover[4];
   // cells: SMALL's up to gitemsS, BIG's up to gitemsW, WIDE's up to gitemsB
   uint32_t num_grid, gitemsA, gitemsS, gitemsW, gitemsB, gitemsC, gtile_log2;
-  uint32_t gmax_keys;           // a cell of more keys is abandoned (0: none is)
+  uint32_t gmax_keys;           // a cell of more keys is not sorted but abandoned, one of 16
+                                //   times as many not even read (0: any is finished)
   // Upload: 16-byte units of the header and the lists behind it, and of the
   // work-queue counters behind those, which the upload clears.
   uint32_t upload16, clear16;

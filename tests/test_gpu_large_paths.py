@@ -49,6 +49,14 @@ def test_ordinary_traffic_is_partitioned(n, draw):
     assert taken(draw(rng, n), draw(rng, n), draw.__name__) == (1, 0)
 
 
+def test_links_of_many_packets():
+    # a hundred links of 3.4 * 10^5 packets each, more of them than there are
+    # dominant addresses: cells of a few links and very many keys
+    n = (1 << 25) + 3
+    i = (np.arange(n) % 100).astype(np.uint32)
+    assert taken(i * np.uint32(7), i + np.uint32(5000), "a hundred links") == (1, 0)
+
+
 def test_fixed_scratch_and_plain_forms():
     rng = np.random.default_rng(1)
     src, dst = heavy_tailed(rng, 1 << 20), heavy_tailed(rng, 1 << 20)
