@@ -18,11 +18,11 @@
 //
 // Measured against that path, whole calls: 64 windows of 2^17 packets 237 ->
 // 202 us; one of 40013 packets 58 -> 39 us; nine of 2^12 .. 2^22 packets 434 ->
-// 171 us; 512 of 2^10 .. 2^23 packets 11.5 -> 7.1 ms; 128 of 2^23 14.2 -> 9.5
+// 165 us; 512 of 2^10 .. 2^23 packets 11.5 -> 7.1 ms; 128 of 2^23 14.2 -> 9.5
 // ms; one of 2^20 with all addresses distinct 680 -> 128 us, among 4096 152 ->
-// 92.  Slower is a window of 2^20 to 2^22 packets among a hundred to a thousand
+// 92.  Slower is a window of 2^20 to 2^22 packets among 65 to a thousand
 // addresses, whose few links one link bucket per range counts in fewer launches
-// (one of 2^20 among 300 56 -> 85 us, eight 150 -> 178; among 2000 150 -> 94).
+// (one of 2^20 among 300 56 -> 85 us, eight 150 -> 176; among 2000 150 -> 94).
 // Windows of up to 2^13 packets have one workgroup each.
 #include <hip/hip_runtime.h>
 
@@ -1272,7 +1272,7 @@ __device__ __forceinline__ void clear_id_table(uint32_t tid, u64* tv, uint32_t* 
 }
 
 // What phase-C item k of a window is: one of the items of the dominant
-// addresses (`heavy`: 1 sources, 2 destinations, 16 of them from slot `sub`;
+// addresses (`heavy`: 1 sources, 2 destinations, a few of them from slot `sub`;
 // 3 the links between them; first in the window, since they are chains of
 // loads), row buckets, or column buckets (1 << group of them, neighbours in one
 // strip).
@@ -1282,7 +1282,8 @@ struct BucketItem {
 __device__ __forceinline__ BucketItem bucket_item(const nsgc_grid_desc& W, uint32_t HV, uint32_t k) {
   BucketItem B;
   const uint32_t R = 1u << W.logRi, H = NSGC_GRID_CITEMS(HV) - 1u;
-  B.heavy = k > H ? 0u : k == H ? 3u : 1u + k / (HV / 16);
+  B.heavy = k > H ? 0u : k == H ? 3u : 1u + k / (H / 2u);
+  const uint32_t of_view = k % (H / 2u);
   k -= B.heavy ? 0u : H + 1u;
   B.row = k < R;
   if (!B.row) k -= R;
@@ -1291,7 +1292,7 @@ __device__ __forceinline__ BucketItem bucket_item(const nsgc_grid_desc& W, uint3
   B.group = (B.row ? W.logR : W.logC) - items;
   B.strip = k >> (items - strips);
   B.sub = (k << B.group) & ((1u << (items - strips + B.group)) - 1u);
-  if (B.heavy) B.sub = (k % (HV / 16)) * 16u;
+  if (B.heavy) B.sub = of_view << NSGC_GRID_HV_ITEM_LOG2(HV);
   B.nseg = B.row ? 1u << W.logBc : 1u << W.logA;   // cells of the strip
   B.word = (B.row ? 1u : 2u + (1u << (W.logR - W.logA))) + B.sub;   // its first start in a cell record
   return B;
@@ -1493,24 +1494,28 @@ __global__ __launch_bounds__(GC_NT) __attribute__((amdgpu_waves_per_eu(6))) void
         }
         block_sum2_max_to0<NW>(n, mp, ml, red);
       } else {        // dominant sources (destinations): the cells' counters and the matrix
+        const uint32_t G = 1u << NSGC_GRID_HV_ITEM_LOG2(HV), stride = NT >> NSGC_GRID_HV_ITEM_LOG2(HV);
         u64* sum = tv;
-        const uint32_t s = B.sub + (tid & 15u), g = tid >> 4;
+        const uint32_t s = B.sub + (tid & (G - 1u)), g = tid >> NSGC_GRID_HV_ITEM_LOG2(HV);
         const uint32_t cells = 1u << W.logP;
         const NSGC_GLOBAL u64* acc = gptr(W.acc) + k * HV + s;
         u64 x = 0;
 #pragma unroll 16
-        for (uint32_t cell = g; cell < cells; cell += NT / 16) x += acc[u64(cell) * (2 * HV)];
-        for (uint32_t o = g; o < HV; o += NT / 16) {
+        for (uint32_t cell = g; cell < cells; cell += stride) x += acc[u64(cell) * (2 * HV)];
+        for (uint32_t o = g; o < HV; o += stride) {
           const uint32_t y = k == 0 ? m[s * HV + o] : m[o * HV + s];
           x += (u64(y ? 1u : 0u) << 32) | y;
         }
         sum[tid] = x;
         lds_barrier();
-        if (tid < 16) {
-          for (uint32_t o = 1; o < NT / 16; ++o) x += sum[o * 16 + tid];
-          n = (x >> 32) ? 1u : 0u;
-          mp = uint32_t(x);
-          ml = uint32_t(x >> 32);
+        if (tid < 64) {
+          for (uint32_t o = 1; o < NW; ++o) x += sum[o * 64 + tid];
+          for (uint32_t o = G; o < 64; o *= 2) x += __shfl_xor(x, int(o));
+          if (tid < G) {
+            n = (x >> 32) ? 1u : 0u;
+            mp = uint32_t(x);
+            ml = uint32_t(x >> 32);
+          }
         }
         block_sum_max2_to0<NW>(n, mp, ml, red);
       }

@@ -138,9 +138,15 @@
 #define NSGC_GRID_MAX_SUB_LOG2 6               // row or column buckets per strip
 #define NSGC_GRID_MAX_SUB (1 << NSGC_GRID_MAX_SUB_LOG2)
 #define NSGC_GRID_BUCKET 4096                  // packets per row or column bucket, at most
-// Phase-C items of a window's dominant addresses: 16 of one view each, and one
-// for the links between them.
-#define NSGC_GRID_CITEMS(hv) ((hv) / 8 + 1)
+// Phase-C items of a window's dominant addresses: HV_ITEM of one view each, and
+// one for the links between them.  An item reads its addresses' counters of every
+// cell, a chain of loads that the window waits for where there are many cells
+// (one window of 2^21 packets among 65 addresses: 25 us in k_grid_rowcol with 16
+// per item, 15 with 8, 10 with 4; nine of 2^12 .. 2^22 packets 170 us in all, 164
+// and 164), and in batches of smaller ones more items cost more (64 of 2^17 in
+// 202 us with 16 per item, 203 with 8 and 207 with 4; others up to 2% with 8).
+#define NSGC_GRID_HV_ITEM_LOG2(hv) ((hv) == 64 ? 3 : 4)
+#define NSGC_GRID_CITEMS(hv) (2 * ((hv) >> NSGC_GRID_HV_ITEM_LOG2(hv)) + 1)
 // Words of a window's dominant-address block: the ids of both views, the matrix,
 // the lookup shift of each view.
 #define NSGC_GRID_HV_WORDS(hv) (2 * (hv) + (hv) * (hv) + 2)

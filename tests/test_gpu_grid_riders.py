@@ -32,6 +32,8 @@ def packets(rng, n):
     [1025, 8193], [8193, 2047, 2048, 2049, 4095, 4096, 4097, 8192], [1024, 8193, 1025, 4097],
     [0, 8193, 1025], [8193] + [1100] * 256, [8193] + [1100] * 257, [8193] + [4097] * 250 + [2000] * 7,
     [1500000, 1300, 3000], [1 << 21, 5000, 2000],
+    # fewer row buckets than items for the dominant addresses
+    [1 << 21, 9282, 17342, 40013],
 ])
 @pytest.mark.parametrize("small_max", [1024, 2048])
 def test_riders(sizes, small_max):
